@@ -110,14 +110,15 @@ typedef struct {
     int32_t scheme;       /* sph_scheme */
     int32_t integrator;   /* sph_integrator (sph_step only); EULER needs the
                            * continuity scheme */
-    int32_t pair_tiles;   /* 3D mixed-precision summation passes (Section
+    int32_t pair_tiles;   /* 3D summation passes (Section
                            * 2.2's cell grid cut into boxes whose particles
                            * and neighbour cells are staged in on-chip
                            * memory): 0 = used where they apply on grids with
                            * at least one particle per cell on average
                            * (default), < 0 = never (lists read from global
                            * memory), k > 0 = used wherever they apply, with at
-                           * most k staged particles per box (3072 at most;
+                           * most k staged particles per box (3072 at most,
+                           * 1920 in FP64;
                            * larger boxes take the cell walk).  Results do not
                            * depend on it. */
     int32_t cell_order;   /* sort key of the cells (Section 2.2): 0 = row-major,

@@ -97,7 +97,7 @@ def _rc(code: int):
 def make_params(p, precision: int = FP64, nbr_cap: int = 0, pair_tiles: int = 0) -> Params:
     """C parameter struct from a sph_workloads.Params-like object.  nbr_cap:
     neighbour-list capacity per particle (0 default, < 0 cell walks only);
-    pair_tiles: LDS-staged tiles of the 3D mixed-precision passes (0 where
+    pair_tiles: LDS-staged tiles of the 3D summation passes (0 where
     they apply, < 0 never, k > 0 at most k staged particles per tile)."""
     c = Params()
     c.dim, c.kernel, c.precision, c.cell_div = p.dim, p.kernel, precision, p.cell_div

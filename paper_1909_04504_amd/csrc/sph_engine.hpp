@@ -264,8 +264,34 @@ inline uint32_t list_cap(const sph_params* p, int64_t n) {
     return p->dim == 2 ? 64u : 192u;
 }
 
-// Tiles of the 3D mixed-precision summation passes (ntiles = 0: not used).
-// Boxes of 6 x 6 x 4 cells with half-size cells (about 490 targets for the
+// Box of the FP64 tiles: the first of a list (by the share of the union that
+// is targets) whose union is expected to fit the staging with 8% to spare.
+// The expected particles per cell are the grid's mean where every axis is
+// periodic (the fluid fills the box); elsewhere a tank may be partly empty,
+// and at least those of a lattice at h = 1.5 dx are assumed.
+// False: no box fits.
+inline bool box64(const sph_params* p, const sph::Grid& G, double occ, sph::Tiles* T) {
+    static const int half[][3] = {{4, 4, 4}, {4, 4, 3}, {4, 4, 2}, {4, 3, 2}, {3, 3, 2}, {2, 2, 2}};
+    static const int whole[][3] = {{4, 2, 2}, {3, 2, 2}, {2, 2, 2}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
+    if (!(p->periodic[0] && p->periodic[1] && p->periodic[2])) {
+        double lattice = 1.0;
+        for (int k = 0; k < 3; ++k) lattice *= G.cs[k] / (p->h / 1.5);
+        occ = std::max(occ, lattice);
+    }
+    for (int b = 0; b < 6; ++b) {
+        const int* t = T->S == 2 ? half[b] : whole[b];
+        const int cells = (t[0] + 2 * T->S) * (t[1] + 2 * T->S) * (t[2] + 2 * T->S);
+        if (1.08 * occ * cells > (double)sph::CfgD::kCap) continue;
+        T->tw = t[0];
+        T->th = t[1];
+        T->td = t[2];
+        return true;
+    }
+    return false;
+}
+
+// Tiles of the 3D summation passes (ntiles = 0: not used).  Mixed precision:
+// boxes of 6 x 6 x 4 cells with half-size cells (about 490 targets for the
 // 512 threads; a union of 10 x 10 x 8 cells, about 2,700 particles on the
 // 256^3 lattice at h = 1.5 dx; measured against 8 x 4 x 4, 4 x 6 x 6,
 // 6 x 4 x 6, 7 x 5 x 4 and 8 x 6 x 3 boxes: 13.6 against 14.5, 13.8, 13.7,
@@ -279,14 +305,19 @@ inline uint32_t list_cap(const sph_params* p, int64_t n) {
 inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells) {
     sph::Tiles T;
     std::memset(&T, 0, sizeof T);
-    if (p->dim != 3 || p->precision != SPH_FP32_MIXED || p->scheme != SPH_SCHEME_SUMMATION ||
-        p->pair_tiles < 0 || list_cap(p, n) < 8)
+    if (p->dim != 3 || p->scheme != SPH_SCHEME_SUMMATION || p->pair_tiles < 0 ||
+        list_cap(p, n) < 8)
         return T;
     if (p->pair_tiles == 0 && n < ncells) return T;
+    const bool f64 = p->precision == SPH_FP64;
+    const int cfg_cap = f64 ? sph::CfgD::kCap : sph::CfgF::kCap;
+    const double occ = (double)n / (double)ncells;
     T.S = G.S;
-    if (T.S == 2) {
+    if (f64) {
+        if (!box64(p, G, occ, &T)) return T;
+    } else if (T.S == 2) {
         T.tw = 6; T.th = 6; T.td = 4;
-    } else if ((double)n / (double)ncells <= 19.0) {
+    } else if (occ <= 19.0) {
         T.tw = 4; T.th = 4; T.td = 2;
     } else {
         T.tw = 2; T.th = 2; T.td = 2;
@@ -310,10 +341,11 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
     const double R = support_radius(p);
     T.rclip2 = (float)(R * R * (1.0 + 1e-4));
     T.clip_pad = (float)(1e-4 * std::min(G.cs[0], std::min(G.cs[1], G.cs[2])));
-    T.cap = p->pair_tiles > 0 ? std::min(p->pair_tiles, sph::kTileCap) : sph::kTileCap;
+    T.cap = p->pair_tiles > 0 ? std::min(p->pair_tiles, cfg_cap) : cfg_cap;
     if (nt > (int64_t)1 << 30 || T.uw > sph::kTileUnionAxisMax || T.uh > sph::kTileUnionAxisMax ||
-        T.ud > sph::kTileUnionAxisMax || T.uw * T.uh * T.ud > sph::kTileCellsMax ||
-        T.tw * T.th * T.td > sph::kTileTargetCellsMax) {
+        T.ud > sph::kTileUnionAxisMax ||
+        T.uw * T.uh * T.ud > (f64 ? sph::CfgD::kCells : sph::CfgF::kCells) ||
+        T.tw * T.th * T.td > (f64 ? sph::CfgD::kTCells : sph::CfgF::kTCells)) {
         std::memset(&T, 0, sizeof T);
         return T;
     }
@@ -738,8 +770,10 @@ struct Engine {
     }
     const uint32_t* list_or_null() const { return L.cap ? list() : nullptr; }
 
-    // --- LDS-tiled passes (3D mixed precision, summation scheme) -----------
-    static constexpr bool kTileable = DIM == 3 && std::is_same<T, float>::value;
+    // --- LDS-tiled passes (3D, summation scheme) ----------------------------
+    static constexpr bool kTileable = DIM == 3;
+    static constexpr bool kF64 = sizeof(T) == 8;
+    using Cfg = typename sph::TileCfgOf<T>::type;
     bool tiled() const { return kTileable && L.tiles.ntiles > 0; }
     uint32_t tcap() const { return L.cap & ~7u; }
     uint32_t* fbword() const { return (uint32_t*)(ws + L.flags + 4); }
@@ -753,29 +787,36 @@ struct Engine {
             tile_epoch = next_tile_epoch();
             const sph::Tiles TL = L.tiles;
             with_reach([&](auto R) {
-                launch_b(K_TILE_BUILD, sph::k_tile_build<decltype(R)::value>, (unsigned)TL.ntiles,
-                         sph::kTileThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
-                         (uint4*)list(), lcnt(), count_pairs ? 1 : 0, pairs(), tile_epoch,
+                launch_b(K_TILE_BUILD, sph::k_tile_build<decltype(R)::value, T>,
+                         (unsigned)TL.ntiles, Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce,
+                         tcap(), (uint4*)list(), lcnt(), count_pairs ? 1 : 0, pairs(), tile_epoch,
                          fbword());
             });
             SPH_TRY(launch_check("k_tile_build"));
             if (!with_density) return SPH_OK;
             with_reach([&](auto R) {
-                launch_b(K_TILE_DENSITY, sph::k_tile_density<decltype(R)::value, KERNEL>,
-                         (unsigned)TL.ntiles, sph::kTileThreads, st, n, G, C, TL, TL.cap, pos(), cs,
-                         ce, tcap(), (const uint4*)list(), lcnt(), (float*)s.rho, (float*)s.p,
-                         vel(), rp(), with_eos ? 1 : 0);
+                constexpr int S = decltype(R)::value;
+                if constexpr (kF64)
+                    launch_b(K_TILE_DENSITY, sph::k_tile_density64<S, KERNEL>, (unsigned)TL.ntiles,
+                             Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
+                             (const uint4*)list(), lcnt(), (double*)s.rho, (double*)s.p, vel(), rp(),
+                             with_eos ? 1 : 0);
+                else
+                    launch_b(K_TILE_DENSITY, sph::k_tile_density<S, KERNEL>, (unsigned)TL.ntiles,
+                             Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
+                             (const uint4*)list(), lcnt(), (float*)s.rho, (float*)s.p, vel(), rp(),
+                             with_eos ? 1 : 0);
             });
             SPH_TRY(launch_check("k_tile_density"));
             with_reach([&](auto R) {
-                launch(K_TILE_FALLBACK, sph::k_tile_fallback_density<decltype(R)::value, KERNEL>,
+                launch(K_TILE_FALLBACK, sph::k_tile_fallback_density<decltype(R)::value, KERNEL, T>,
                        fallback_blocks(n), st, n, G, C, skey(), pos(), cs, ce, lcnt(), tcap(),
-                       (float*)s.rho, (float*)s.p, vel(), rp(), with_eos ? 1 : 0,
+                       (T*)s.rho, (T*)s.p, vel(), rp(), with_eos ? 1 : 0,
                        count_pairs ? 1 : 0, pairs(), tile_epoch, fbword());
             });
             return launch_check("k_tile_fallback_density");
         }
-        return fail(SPH_EINVAL, "tiled passes need 3D mixed precision");
+        return fail(SPH_EINVAL, "tiled passes need 3D");
     }
 
     // Tiled momentum of the targets with complete tile lists, then the
@@ -791,25 +832,33 @@ struct Engine {
             // wgs-th tile
             const unsigned wgs = std::min<unsigned>((unsigned)TL.ntiles, device_cus());
             with_reach([&](auto R) {
-                launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<decltype(R)::value, KERNEL>, wgs,
-                         sph::kTileThreads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
-                         cs, ce, tcap(), (const uint4*)list(), lcnt(), s, kick ? 1 : 0,
-                         drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(), part,
-                         stride);
+                constexpr int S = decltype(R)::value;
+                if constexpr (kF64)
+                    launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum64<S, KERNEL>, (unsigned)TL.ntiles,
+                             Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
+                             cs, ce, tcap(), (const uint4*)list(), lcnt(), s, kick ? 1 : 0,
+                             drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(), part,
+                             stride);
+                else
+                    launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<S, KERNEL>, wgs, Cfg::kThreads,
+                             st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type, cs, ce, tcap(),
+                             (const uint4*)list(), lcnt(), s, kick ? 1 : 0, drift ? 1 : 0,
+                             0.5 * prm->dt, prm->dt, key(), counts(), flags(), part, stride);
             });
             SPH_TRY(launch_check("k_tile_momentum"));
             with_reach([&](auto R) {
-                launch(K_TILE_FALLBACK, sph::k_tile_fallback_momentum<decltype(R)::value, KERNEL>,
-                       fb, st, n, G, C, skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(),
-                       s, kick ? 1 : 0, drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(),
-                       flags(), part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword());
+                launch(K_TILE_FALLBACK,
+                       sph::k_tile_fallback_momentum<decltype(R)::value, KERNEL, T>, fb, st, n, G, C,
+                       skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(), s, kick ? 1 : 0,
+                       drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(),
+                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword());
             });
             SPH_TRY(launch_check("k_tile_fallback_momentum"));
             if (!diag_out) return SPH_OK;
             launch(K_DIAG, sph::k_diag_final<DIM>, 1, st, stride, part, diag_out);
             return launch_check("k_diag_final");
         }
-        return fail(SPH_EINVAL, "tiled passes need 3D mixed precision");
+        return fail(SPH_EINVAL, "tiled passes need 3D");
     }
 
     // Lists of the current records, then the density over them; without

@@ -1,4 +1,4 @@
-// LDS-staged cell tiles for the 3D mixed-precision pair passes.
+// LDS-staged cell tiles for the 3D pair passes (summation scheme).
 //
 // The cell grid (Sec. 2.2) is cut into boxes of tw x th x td cells.  A
 // workgroup takes one box: its targets are the particles of the box's cells,
@@ -38,11 +38,22 @@
 
 namespace sph {
 
-constexpr int kTileThreads = 512;                // 8 waves per workgroup
-constexpr int kTileCellsMax = 1024;              // union cells per tile (two per thread)
-constexpr int kTileTargetCellsMax = 160;         // target cells per tile
-constexpr int kTileCap = 3072;                   // union particles staged in LDS
+// Sizes of one pass's workgroup: threads (waves of 64) that set tiles up and
+// stage them, union cells (two per thread), target cells and staged particles
+// per tile.
+template <int THREADS, int CELLS, int TCELLS, int CAP>
+struct TileCfg {
+    static constexpr int kThreads = THREADS, kCells = CELLS, kTCells = TCELLS, kCap = CAP;
+    static_assert(CELLS <= 2 * THREADS && TCELLS <= THREADS, "cells per thread");
+};
+using CfgF = TileCfg<512, 1024, 160, 3072>;  // mixed precision
+using CfgD = TileCfg<256, 512, 64, 1920>;    // FP64
+template <typename T> struct TileCfgOf;
+template <> struct TileCfgOf<float> { using type = CfgF; };
+template <> struct TileCfgOf<double> { using type = CfgD; };
+constexpr int kTileCellsMax = 1024;              // of every configuration
 constexpr int kTileUnionAxisMax = 12;            // union cells per axis: 12 * 2^27 + 2^29 < 2^31
+template <bool B> struct BoolC { static constexpr bool value = B; };
 constexpr uint32_t kTileOverflow = 0xffffffffu;  // count of a target left to the fallback
 constexpr int kFallbackBlocks = 1024;            // grid of the fallback kernels (grid-stride)
 
@@ -82,21 +93,23 @@ __device__ __forceinline__ void union_coords(const Tiles& TL, int c, int uc[3]) 
 }
 
 // Per-workgroup bookkeeping in LDS.
+template <typename CFG>
 struct TileMeta {
-    uint32_t off[kTileCellsMax + 1];  // union index of each cell's first particle; off[ncu] = total
-    uint32_t gs[kTileCellsMax];       // global slot of each cell's first particle
-    uint32_t tpre[kTileTargetCellsMax + 1];  // targets before each target cell
-    int tc[kTileTargetCellsMax];             // union index of each target cell
+    uint32_t off[CFG::kCells + 1];  // union index of each cell's first particle; off[ncu] = total
+    uint32_t gs[CFG::kCells];       // global slot of each cell's first particle
+    uint32_t tpre[CFG::kTCells + 1];  // targets before each target cell
+    int tc[CFG::kTCells];             // union index of each target cell
     int ntcells;
     uint32_t total, ntargets;
-    uint32_t wsum[kTileThreads / 64];
+    uint32_t wsum[CFG::kThreads / 64];
 };
 
 // Exclusive scan of two counts per thread (cells 2t, 2t+1) over the
 // workgroup; returns the offset of cell 2t, total in *total.
-__device__ __forceinline__ uint32_t tile_scan2(uint32_t a, uint32_t b, TileMeta& M,
-                                               uint32_t* total) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+template <typename CFG>
+__device__ __forceinline__ uint32_t tile_scan2(uint32_t a, uint32_t b, TileMeta<CFG>& M,
+                                               uint32_t* total, int tid) {
+    const int lane = tid & 63, w = tid >> 6;
     const uint32_t v = a + b;
     uint32_t incl = v;
 #pragma unroll
@@ -108,7 +121,7 @@ __device__ __forceinline__ uint32_t tile_scan2(uint32_t a, uint32_t b, TileMeta&
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
-    for (int k = 0; k < kTileThreads / 64; ++k) {
+    for (int k = 0; k < CFG::kThreads / 64; ++k) {
         before += k < w ? M.wsum[k] : 0u;
         all += M.wsum[k];
     }
@@ -178,12 +191,13 @@ __device__ __forceinline__ void keep_in_flight(V& v) {
 __device__ __forceinline__ SetupLoads tile_setup_loads(const Grid& G, const Tiles& TL,
                                                        const int c0[3],
                                                        const uint32_t* __restrict__ cstart,
-                                                       const uint32_t* __restrict__ cend) {
+                                                       const uint32_t* __restrict__ cend,
+                                                       int tid) {
     const int ncu = TL.uw * TL.uh * TL.ud;
     SetupLoads r;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const int c = 2 * (int)threadIdx.x + q;
+        const int c = 2 * tid + q;
         r.s[q] = r.e[q] = 0;
         r.in[q] = false;
         if (c < ncu) {
@@ -204,14 +218,16 @@ __device__ __forceinline__ SetupLoads tile_setup_loads(const Grid& G, const Tile
     return r;
 }
 // Returns the number of union particles (every thread).
+template <typename CFG>
 __device__ __forceinline__ uint32_t tile_setup_finish(const Grid& G, const Tiles& TL,
                                                       const int c0[3], int n,
-                                                      const SetupLoads& r, TileMeta& M) {
+                                                      const SetupLoads& r, TileMeta<CFG>& M,
+                                                      int tid) {
     const int ncu = TL.uw * TL.uh * TL.ud;
     uint32_t cnt[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const int c = 2 * (int)threadIdx.x + q;
+        const int c = 2 * tid + q;
         cnt[q] = 0;
         if (c < ncu) {
             uint32_t s = 0;
@@ -224,13 +240,13 @@ __device__ __forceinline__ uint32_t tile_setup_finish(const Grid& G, const Tiles
         }
     }
     uint32_t total;
-    const uint32_t o = tile_scan2(cnt[0], cnt[1], M, &total);
+    const uint32_t o = tile_scan2(cnt[0], cnt[1], M, &total, tid);
     {
-        const int c = 2 * (int)threadIdx.x;
+        const int c = 2 * tid;
         if (c < ncu) M.off[c] = o;
         if (c + 1 < ncu) M.off[c + 1] = o + cnt[0];
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         M.off[ncu] = total;
         M.total = total;
     }
@@ -242,11 +258,11 @@ __device__ __forceinline__ uint32_t tile_setup_finish(const Grid& G, const Tiles
     const int thc = min(TL.th, G.nc[1] - c0[1]);
     const int tdc = min(TL.td, G.nc[2] - c0[2]);
     const int ntc = twc * thc * tdc;
-    const int rr = (int)threadIdx.x;
+    const int rr = tid;
     uint32_t tcnt = 0;
     int tcell = 0;
     if (rr < ntc) {
-        // rr < kTileTargetCellsMax, twc thc <= 144: exact FP32 quotients
+        // rr < kTCells, twc thc <= 144: exact FP32 quotients
         const int z = small_quot(rr, __builtin_amdgcn_rcpf((float)(twc * thc)));
         const int rem = rr - z * (twc * thc);
         const int y = small_quot(rem, __builtin_amdgcn_rcpf((float)twc));
@@ -255,12 +271,12 @@ __device__ __forceinline__ uint32_t tile_setup_finish(const Grid& G, const Tiles
         tcnt = M.off[tcell + 1] - M.off[tcell];
     }
     uint32_t ntargets;
-    const uint32_t tpre = tile_scan2(tcnt, 0u, M, &ntargets);
+    const uint32_t tpre = tile_scan2(tcnt, 0u, M, &ntargets, tid);
     if (rr < ntc) {
         M.tc[rr] = tcell;
         M.tpre[rr] = tpre;
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         M.tpre[ntc] = ntargets;
         M.ntcells = ntc;
         M.ntargets = ntargets;
@@ -268,15 +284,17 @@ __device__ __forceinline__ uint32_t tile_setup_finish(const Grid& G, const Tiles
     __syncthreads();
     return total;
 }
+template <typename CFG>
 __device__ __forceinline__ uint32_t tile_setup(const Grid& G, const Tiles& TL, const int c0[3],
                                                const uint32_t* __restrict__ cstart,
                                                const uint32_t* __restrict__ cend, int n,
-                                               TileMeta& M) {
-    return tile_setup_finish(G, TL, c0, n, tile_setup_loads(G, TL, c0, cstart, cend), M);
+                                               TileMeta<CFG>& M, int tid) {
+    return tile_setup_finish(G, TL, c0, n, tile_setup_loads(G, TL, c0, cstart, cend, tid), M, tid);
 }
 
 // Target t of the tile: its union index, global slot and union cell coords.
-__device__ __forceinline__ void tile_target(const Tiles& TL, const TileMeta& M, uint32_t t,
+template <typename CFG>
+__device__ __forceinline__ void tile_target(const Tiles& TL, const TileMeta<CFG>& M, uint32_t t,
                                             uint32_t* ui, uint32_t* gi, int uc[3]) {
     // the target cell: the last r with tpre[r] <= t (binary search)
     int lo = 0, hi = M.ntcells;
@@ -292,10 +310,12 @@ __device__ __forceinline__ void tile_target(const Tiles& TL, const TileMeta& M, 
 }
 
 // Marks every target of the tile for the fallback (its union does not fit).
-__device__ __forceinline__ void tile_mark_overflow(const TileMeta& M, uint32_t* __restrict__ ncnt) {
+template <typename CFG>
+__device__ __forceinline__ void tile_mark_overflow(const TileMeta<CFG>& M,
+                                                   uint32_t* __restrict__ ncnt) {
     for (int r = 0; r < M.ntcells; ++r) {
         const uint32_t len = M.tpre[r + 1] - M.tpre[r];
-        for (uint32_t k = threadIdx.x; k < len; k += kTileThreads)
+        for (uint32_t k = threadIdx.x; k < len; k += CFG::kThreads)
             ncnt[M.gs[M.tc[r]] + k] = kTileOverflow;
     }
 }
@@ -303,44 +323,48 @@ __device__ __forceinline__ void tile_mark_overflow(const TileMeta& M, uint32_t* 
 // Stages the union's records: store(u, load(j), ux, uy, uz) for union
 // particle u held in global slot j of union cell (ux, uy, uz).  The cell of
 // every union index is noted first (tile_cellof), so that each thread then
-// loads its particles at indices t, t + 512, ... with all loads in flight
-// (tile_stage_loads; kTileCap <= 8 * kTileThreads: a single round) and
-// stores them (tile_stage_store).  cellof: kTileCap entries of LDS, the
-// union cell of each staged particle.
-__device__ __forceinline__ void tile_cellof(const Tiles& TL, const TileMeta& M,
+// loads its particles at indices t, t + kThreads, ... with all loads in flight
+// (tile_stage_loads; kCap <= 8 kThreads: a single round) and
+// stores them (tile_stage_store).  cellof: kCap entries of LDS, the
+// union cell of each staged particle (left unset when the union does not
+// fit).
+template <typename CFG>
+__device__ __forceinline__ void tile_cellof(const Tiles& TL, const TileMeta<CFG>& M,
                                             uint16_t* cellof) {
     const int ncu = TL.uw * TL.uh * TL.ud;
-    for (int c = threadIdx.x; c < ncu; c += kTileThreads)
-        for (uint32_t u = M.off[c]; u < M.off[c + 1]; ++u) cellof[u] = (uint16_t)c;
+    if (M.total <= (uint32_t)CFG::kCap)
+        for (int c = threadIdx.x; c < ncu; c += CFG::kThreads)
+            for (uint32_t u = M.off[c]; u < M.off[c + 1]; ++u) cellof[u] = (uint16_t)c;
     __syncthreads();
 }
-constexpr int kStageQ = (kTileCap + kTileThreads - 1) / kTileThreads;
-static_assert(kStageQ <= 8, "staging registers");
-template <typename P>
+template <typename CFG, typename P>
 struct StageRegs {
-    P v[kStageQ];
+    static constexpr int kQ = (CFG::kCap + CFG::kThreads - 1) / CFG::kThreads;
+    static_assert(kQ <= 8, "staging registers");
+    P v[kQ];
 };
-template <typename P, typename Load>
-__device__ __forceinline__ void tile_stage_loads(const TileMeta& M, const uint16_t* cellof,
-                                                 Load&& load, StageRegs<P>& R) {
+template <typename CFG, typename P, typename Load>
+__device__ __forceinline__ void tile_stage_loads(const TileMeta<CFG>& M, const uint16_t* cellof,
+                                                 Load&& load, StageRegs<CFG, P>& R, int tid) {
     const uint32_t total = M.total;
 #pragma unroll
-    for (int q = 0; q < kStageQ; ++q) {
-        const uint32_t u = threadIdx.x + (uint32_t)q * kTileThreads;
+    for (int q = 0; q < StageRegs<CFG, P>::kQ; ++q) {
+        const uint32_t u = (uint32_t)(tid + q * CFG::kThreads);
         if (u < total) {
             const int c = cellof[u];
             R.v[q] = load(M.gs[c] + (u - M.off[c]));
         }
     }
 }
-template <typename P, typename Store>
-__device__ __forceinline__ void tile_stage_store(const Tiles& TL, const TileMeta& M,
-                                                 const uint16_t* cellof, const StageRegs<P>& R,
-                                                 Store&& store) {
+template <typename CFG, typename P, typename Store>
+__device__ __forceinline__ void tile_stage_store(const Tiles& TL, const TileMeta<CFG>& M,
+                                                 const uint16_t* cellof,
+                                                 const StageRegs<CFG, P>& R, Store&& store,
+                                                 int tid) {
     const uint32_t total = M.total;
 #pragma unroll
-    for (int q = 0; q < kStageQ; ++q) {
-        const uint32_t u = threadIdx.x + (uint32_t)q * kTileThreads;
+    for (int q = 0; q < StageRegs<CFG, P>::kQ; ++q) {
+        const uint32_t u = (uint32_t)(tid + q * CFG::kThreads);
         if (u < total) {
             int uc[3];
             union_coords(TL, cellof[u], uc);
@@ -348,14 +372,15 @@ __device__ __forceinline__ void tile_stage_store(const Tiles& TL, const TileMeta
         }
     }
 }
-template <typename Load, typename Store>
-__device__ __forceinline__ void tile_stage(const Tiles& TL, TileMeta& M, uint16_t* cellof,
+template <typename CFG, typename Load, typename Store>
+__device__ __forceinline__ void tile_stage(const Tiles& TL, TileMeta<CFG>& M, uint16_t* cellof,
                                            Load&& load, Store&& store) {
     tile_cellof(TL, M, cellof);
     using P = decltype(load(0u));
-    StageRegs<P> R;
-    tile_stage_loads(M, cellof, load, R);
-    tile_stage_store(TL, M, cellof, R, store);
+    StageRegs<CFG, P> R;
+    const int tid = (int)threadIdx.x;
+    tile_stage_loads(M, cellof, load, R, tid);
+    tile_stage_store(TL, M, cellof, R, store, tid);
 }
 
 // Union-frame record: cell-relative fixed point plus the union cell times 2^27.
@@ -434,10 +459,10 @@ __device__ __forceinline__ void tile_list_loop(const uint4* __restrict__ list, u
 
 // Per-thread FP64 values summed over the workgroup (wave butterflies, then
 // the waves in order) into part[q * stride + b].
-template <int NV>
+template <int NV, int NT>
 __device__ __forceinline__ void tile_block_sum(double v[NV], double* __restrict__ part, int b,
                                                int stride) {
-    __shared__ double sh[NV][kTileThreads / 64];
+    __shared__ double sh[NV][NT / 64];
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         double x = v[q];
@@ -451,81 +476,171 @@ __device__ __forceinline__ void tile_block_sum(double v[NV], double* __restrict_
     if (threadIdx.x == 0)
         for (int q = 0; q < NV; ++q) {
             double s = 0.0;
-            for (int w = 0; w < kTileThreads / 64; ++w) s += sh[q][w];
+            for (int w = 0; w < NT / 64; ++w) s += sh[q][w];
             part[(int64_t)q * stride + b] = s;
         }
 }
 
 // Workgroup sum of a per-thread count into the tile's interaction counter.
+template <int NT>
 __device__ __forceinline__ void tile_count(uint32_t cnt, unsigned long long* __restrict__ pairs,
                                            int blk) {
-    __shared__ uint32_t wc[kTileThreads / 64];
+    __shared__ uint32_t wc[NT / 64];
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
     if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = cnt;
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long t = 0;
-        for (int w = 0; w < kTileThreads / 64; ++w) t += wc[w];
+        for (int w = 0; w < NT / 64; ++w) t += wc[w];
         add_pairs(pairs, blk, t);
     }
+}
+
+// Float copy of a staged record, relative to the centre of the union's cell
+// TL.cen, for the build's filter (w: the particle's union cell).  FP64
+// records are absolute: w L moves one to the image of its union cell (w grid
+// lengths away) and the union centre is subtracted before the conversion, so
+// that the copy's error is below a tenth of the filter's band as in mixed
+// precision.  *far: more than 4 cells outside its cell (a particle clamped
+// into an edge cell from far outside, or not finite; mixed-precision records
+// are clamped there): the copy is not accurate enough then, and the tile is
+// left to the fallback.
+__device__ __forceinline__ float4 filt_copy(const int4& r, const int uc[3], const int[3],
+                                            const Grid&, const Tiles& TL,
+                                            const PairConst<float>& C, bool*) {
+    const int4 p = tile_rec(r, uc[0], uc[1], uc[2]);
+    float4 f;
+    f.x = (float)(p.x - TL.cen[0] * (1 << kFixBits)) * C.fix_scale_f[0];
+    f.y = (float)(p.y - TL.cen[1] * (1 << kFixBits)) * C.fix_scale_f[1];
+    f.z = (float)(p.z - TL.cen[2] * (1 << kFixBits)) * C.fix_scale_f[2];
+    return f;
+}
+__device__ __forceinline__ float4 filt_copy(const double4& r, const int uc[3], const int c0[3],
+                                            const Grid& G, const Tiles& TL,
+                                            const PairConst<double>&, bool* far) {
+    const double x[3] = {r.x, r.y, r.z};
+    float f[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        // grid lengths between the union cell and its cell inside the grid
+        int w = 0, c = c0[k] - TL.S + uc[k];
+        while (c < 0) { c += G.nc[k]; --w; }
+        while (c >= G.nc[k]) { c -= G.nc[k]; ++w; }
+        const double centre =
+            G.lo[k] + ((double)(c0[k] - TL.S + TL.cen[k]) + 0.5) * G.cs[k];
+        f[k] = (float)((x[k] + (double)w * G.L[k]) - centre);
+        *far |= !(fabsf(f[k] - (float)(uc[k] - TL.cen[k]) * TL.csf[k]) <= 4.f * TL.csf[k]);
+    }
+    float4 o;
+    o.x = f[0];
+    o.y = f[1];
+    o.z = f[2];
+    return o;
+}
+// Periodic image of a tile's union cell coordinate u along axis k (the
+// stencil_axis wrap of every target that reaches it).
+__device__ __forceinline__ int tile_wrap(const Grid& G, int k, int c0, int u, int S) {
+    const int c = c0 - S + u;
+    return c < 0 ? -1 : (c >= G.nc[k] ? 1 : 0);
+}
+// Exact predicate of target record ri (global slot record of union cell ut)
+// and candidate record rj of union cell uj: the geometry of pair_geom.
+__device__ __forceinline__ bool tile_exact(const int4& ri, const int ut[3], const int4& rj,
+                                           const int uj[3], const int[3], const Grid&,
+                                           const Tiles&, const PairConst<float>& C) {
+    const Geom<float> g =
+        pair_geom<3>(tile_rec(ri, ut[0], ut[1], ut[2]), tile_rec(rj, uj[0], uj[1], uj[2]), 0, 0,
+                     0, 0, 0, 0, C);
+    return geom_r2d(g, C) < C.R2_d;
+}
+__device__ __forceinline__ bool tile_exact(const double4& ri, const int[3], const double4& rj,
+                                           const int uj[3], const int c0[3], const Grid& G,
+                                           const Tiles& TL, const PairConst<double>& C) {
+    const Geom<double> g =
+        pair_geom<3>(ri, rj, 0, 0, 0, tile_wrap(G, 0, c0[0], uj[0], TL.S),
+                     tile_wrap(G, 1, c0[1], uj[1], TL.S), tile_wrap(G, 2, c0[2], uj[2], TL.S), C);
+    return pair_accept(g, C);
+}
+// Whether a target lies inside its cell (its rows may then be clipped): the
+// fixed-point offset itself, or the float copy's (FP64; the margin is far
+// below the clip's).
+__device__ __forceinline__ bool tile_inside(const int4& r, const float4&, const int[3],
+                                            const Tiles&) {
+    const int half = 1 << (kFixBits - 1);
+    return abs(r.x) <= half && abs(r.y) <= half && abs(r.z) <= half;
+}
+__device__ __forceinline__ bool tile_inside(const double4&, const float4& f, const int uc[3],
+                                            const Tiles& TL) {
+    auto in = [&](float v, int k) {
+        return fabsf(v - (float)(uc[k] - TL.cen[k]) * TL.csf[k]) <= 0.50001f * TL.csf[k];
+    };
+    return in(f.x, 0) && in(f.y, 1) && in(f.z, 2);
 }
 
 // Neighbour lists of the tile's targets: ncnt[i] = |N(i)|, entries while the
 // count is within cap; targets with more are left to the fallback, as are all
 // targets of a tile whose union exceeds cap_union.  count_pairs: the
 // interactions of the counted targets go to the tile's counter.  Only the
-// float copy of the union is staged (so that two workgroups share a CU); the
-// exact predicate inside the band reads the candidate's record from global
+// float copy of the union is staged (so that several workgroups share a CU);
+// the exact predicate inside the band reads the candidate's record from global
 // memory.  Entries are appended without branches: every candidate is written
 // at the next free place of a 16-entry ring and the count advances only for
 // accepted ones; a completed octet is stored at once.
-template <int S>
-__global__ __launch_bounds__(kTileThreads) void k_tile_build(
-    int n, Grid G, PairConst<float> C, Tiles TL, int cap_union, const int4* __restrict__ pos,
-    const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
-    uint4* __restrict__ list, uint32_t* __restrict__ ncnt, int count_pairs,
-    unsigned long long* __restrict__ pairs, uint32_t epoch, uint32_t* __restrict__ fallback) {
-    __shared__ TileMeta M;
+template <int S, typename T>
+__global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
+    int n, Grid G, PairConst<T> C, Tiles TL, int cap_union,
+    const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, uint32_t cap, uint4* __restrict__ list,
+    uint32_t* __restrict__ ncnt, int count_pairs, unsigned long long* __restrict__ pairs,
+    uint32_t epoch, uint32_t* __restrict__ fallback) {
+    using R = typename Rec<T>::type;
+    using CFG = typename TileCfgOf<T>::type;
+    constexpr int NT = CFG::kThreads;
+    __shared__ TileMeta<CFG> M;
     // float copy of the union (w: the particle's union cell), + the
     // candidates read past a row's end
-    __shared__ float4 Pf[kTileCap + 8];
+    __shared__ float4 Pf[CFG::kCap + 8];
     // each thread's ring of 16 list entries (two octets), 40 bytes apart so
     // that the lanes' appends spread over the LDS banks; the staging's cell
     // table before that
     constexpr int kRingStride = 5;  // uint2 per thread
-    __shared__ uint2 ringbuf[kTileThreads * kRingStride];
-    static_assert(sizeof(ringbuf) >= kTileCap * sizeof(uint16_t), "cell table");
+    __shared__ uint2 ringbuf[NT * kRingStride];
+    static_assert(sizeof(ringbuf) >= CFG::kCap * sizeof(uint16_t), "cell table");
     const int blk = xcd_block();
     int c0[3];
     tile_origin(TL, blk, c0);
     // the cell-range loads go out before the empty-box probe, so that the
     // two round trips overlap
-    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend);
+    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
     if (tile_empty(G, TL, c0, cstart, cend)) {
-        if (count_pairs) tile_count(0u, pairs, blk);
+        if (count_pairs) tile_count<NT>(0u, pairs, blk);
         return;
     }
-    const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M);
-    if (total > (uint32_t)cap_union) {
+    const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
+    bool overflow = total > (uint32_t)cap_union;
+    if (!overflow) {
+        bool far = false;
+        tile_stage(TL, M, (uint16_t*)ringbuf, [&](uint32_t j) { return pos[j]; },
+                   [&](uint32_t u, const R& r, int ux, int uy, int uz) {
+                       const int uc[3] = {ux, uy, uz};
+                       float4 f = filt_copy(r, uc, c0, G, TL, C, &far);
+                       f.w = __int_as_float(ux + TL.uw * (uy + TL.uh * uz));
+                       Pf[u] = f;
+                   });
+        if constexpr (sizeof(T) == 8)
+            overflow = __syncthreads_or(far);
+        else
+            __syncthreads();
+    }
+    if (overflow) {
         tile_mark_overflow(M, ncnt);
         if (threadIdx.x == 0 && M.ntargets) *fallback = epoch;
         // the counter is still touched: tile 0 raises the number of counters
         // the reader sums
-        if (count_pairs) tile_count(0u, pairs, blk);
+        if (count_pairs) tile_count<NT>(0u, pairs, blk);
         return;
     }
-    tile_stage(TL, M, (uint16_t*)ringbuf, [&](uint32_t j) { return pos[j]; },
-               [&](uint32_t u, const int4& r, int ux, int uy, int uz) {
-                   const int4 p = tile_rec(r, ux, uy, uz);
-                   float4 f;
-                   f.x = (float)(p.x - TL.cen[0] * (1 << kFixBits)) * C.fix_scale_f[0];
-                   f.y = (float)(p.y - TL.cen[1] * (1 << kFixBits)) * C.fix_scale_f[1];
-                   f.z = (float)(p.z - TL.cen[2] * (1 << kFixBits)) * C.fix_scale_f[2];
-                   f.w = __int_as_float(ux + TL.uw * (uy + TL.uh * uz));
-                   Pf[u] = f;
-               });
-    __syncthreads();
     uint2* const myring = &ringbuf[threadIdx.x * kRingStride];
     uint16_t* my = (uint16_t*)myring;
     auto ring_octet = [&](uint32_t k8) {
@@ -535,28 +650,22 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_build(
     uint32_t counted = 0;
     bool need_fb = false;
     const float cxf = (float)TL.cen[0], cyf = (float)TL.cen[1], czf = (float)TL.cen[2];
-    for (uint32_t t = threadIdx.x; t < M.ntargets; t += kTileThreads) {
+    for (uint32_t t = threadIdx.x; t < M.ntargets; t += NT) {
         uint32_t ui, i;
         int uc[3];
         tile_target(TL, M, t, &ui, &i, uc);
         const float4 pf = Pf[ui];
-        const int4 pi = tile_rec(pos[i], uc[0], uc[1], uc[2]);
+        const R ri = pos[i];
         // rows are clipped only for a target inside its cell (a particle
         // clamped into an edge cell from outside a non-periodic box walks
         // whole rows, as walk_pairs does)
-        const int half = 1 << (kFixBits - 1);
-        const bool clip = abs(pi.x - uc[0] * (1 << kFixBits)) <= half &&
-                          abs(pi.y - uc[1] * (1 << kFixBits)) <= half &&
-                          abs(pi.z - uc[2] * (1 << kFixBits)) <= half;
-        // exact predicate on the integer separation (candidate's record from
-        // global memory, in the union frame)
+        const bool clip = tile_inside(ri, pf, uc, TL);
+        // exact predicate on the records (the candidate's from global memory)
         auto exact = [&](uint32_t u) {
             const int c = __float_as_int(Pf[u].w);
             int cu[3];
             union_coords(TL, c, cu);
-            const int4 pj = tile_rec(pos[M.gs[c] + (u - M.off[c])], cu[0], cu[1], cu[2]);
-            const Geom<float> g = pair_geom<3>(pi, pj, 0, 0, 0, 0, 0, 0, C);
-            return geom_r2d(g, C) < C.R2_d;
+            return tile_exact(ri, uc, pos[M.gs[c] + (u - M.off[c])], cu, c0, G, TL, C);
         };
         uint32_t cnt = 0;
         // the (2S+1)^2 stencil rows in walk order (z planes, then y rows);
@@ -644,35 +753,35 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_build(
         need_fb |= cnt > cap;
     }
     if (__syncthreads_or(need_fb) && threadIdx.x == 0) *fallback = epoch;
-    if (count_pairs) tile_count(counted, pairs, blk);
+    if (count_pairs) tile_count<NT>(counted, pairs, blk);
 }
 
 // Summation density (eq. 2), and with_eos the Tait EOS (eq. eos), of the
 // tile's targets with complete lists (as k_density), over the union's
 // position records staged in LDS.
 template <int S, int KERNEL>
-__global__ __launch_bounds__(kTileThreads) void k_tile_density(
+__global__ __launch_bounds__(CfgF::kThreads) void k_tile_density(
     int n, Grid G, PairConst<float> C, Tiles TL, int cap_union, const int4* __restrict__ pos,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
     const uint4* __restrict__ list, const uint32_t* __restrict__ ncnt,
     float* __restrict__ rho_out, float* __restrict__ p_out, float4* __restrict__ vel,
     float2* __restrict__ rp, int with_eos) {
-    __shared__ TileMeta M;
-    __shared__ int4 Pi[kTileCap];
-    __shared__ uint16_t cellof[kTileCap];
+    __shared__ TileMeta<CfgF> M;
+    __shared__ int4 Pi[CfgF::kCap];
+    __shared__ uint16_t cellof[CfgF::kCap];
     const int blk = xcd_block();
     int c0[3];
     tile_origin(TL, blk, c0);
-    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend);
+    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
     if (tile_empty(G, TL, c0, cstart, cend)) return;
-    const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M);
+    const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
     if (total > (uint32_t)cap_union) return;  // every target is the fallback's
     tile_stage(TL, M, cellof, [&](uint32_t j) { return pos[j]; },
                [&](uint32_t u, const int4& r, int ux, int uy, int uz) {
                    Pi[u] = tile_rec(r, ux, uy, uz);
                });
     __syncthreads();
-    for (uint32_t t = threadIdx.x; t < M.ntargets; t += kTileThreads) {
+    for (uint32_t t = threadIdx.x; t < M.ntargets; t += CfgF::kThreads) {
         uint32_t ui, i;
         int uc[3];
         tile_target(TL, M, t, &ui, &i, uc);
@@ -709,7 +818,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_density(
 // metas and two cell tables alternate.  The pair loops take half octets at
 // a time, which keeps the staging registers clear of spills.
 template <int S, int KERNEL>
-__global__ __launch_bounds__(kTileThreads) void k_tile_momentum(
+__global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
     int n, Grid G, PairConst<float> C, Tiles TL, int cap_union, const int4* __restrict__ pos,
     const float4* __restrict__ vel, const float2* __restrict__ rp,
     const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
@@ -717,11 +826,12 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_momentum(
     const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
     uint32_t* __restrict__ key, uint32_t* __restrict__ counts, uint32_t* __restrict__ flags,
     double* __restrict__ diag_part, int stride) {
-    __shared__ TileMeta MM[2];
-    __shared__ uint16_t cellofs[2][kTileCap];
-    __shared__ int4 Pi[kTileCap];
-    __shared__ float4 V[kTileCap];
-    __shared__ float2 RP[kTileCap];
+    __shared__ TileMeta<CfgF> MM[2];
+    __shared__ uint16_t cellofs[2][CfgF::kCap];
+    __shared__ int4 Pi[CfgF::kCap];
+    __shared__ float4 V[CfgF::kCap];
+    __shared__ float2 RP[CfgF::kCap];
+    const int tid = (int)threadIdx.x;
     // tiles w, w + P, w + 2P, ... (P workgroups): the tiles in flight at
     // any time are P consecutive ones, each XCD's a contiguous run of them
     const int P = (int)gridDim.x;
@@ -739,39 +849,39 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_momentum(
         V[u] = r.v;
         RP[u] = r.rp;
     };
-    auto fits = [&](const TileMeta& M) { return M.total <= (uint32_t)cap_union; };
+    auto fits = [&](const TileMeta<CfgF>& M) { return M.total <= (uint32_t)cap_union; };
     int c0[3];
     // prologue: tile t0 set up and staged, tile t0 + 1 set up
     tile_origin(TL, t0, c0);
-    tile_setup(G, TL, c0, cstart, cend, n, MM[0]);
+    tile_setup(G, TL, c0, cstart, cend, n, MM[0], tid);
     tile_cellof(TL, MM[0], cellofs[0]);
     if (fits(MM[0])) {
-        StageRegs<Rc> R0;
-        tile_stage_loads(MM[0], cellofs[0], load_rc, R0);
-        tile_stage_store(TL, MM[0], cellofs[0], R0, store_rc);
+        StageRegs<CfgF, Rc> R0;
+        tile_stage_loads(MM[0], cellofs[0], load_rc, R0, tid);
+        tile_stage_store(TL, MM[0], cellofs[0], R0, store_rc, tid);
     }
     if (t0 + P < t1) {
         tile_origin(TL, t0 + P, c0);
-        tile_setup(G, TL, c0, cstart, cend, n, MM[1]);  // its barriers also publish the staging
+        tile_setup(G, TL, c0, cstart, cend, n, MM[1], tid);  // its barriers also publish the staging
         tile_cellof(TL, MM[1], cellofs[1]);
     } else {
         __syncthreads();
     }
     int cur = 0;
     for (int t = t0; t < t1; t += P) {
-        const TileMeta& M = MM[cur];
-        const TileMeta& MN = MM[cur ^ 1];
+        const TileMeta<CfgF>& M = MM[cur];
+        const TileMeta<CfgF>& MN = MM[cur ^ 1];
         // issued with the targets' loads: the next tile's staging loads and
         // the cell-range loads of the one after
         const bool stage_next = t + P < t1 && fits(MN);
-        StageRegs<Rc> R;
-        if (stage_next) tile_stage_loads(MN, cellofs[cur ^ 1], load_rc, R);
+        StageRegs<CfgF, Rc> R;
+        if (stage_next) tile_stage_loads(MN, cellofs[cur ^ 1], load_rc, R, tid);
         const bool setup_next2 = t + 2 * P < t1;
         int c2[3] = {0, 0, 0};
         SetupLoads sl{};
         if (setup_next2) {
             tile_origin(TL, t + 2 * P, c2);
-            sl = tile_setup_loads(G, TL, c2, cstart, cend);
+            sl = tile_setup_loads(G, TL, c2, cstart, cend, tid);
         }
         double dsum[4] = {0.0, 0.0, 0.0, 0.0};
         const uint32_t nt = M.ntargets;
@@ -795,7 +905,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_momentum(
                 g.ci = close_load<3>((int)g.i, St, drift, diag_part != nullptr);
                 return g;
             };
-            for (uint32_t tt = threadIdx.x; tt < nt; tt += kTileThreads) {
+            for (uint32_t tt = threadIdx.x; tt < nt; tt += CfgF::kThreads) {
                 const Tgt cur_t = target_loads(tt);
                 const uint32_t ui = cur_t.ui, i = cur_t.i, cnt = cur_t.cnt;
                 if (cnt > cap) continue;  // the fallback's
@@ -830,17 +940,17 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_momentum(
                 for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
             }
         }
-        if (diag_part) tile_block_sum<4>(dsum, diag_part, t, stride);
+        if (diag_part) tile_block_sum<4, CfgF::kThreads>(dsum, diag_part, t, stride);
         __syncthreads();  // tile t's records, meta and cell table are free
         if (stage_next) {
 #pragma unroll
-            for (int q = 0; q < kStageQ; ++q) keep_in_flight(R.v[q]);
-            tile_stage_store(TL, MN, cellofs[cur ^ 1], R, store_rc);
+            for (int q = 0; q < StageRegs<CfgF, Rc>::kQ; ++q) keep_in_flight(R.v[q]);
+            tile_stage_store(TL, MN, cellofs[cur ^ 1], R, store_rc, tid);
         }
         if (setup_next2) {
             keep_in_flight(sl.s);
             keep_in_flight(sl.e);
-            tile_setup_finish(G, TL, c2, n, sl, MM[cur]);
+            tile_setup_finish(G, TL, c2, n, sl, MM[cur], tid);
             tile_cellof(TL, MM[cur], cellofs[cur]);  // its barrier publishes the staging
         } else {
             __syncthreads();
@@ -849,16 +959,220 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_momentum(
     }
 }
 
+// ---------------------------------------------------------------------------
+// FP64 passes over the tiles: the lists of k_tile_build<S, double>, the
+// union's records staged in LDS as they are (absolute positions), and the pair
+// terms of the global passes in the same order, so the results are bitwise
+// theirs.  A separation across a periodic face needs the neighbour's image
+// (pair_geom's w): a byte per staged particle, read only in tiles whose
+// union reaches over a face.
+// (160^3 cube, h = 1.5 dx, half-size cells, against the walk build and the
+// passes over global lists: build 1.80 against 4.62 ms, density 1.11 against
+// 1.93, momentum 3.15 against 3.90; those gather 80 bytes a neighbour through
+// L1 and L2 at 9 TB/s.  Boxes of 4 x 4 x 4 cells are what 72 bytes a staged
+// particle leaves room for.)
+struct RecD {
+    double4 p;
+    uint32_t w;
+};
+__device__ __forceinline__ uint32_t tile_image(const Grid& G, const Tiles& TL, const int c0[3],
+                                               int ux, int uy, int uz) {
+    return (uint32_t)(tile_wrap(G, 0, c0[0], ux, TL.S) + 1) |
+           ((uint32_t)(tile_wrap(G, 1, c0[1], uy, TL.S) + 1) << 2) |
+           ((uint32_t)(tile_wrap(G, 2, c0[2], uz, TL.S) + 1) << 4);
+}
+// Whether some union cell of the tile lies over a periodic face.
+__device__ __forceinline__ bool tile_wraps(const Grid& G, const Tiles& TL, const int c0[3]) {
+    const int hi[3] = {TL.tw, TL.th, TL.td};
+    bool w = false;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        w |= G.periodic[k] && (c0[k] < TL.S || c0[k] + hi[k] + TL.S > G.nc[k]);
+    return w;
+}
+template <bool WRAP>
+__device__ __forceinline__ Geom<double> tile_geom(const double4& ri, const double4& rj, uint32_t w,
+                                                  const PairConst<double>& C) {
+    if (!WRAP) return pair_geom<3>(ri, rj, 0, 0, 0, 0, 0, 0, C);
+    return pair_geom<3>(ri, rj, 0, 0, 0, (int)(w & 3u) - 1, (int)((w >> 2) & 3u) - 1,
+                        (int)(w >> 4) - 1, C);
+}
+
+// Summation density (eq. 2), and with_eos the Tait EOS, of the tile's targets
+// with complete lists, FP64 (as k_density).
+template <int S, int KERNEL>
+__global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
+    int n, Grid G, PairConst<double> C, Tiles TL, int cap_union, const double4* __restrict__ pos,
+    const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
+    const uint4* __restrict__ list, const uint32_t* __restrict__ ncnt,
+    double* __restrict__ rho_out, double* __restrict__ p_out, double4* __restrict__ vel,
+    double2* __restrict__ rp, int with_eos) {
+    __shared__ TileMeta<CfgD> M;
+    __shared__ double4 P[CfgD::kCap];
+    __shared__ uint8_t W[CfgD::kCap];
+    __shared__ uint16_t cellof[CfgD::kCap];
+    const int blk = xcd_block();
+    int c0[3];
+    tile_origin(TL, blk, c0);
+    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
+    if (tile_empty(G, TL, c0, cstart, cend)) return;
+    const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
+    if (total > (uint32_t)cap_union) return;  // every target is the fallback's
+    tile_stage(TL, M, cellof, [&](uint32_t j) { return pos[j]; },
+               [&](uint32_t u, const double4& r, int ux, int uy, int uz) {
+                   P[u] = r;
+                   W[u] = (uint8_t)tile_image(G, TL, c0, ux, uy, uz);
+               });
+    __syncthreads();
+    const bool wraps = tile_wraps(G, TL, c0);
+    for (uint32_t t = threadIdx.x; t < M.ntargets; t += CfgD::kThreads) {
+        uint32_t ui, i;
+        int uc[3];
+        tile_target(TL, M, t, &ui, &i, uc);
+        const uint32_t cnt = ncnt[i];
+        const ListHead head = tile_list_head(list, i, cap);
+        if (cnt > cap) continue;  // the fallback's
+        const double4 pi = P[ui];
+        double acc = 0.0;
+        auto sum = [&](auto wrap) {
+            constexpr bool kWrap = decltype(wrap)::value;
+            tile_list_loop(list, i, cap, cnt, head,
+                           [&](uint32_t u) { return RecD{P[u], kWrap ? (uint32_t)W[u] : 0u}; },
+                           [&](const RecD& b) {
+                               const Geom<double> g = tile_geom<kWrap>(pi, b.p, b.w, C);
+                               density_add<KERNEL, double>(acc, g, rec_mass(b.p), C);
+                           });
+        };
+        if (wraps)
+            sum(BoolC<true>());
+        else
+            sum(BoolC<false>());
+        finish_density<3, double>((int)i, acc, C, rho_out, 0, p_out, vel, rp, with_eos);
+    }
+}
+
+// Momentum equation of the tile's targets with complete lists, FP64 (as
+// k_momentum), with momentum_close as the epilogue; per-tile partial sums of
+// the diagnostics into diag_part[q * stride + tile].  A staged particle takes
+// 73 bytes, so that one workgroup fills a CU's LDS: four waves, one per SIMD,
+// with all of its registers (eight staged records per thread in flight).
+template <int S, int KERNEL>
+__global__ __launch_bounds__(CfgD::kThreads, 1) void k_tile_momentum64(
+    int n, Grid G, PairConst<double> C, Tiles TL, int cap_union, const double4* __restrict__ pos,
+    const double4* __restrict__ vel, const double2* __restrict__ rp,
+    const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
+    const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
+    uint32_t* __restrict__ key, uint32_t* __restrict__ counts, uint32_t* __restrict__ flags,
+    double* __restrict__ diag_part, int stride) {
+    __shared__ TileMeta<CfgD> M;
+    __shared__ uint16_t cellof[CfgD::kCap];
+    __shared__ double4 P[CfgD::kCap];
+    __shared__ double2 Vxy[CfgD::kCap];
+    __shared__ double2 RP[CfgD::kCap];
+    __shared__ double Vz[CfgD::kCap];
+    __shared__ uint8_t W[CfgD::kCap];
+    const int blk = xcd_block();
+    int c0[3];
+    tile_origin(TL, blk, c0);
+    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
+    double dsum[4] = {0.0, 0.0, 0.0, 0.0};
+    const bool empty = tile_empty(G, TL, c0, cstart, cend);
+    const uint32_t total =
+        empty ? 0u : tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
+    if (!empty && total <= (uint32_t)cap_union) {
+        struct Rc {
+            double4 p;
+            double2 vxy;
+            double vz;
+            double2 rp;
+        };
+        tile_stage(
+            TL, M, cellof,
+            [&](uint32_t j) {
+                const double4 v = vel[j];
+                return Rc{pos[j], make_double2(v.x, v.y), v.z, rp[j]};
+            },
+            [&](uint32_t u, const Rc& r, int ux, int uy, int uz) {
+                P[u] = r.p;
+                Vxy[u] = r.vxy;
+                Vz[u] = r.vz;
+                RP[u] = r.rp;
+                W[u] = (uint8_t)tile_image(G, TL, c0, ux, uy, uz);
+            });
+        __syncthreads();
+        const bool wraps = tile_wraps(G, TL, c0);
+        for (uint32_t tt = threadIdx.x; tt < M.ntargets; tt += CfgD::kThreads) {
+            uint32_t ui, i;
+            int uc[3];
+            tile_target(TL, M, tt, &ui, &i, uc);
+            const uint32_t cnt = ncnt[i];
+            const bool fluid = type[i] == 0;
+            const ListHead head = tile_list_head(list, i, cap);
+            const CloseIn ci = close_load<3>((int)i, St, drift, diag_part != nullptr);
+            if (cnt > cap) continue;  // the fallback's
+            double acc[3] = {0.0, 0.0, 0.0};
+            if (fluid) {
+                const double4 pi = P[ui];
+                double4 vi;
+                vi.x = Vxy[ui].x;
+                vi.y = Vxy[ui].y;
+                vi.z = Vz[ui];
+                vi.w = 0.0;
+                const double2 rpi = RP[ui];
+                double ax = C.g[0], ay = C.g[1], az = C.g[2];
+                struct Nb {
+                    double4 p;
+                    double2 vxy;
+                    double vz;
+                    double2 rp;
+                    uint32_t w;
+                };
+                auto sum = [&](auto wrap) {
+                    constexpr bool kWrap = decltype(wrap)::value;
+                    tile_list_loop<4>(
+                        list, i, cap, cnt, head,
+                        [&](uint32_t u) {
+                            return Nb{P[u], Vxy[u], Vz[u], RP[u], kWrap ? (uint32_t)W[u] : 0u};
+                        },
+                        [&](const Nb& b) {
+                            const Geom<double> g = tile_geom<kWrap>(pi, b.p, b.w, C);
+                            double4 vj;
+                            vj.x = b.vxy.x;
+                            vj.y = b.vxy.y;
+                            vj.z = b.vz;
+                            vj.w = 0.0;
+                            momentum_add<3, KERNEL, double>(ax, ay, az, g, rec_mass(b.p), vi, rpi,
+                                                            vj, b.rp, C);
+                        });
+                };
+                if (wraps)
+                    sum(BoolC<true>());
+                else
+                    sum(BoolC<false>());
+                acc[0] = ax;
+                acc[1] = ay;
+                acc[2] = az;
+            }
+            double dv[4] = {0.0, 0.0, 0.0, 0.0};
+            momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, key, counts,
+                                      flags, diag_part != nullptr, dv, &ci);
+            for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
+        }
+    }
+    if (diag_part) tile_block_sum<4, CfgD::kThreads>(dsum, diag_part, blk, stride);
+}
+
 // Fallback density: the targets the tile build left (count above cap, or
 // kTileOverflow), by the cell walk in global memory (density_one); only the
 // kTileOverflow ones are counted (the build counted the others).
-template <int S, int KERNEL>
+template <int S, int KERNEL, typename T>
 __global__ __launch_bounds__(kBlock) void k_tile_fallback_density(
-    int n, Grid G, PairConst<float> C, const uint32_t* __restrict__ skey,
-    const int4* __restrict__ pos, const uint32_t* __restrict__ cstart,
+    int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
+    const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, const uint32_t* __restrict__ ncnt, uint32_t cap,
-    float* __restrict__ rho_out, float* __restrict__ p_out, float4* __restrict__ vel,
-    float2* __restrict__ rp, int with_eos, int count_pairs, unsigned long long* __restrict__ pairs,
+    T* __restrict__ rho_out, T* __restrict__ p_out, typename Vec4<T>::type* __restrict__ vel,
+    typename Vec2<T>::type* __restrict__ rp, int with_eos, int count_pairs, unsigned long long* __restrict__ pairs,
     uint32_t epoch, const uint32_t* __restrict__ fallback) {
     if (*fallback != epoch) return;
     uint32_t counted = 0;
@@ -866,9 +1180,9 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_density(
         const uint32_t c = ncnt[i];
         if (c <= cap) continue;
         // a null list makes density_one walk the cells
-        const uint32_t k = density_one<3, S, KERNEL, float>(i, G, C, skey, pos, cstart, cend, n,
-                                                            nullptr, ncnt, cap, rho_out, 0, p_out,
-                                                            vel, rp, with_eos);
+        const uint32_t k = density_one<3, S, KERNEL, T>(i, G, C, skey, pos, cstart, cend, n,
+                                                        nullptr, ncnt, cap, rho_out, 0, p_out,
+                                                        vel, rp, with_eos);
         if (c == kTileOverflow) counted += k;
     }
     if (count_pairs) block_count(counted, pairs, blockIdx.x);
@@ -876,11 +1190,11 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_density(
 
 // Fallback momentum, as k_tile_fallback_density; diagnostics partials of its
 // blocks at diag_part[q * stride + b] (zeros when there is nothing to do).
-template <int S, int KERNEL>
+template <int S, int KERNEL, typename T>
 __global__ __launch_bounds__(kBlock) void k_tile_fallback_momentum(
-    int n, Grid G, PairConst<float> C, const uint32_t* __restrict__ skey,
-    const int4* __restrict__ pos, const float4* __restrict__ vel, const float2* __restrict__ rp,
-    const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
+    int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
+    const typename Rec<T>::type* __restrict__ pos, const typename Vec4<T>::type* __restrict__ vel,
+    const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, const uint32_t* __restrict__ ncnt, uint32_t cap, State St,
     int kick, int drift, double hdt, double dt, uint32_t* __restrict__ key,
     uint32_t* __restrict__ counts, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
@@ -890,9 +1204,9 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_momentum(
         for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
             if (ncnt[i] <= cap) continue;
             double dv[4] = {0.0, 0.0, 0.0, 0.0};
-            momentum_one<3, S, KERNEL, float>(i, G, C, skey, pos, vel, rp, type, cstart, cend, n,
-                                              nullptr, ncnt, cap, St, kick, drift, hdt, dt, key,
-                                              counts, flags, diag_part != nullptr, dv);
+            momentum_one<3, S, KERNEL, T>(i, G, C, skey, pos, vel, rp, type, cstart, cend, n,
+                                          nullptr, ncnt, cap, St, kick, drift, hdt, dt, key,
+                                          counts, flags, diag_part != nullptr, dv);
             for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
         }
     }
