@@ -596,7 +596,7 @@ sph::PairConst<T> pair_const(const sph_params* p, const sph::Grid& G) {
     C.inv_h = (T)(1.0 / h);
     C.sigma = (T)sigma;
     C.sigma_h2 = (T)(sigma / (h * h));
-    C.eta_h2 = (T)(p->eta * h * h);
+    C.eta_h2 = (T)(std::max(p->eta, 1e-24) * h * h);
     C.four_nu = (T)(4.0 * p->nu);
     for (int k = 0; k < 3; ++k) {
         C.g[k] = (T)p->g[k];

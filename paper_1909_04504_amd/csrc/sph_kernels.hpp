@@ -195,7 +195,7 @@ struct PairConst {
     T inv_h;       // 1/h
     T sigma;       // kernel normalisation (includes h^-dim)
     T sigma_h2;    // sigma / h^2: scale of F = (dW/dr)/r
-    T eta_h2;      // eta h^2
+    T eta_h2;      // eta h^2, at least 1e-24 h^2
     T four_nu;     // 4 nu
     T g[3];        // body acceleration
     T cs[3];       // cell sizes
@@ -226,13 +226,42 @@ __device__ __forceinline__ double geom_r2d(const Geom<float>& g, const PairConst
 
 // ---------------------------------------------------------------------------
 // Precision-generic helpers.  Mixed precision uses the hardware square root
-// and reciprocal (1 ulp); FP64 uses the correctly rounded library forms.
+// and reciprocal (1 ulp).  FP64 starts from the hardware's approximations
+// (v_rcp_f64, v_rsq_f64: about 26 bits) and takes one correction of third order
+// (with e = 1 - x y the reciprocal is y (1 + e + e^2 + ..), with e = 1 - x y^2
+// the reciprocal square root y (1 + e/2 + 3 e^2/8 + ..)), the square root
+// two steps of Newton's iteration with an exact residual: 4, 6 and 8
+// instructions where the correctly rounded division and square root take
+// about 12 and 18, and at most one unit in the last place from the exact
+// value (over 2^-60 .. 2^20: 0.50, 0.99 and 0.50 units; 1 / sqrt(x) rounded
+// twice 1.49).  The arguments are positive and finite: |r| and |r|^2 of
+// accepted pairs (at least the smallest normal number, tiny_normal), sums of
+// densities and |r|^2 + eta h^2 (at least 1e-24 h^2); an infinite density makes
+// its pressure term NaN in either form.
 __device__ __forceinline__ float p_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double p_sqrt(double x) { return sqrt(x); }
+__device__ __forceinline__ double p_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    return fma(fma(-g, g, x), h, g);
+}
 __device__ __forceinline__ float p_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double p_rcp(double x) { return 1.0 / x; }
+__device__ __forceinline__ double p_rcp(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(fma(e, e, e), y, y);
+}
 __device__ __forceinline__ float p_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double p_rsqrt(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double p_rsqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+template <typename T> __device__ __forceinline__ T tiny_normal();
+template <> __device__ __forceinline__ float tiny_normal<float>() { return 1.17549435e-38f; }
+template <> __device__ __forceinline__ double tiny_normal<double>() { return 2.2250738585072014e-308; }
 
 // FP64 square root for the mixed-precision density terms: an FP32
 // reciprocal square root y as the seed, r = x y, and one Newton step
@@ -240,7 +269,7 @@ __device__ __forceinline__ double p_rsqrt(double x) { return 1.0 / sqrt(x); }
 // a square root and a reciprocal).  x is taken at least the smallest normal
 // float, so that x = 0 (the self pair) gives r ~ 1e-19 instead of 0 * inf;
 // a kernel evaluated at q ~ 1e-19 / h rounds to its value at 0 (every
-// kernel here is flat there).  The FP64 path uses the correctly rounded sqrt.
+// kernel here is flat there).  The FP64 path takes p_sqrt of the same clamp.
 __device__ __forceinline__ double sqrt_newton(double x) {
     const double xc = fmax(x, 1.1754943508222875e-38);
     const double y = (double)__builtin_amdgcn_rsqf((float)xc);
@@ -248,7 +277,9 @@ __device__ __forceinline__ double sqrt_newton(double x) {
     return fma(fma(-r, r, xc), 0.5 * y, r);
 }
 __device__ __forceinline__ double density_sqrt(double x, float) { return sqrt_newton(x); }
-__device__ __forceinline__ double density_sqrt(double x, double) { return sqrt(x); }
+__device__ __forceinline__ double density_sqrt(double x, double) {
+    return p_sqrt(fmax(x, tiny_normal<double>()));
+}
 
 // Smoothing kernel W(q) = sigma w(q), q = r/h, support q < 2 (q < 3 for
 // the quintic spline).
@@ -325,22 +356,17 @@ __device__ __forceinline__ T kernel_f(T q, T sigma_h2) {
 }
 
 // F = (dW/dr)/r from |r|^2 with one reciprocal square root: rinv = 1/|r|,
-// q = |r| / h, 1/q = h rinv.  At r = 0 (the self pair), F r = 0 anyway.
-// In FP32 the square root is then taken of the smallest normal number
-// instead (every nonzero |r|^2 of a pair is far above it), so rinv stays
-// finite, q = 0 exactly and F is the inner branch's value at q = 0: no
-// select.  In FP64 rinv is set to 0 there by a select, which measured
-// faster than the clamp (the FP64 square root is a software sequence).
-template <typename T> __device__ __forceinline__ T tiny_normal();
-template <> __device__ __forceinline__ float tiny_normal<float>() { return 1.17549435e-38f; }
-template <> __device__ __forceinline__ double tiny_normal<double>() { return 2.2250738585072014e-308; }
+// q = |r| / h, 1/q = h rinv.  At r = 0 (the self pair), F r = 0 anyway: the
+// square root is then taken of the smallest normal number instead (every
+// nonzero |r|^2 of a pair is far above it), so rinv stays finite, q = 0
+// exactly and F is the inner branch's value at q = 0: no select.
 template <int KERNEL, typename T>
 __device__ __forceinline__ T kernel_f_r2(T r2, const PairConst<T>& C) {
-    T rinv;
-    if constexpr (sizeof(T) == 8)
-        rinv = r2 > T(0) ? p_rsqrt(r2) : T(0);
-    else
-        rinv = p_rsqrt(fmax(r2, tiny_normal<T>()));
+    const T rinv = p_rsqrt(fmax(r2, tiny_normal<T>()));
+    if constexpr (KERNEL == 1 && sizeof(T) == 8) {
+        const T t = T(1) - C.half_inv_h_d * (r2 * rinv);
+        return T(-5) * C.sigma_h2 * t * t * t;
+    }
     const T q = r2 * rinv * C.inv_h;
     if (KERNEL == 0) {
         const T t = T(2) - q;
@@ -503,11 +529,15 @@ template <int DIM>
 __device__ __forceinline__ Geom<double> pair_geom(const double4& ri, const double4& rj, int, int,
                                                   int, int wx, int wy, int wz,
                                                   const PairConst<double>& C) {
-    auto shift = [&](int w, int k) { return w == 0 ? 0.0 : (w < 0 ? -C.L[k] : C.L[k]); };
+    // minus w L, an exact product (w in {-1, 0, 1}), as one multiply-add
+    // (none for a w that is known to be 0)
+    auto shifted = [&](double d, int w, int k) {
+        return __builtin_constant_p(w) && w == 0 ? d : fma(-(double)w, C.L[k], d);
+    };
     Geom<double> g;
-    g.d[0] = (ri.x - rj.x) - shift(wx, 0);
-    g.d[1] = (ri.y - rj.y) - shift(wy, 1);
-    g.d[2] = DIM == 3 ? (ri.z - rj.z) - shift(wz, 2) : 0.0;
+    g.d[0] = shifted(ri.x - rj.x, wx, 0);
+    g.d[1] = shifted(ri.y - rj.y, wy, 1);
+    g.d[2] = DIM == 3 ? shifted(ri.z - rj.z, wz, 2) : 0.0;
     g.r2 = g.d[0] * g.d[0] + g.d[1] * g.d[1];
     if (DIM == 3) g.r2 += g.d[2] * g.d[2];
     return g;
@@ -550,12 +580,14 @@ __device__ __forceinline__ bool pair_accept(const Geom<float>& g, const PairCons
 // Stencil codes.  An accepted neighbour is stored as one 32-bit word,
 // (slot j << bits) | code, where the code gives what pair_geom needs besides
 // the two records: the stencil offsets o (mixed precision, base 2S+1 digits)
-// or the periodic images w (FP64, base 3 digits).
+// or the periodic images w (FP64; 2D: two bits per axis, two's complement, so
+// that one signed bit-field extract gives w; 3D: base 3 digits, which leave a
+// bit more for the slot).
 template <int DIM, int SR, typename T>
 struct NbrCode {
     static constexpr int NR = 2 * SR + 1;
     static constexpr bool kFp64 = sizeof(T) == 8;
-    static constexpr int kCodes = kFp64 ? (DIM == 3 ? 27 : 9) : (DIM == 3 ? NR * NR * NR : NR * NR);
+    static constexpr int kCodes = kFp64 ? (DIM == 3 ? 27 : 16) : (DIM == 3 ? NR * NR * NR : NR * NR);
     static constexpr int kBits = kCodes <= 16 ? 4 : (kCodes <= 32 ? 5 : (kCodes <= 64 ? 6 : 7));
     static constexpr uint32_t kMask = (1u << kBits) - 1u;
     // Largest particle count whose slots fit beside the code.
@@ -564,6 +596,7 @@ struct NbrCode {
     // Part of the code fixed for one stencil row piece; the mixed-precision
     // code adds the candidate's own x offset.
     static __device__ __forceinline__ int row_base(int oy, int oz, int wx, int wy, int wz) {
+        if (kFp64 && DIM == 2) return (wx & 3) | ((wy & 3) << 2);
         if (kFp64) return (wx + 1) + 3 * ((wy + 1) + (DIM == 3 ? 3 * (wz + 1) : 0));
         return SR + NR * ((oy + SR) + (DIM == 3 ? NR * (oz + SR) : 0));
     }
@@ -573,6 +606,9 @@ struct NbrCode {
     template <typename R>
     static __device__ __forceinline__ Geom<T> geom(const R& ri, const R& rj, uint32_t c,
                                                    const PairConst<T>& C) {
+        if (kFp64 && DIM == 2)
+            return pair_geom<DIM>(ri, rj, 0, 0, 0, (int)(c << 30) >> 30, (int)(c << 28) >> 30, 0,
+                                  C);
         const int B = kFp64 ? 3 : NR, off = kFp64 ? 1 : SR;
         const int a = (int)(c % (uint32_t)B) - off;
         const uint32_t t = c / (uint32_t)B;
@@ -823,6 +859,7 @@ __device__ __forceinline__ void for_each_neighbor_p(
             for (uint32_t u = 0; u < kGroup; ++u) pp[u] = load(jj[u]);
 #pragma unroll
             for (uint32_t u = 0; u < kGroup; ++u) q[u] = entry(k + kGroup + u);
+            if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (uint32_t u = 0; u < kGroup; ++u) f(jj[u], rr[u], pp[u], Code::geom(ri, rr[u], cc[u], C));
         }
@@ -1564,9 +1601,10 @@ __global__ __launch_bounds__(kBlock) void k_nlist_walk(int n, Grid G, PairConst<
 // Summation density (eq. 2), FP64 terms in both precisions.  Mixed
 // precision: acc += m_j w(|r_ij|), the kernel without its normalisation
 // sigma (finish_density scales the sum), Wendland's factors straight from
-// r.  FP64: acc += m_j W(q) with q = |r_ij|/h, the normalised kernel; in
-// the FP64 list pass this form keeps the kernel at 96 registers (five
-// waves per SIMD), the other measured 10% slower there.
+// r.  FP64: acc += m_j W(q) with q = |r_ij|/h, the normalised kernel: two
+// operations more (3% of the tiled pass), but no rounding of the finished sum,
+// which the EOS would multiply (p 1.4e-14 instead of 1.1e-14 from the exact
+// one on the 160^3 cube).
 template <int KERNEL, typename T>
 __device__ __forceinline__ void density_add(double& acc, const Geom<T>& g, double mj,
                                             const PairConst<T>& C) {
@@ -1581,9 +1619,8 @@ __device__ __forceinline__ void density_add(double& acc, const Geom<T>& g, doubl
 //   a_i += m_j [ -(P_i + P_j) F r_ij + 4 nu/(rho_i+rho_j) F |r|^2/(|r|^2 + eta h^2) v_ij ]
 // with F = (dW/dr)/r.  The self pair (j = i) is not skipped: r = 0 and
 // v_i - v_i = 0 multiply finite factors (F is finite at r = 0, and the
-// viscous factor holds |r|^2 = 0 over a positive denominator in FP32 and
-// is set to 0 by a select in FP64, the faster form in each), so it adds
-// exactly zero.
+// viscous factor holds |r|^2 = 0 over a positive denominator, eta h^2 being
+// at least 1e-24 h^2), so it adds exactly zero.
 template <int DIM, int KERNEL, typename T>
 __device__ __forceinline__ void momentum_add(T& ax, T& ay, T& az, const Geom<T>& g, T mj,
                                              const typename Vec4<T>::type& vi,
@@ -1594,8 +1631,7 @@ __device__ __forceinline__ void momentum_add(T& ax, T& ay, T& az, const Geom<T>&
     const T r2 = g.r2;
     const T F = kernel_f_r2<KERNEL, T>(r2, C);
     const T pres = -(rpi.y + rpj.y) * F;
-    T visc = C.four_nu * F * r2 * p_rcp((rpi.x + rpj.x) * (r2 + C.eta_h2));
-    if constexpr (sizeof(T) == 8) visc = r2 > T(0) ? visc : T(0);
+    const T visc = C.four_nu * F * r2 * p_rcp((rpi.x + rpj.x) * (r2 + C.eta_h2));
     // m_j folded into the two factors once per pair; each component takes
     // two multiply-adds, the pressure term first
     const T mp = mj * pres, mv = mj * visc;
