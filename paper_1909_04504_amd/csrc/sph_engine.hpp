@@ -834,8 +834,8 @@ struct Engine {
             with_reach([&](auto R) {
                 constexpr int S = decltype(R)::value;
                 if constexpr (kF64)
-                    launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum64<S, KERNEL>, (unsigned)TL.ntiles,
-                             Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
+                    launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum64<S, KERNEL>, wgs,
+                             sph::kMom64Threads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
                              cs, ce, tcap(), (const uint4*)list(), lcnt(), s, kick ? 1 : 0,
                              drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(), part,
                              stride);

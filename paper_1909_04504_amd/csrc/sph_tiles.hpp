@@ -105,7 +105,9 @@ struct TileMeta {
 };
 
 // Exclusive scan of two counts per thread (cells 2t, 2t+1) over the
-// workgroup; returns the offset of cell 2t, total in *total.
+// CFG::kThreads threads tid of the set-up (further threads of the workgroup
+// take part in the barriers only); returns the offset of cell 2t, total in
+// *total.
 template <typename CFG>
 __device__ __forceinline__ uint32_t tile_scan2(uint32_t a, uint32_t b, TileMeta<CFG>& M,
                                                uint32_t* total, int tid) {
@@ -117,7 +119,7 @@ __device__ __forceinline__ uint32_t tile_scan2(uint32_t a, uint32_t b, TileMeta<
         const uint32_t o = __shfl_up(incl, d, 64);
         if (lane >= d) incl += o;
     }
-    if (lane == 63) M.wsum[w] = incl;
+    if (lane == 63 && tid < CFG::kThreads) M.wsum[w] = incl;
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
@@ -327,13 +329,13 @@ __device__ __forceinline__ void tile_mark_overflow(const TileMeta<CFG>& M,
 // (tile_stage_loads; kCap <= 8 kThreads: a single round) and
 // stores them (tile_stage_store).  cellof: kCap entries of LDS, the
 // union cell of each staged particle (left unset when the union does not
-// fit).
-template <typename CFG>
+// fit; NT: the workgroup's threads).
+template <typename CFG, int NT = CFG::kThreads>
 __device__ __forceinline__ void tile_cellof(const Tiles& TL, const TileMeta<CFG>& M,
                                             uint16_t* cellof) {
     const int ncu = TL.uw * TL.uh * TL.ud;
     if (M.total <= (uint32_t)CFG::kCap)
-        for (int c = threadIdx.x; c < ncu; c += CFG::kThreads)
+        for (int c = threadIdx.x; c < ncu; c += NT)
             for (uint32_t u = M.off[c]; u < M.off[c + 1]; ++u) cellof[u] = (uint16_t)c;
     __syncthreads();
 }
@@ -454,6 +456,37 @@ __device__ __forceinline__ void tile_list_loop(const uint4* __restrict__ list, u
 #pragma unroll
         for (int e = 0; e < 7; ++e)
             if ((uint32_t)e < rest) body(load(half_of(nxt, e)));
+    }
+}
+
+// Calls body(load(u), k) for the entries u = entry k of slot i's list in
+// whole half octets, the last one completed by entries k >= cnt that are the
+// target itself (body sees to it that they add nothing): no entry by entry
+// tail, whose reads nothing covers.
+template <typename Load, typename Body>
+__device__ __forceinline__ void tile_list_whole(const uint4* __restrict__ list, uint32_t i,
+                                                uint32_t cap, uint32_t cnt, const ListHead& head,
+                                                Load&& load, Body&& body) {
+    using P = decltype(load(0u));
+    if (cnt == 0) return;
+    const uint32_t last = (cnt - 1) >> 3;
+    const uint4* __restrict__ base = list + tile_octet(i, cap, 0);
+    uint4 nxt = head.o0, nxt2 = head.o1;
+    for (uint32_t k = 0; k < cnt; k += 8) {
+        const uint4 cur = nxt;
+        nxt = nxt2;
+        nxt2 = base[(size_t)min((k >> 3) + 2, last) * 64];
+        P p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = load(half_of(cur, e));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) body(p[e], k + (uint32_t)e);
+        if (k + 4 < cnt) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = load(half_of(cur, 4 + e));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) body(p[e], k + 4 + (uint32_t)e);
+        }
     }
 }
 
@@ -642,7 +675,9 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
         return;
     }
     uint2* const myring = &ringbuf[threadIdx.x * kRingStride];
-    uint16_t* my = (uint16_t*)myring;
+    // the octets are read back as uint2: the halves may alias them
+    typedef uint16_t __attribute__((may_alias)) Half;
+    Half* my = (Half*)myring;
     auto ring_octet = [&](uint32_t k8) {
         const uint2 lo = myring[2 * (k8 & 1)], hi = myring[2 * (k8 & 1) + 1];
         return make_uint4(lo.x, lo.y, hi.x, hi.y);
@@ -736,7 +771,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
                     const uint32_t c_in = cnt;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        my[cnt & 15] = (uint16_t)(u + q);
+                        my[cnt & 15] = (Half)(u + q);
                         cnt += acc[q];
                     }
                     // an octet completed (at most one per group of four)
@@ -747,7 +782,17 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
                 }
             }
         }
-        if (cnt <= cap && (cnt & 7)) list[tile_octet(i, cap, cnt >> 3)] = ring_octet(cnt >> 3);
+        // the last, partial octet is filled up with the target itself
+        if (cnt <= cap && (cnt & 7)) {
+            const uint32_t r = cnt & 7;
+            auto fill = [&](uint32_t w, uint32_t k) {  // the word of entries k, k + 1
+                const uint32_t lo = k < r ? w & 0xffffu : ui;
+                return lo | (k + 1 < r ? w & 0xffff0000u : ui << 16);
+            };
+            const uint4 v = ring_octet(cnt >> 3);
+            list[tile_octet(i, cap, cnt >> 3)] =
+                make_uint4(fill(v.x, 0), fill(v.y, 2), fill(v.z, 4), fill(v.w, 6));
+        }
         ncnt[i] = cnt;
         counted += cnt;
         need_fb |= cnt > cap;
@@ -967,13 +1012,32 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
 // (pair_geom's w): a byte per staged particle, read only in tiles whose
 // union reaches over a face.
 // (160^3 cube, h = 1.5 dx, half-size cells, against the walk build and the
-// passes over global lists: build 1.80 against 4.62 ms, density 1.11 against
-// 1.93, momentum 3.15 against 3.90; those gather 80 bytes a neighbour through
+// passes over global lists: build 1.80 against 4.62 ms, density 0.88 against
+// 1.93, momentum 1.77 against 3.90; those gather 80 bytes a neighbour through
 // L1 and L2 at 9 TB/s.  Boxes of 4 x 4 x 4 cells are what 72 bytes a staged
 // particle leaves room for.)
 struct RecD {
     double4 p;
     uint32_t w;
+};
+// Staged position records in two arrays of 16 bytes an entry: a 16-byte read
+// at a random entry then starts at any of the LDS's 16 groups of four banks
+// (at every other one with 32-byte entries).
+struct PosD {
+    double2 xy[CfgD::kCap], zm[CfgD::kCap];
+    __device__ __forceinline__ void put(uint32_t u, const double4& r) {
+        xy[u] = make_double2(r.x, r.y);
+        zm[u] = make_double2(r.z, r.w);
+    }
+    __device__ __forceinline__ double4 get(uint32_t u) const {
+        const double2 a = xy[u], b = zm[u];
+        double4 r;
+        r.x = a.x;
+        r.y = a.y;
+        r.z = b.x;
+        r.w = b.y;
+        return r;
+    }
 };
 __device__ __forceinline__ uint32_t tile_image(const Grid& G, const Tiles& TL, const int c0[3],
                                                int ux, int uy, int uz) {
@@ -1008,7 +1072,7 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
     double* __restrict__ rho_out, double* __restrict__ p_out, double4* __restrict__ vel,
     double2* __restrict__ rp, int with_eos) {
     __shared__ TileMeta<CfgD> M;
-    __shared__ double4 P[CfgD::kCap];
+    __shared__ PosD P;
     __shared__ uint8_t W[CfgD::kCap];
     __shared__ uint16_t cellof[CfgD::kCap];
     const int blk = xcd_block();
@@ -1020,7 +1084,7 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
     if (total > (uint32_t)cap_union) return;  // every target is the fallback's
     tile_stage(TL, M, cellof, [&](uint32_t j) { return pos[j]; },
                [&](uint32_t u, const double4& r, int ux, int uy, int uz) {
-                   P[u] = r;
+                   P.put(u, r);
                    W[u] = (uint8_t)tile_image(G, TL, c0, ux, uy, uz);
                });
     __syncthreads();
@@ -1032,16 +1096,17 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
         const uint32_t cnt = ncnt[i];
         const ListHead head = tile_list_head(list, i, cap);
         if (cnt > cap) continue;  // the fallback's
-        const double4 pi = P[ui];
+        const double4 pi = P.get(ui);
         double acc = 0.0;
         auto sum = [&](auto wrap) {
             constexpr bool kWrap = decltype(wrap)::value;
-            tile_list_loop(list, i, cap, cnt, head,
-                           [&](uint32_t u) { return RecD{P[u], kWrap ? (uint32_t)W[u] : 0u}; },
-                           [&](const RecD& b) {
-                               const Geom<double> g = tile_geom<kWrap>(pi, b.p, b.w, C);
-                               density_add<KERNEL, double>(acc, g, rec_mass(b.p), C);
-                           });
+            tile_list_whole(list, i, cap, cnt, head,
+                            [&](uint32_t u) { return RecD{P.get(u), kWrap ? (uint32_t)W[u] : 0u}; },
+                            [&](const RecD& b, uint32_t k) {
+                                const Geom<double> g = tile_geom<kWrap>(pi, b.p, b.w, C);
+                                density_add<KERNEL, double>(acc, g, k < cnt ? rec_mass(b.p) : 0.0,
+                                                            C);
+                            });
         };
         if (wraps)
             sum(BoolC<true>());
@@ -1054,10 +1119,16 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
 // Momentum equation of the tile's targets with complete lists, FP64 (as
 // k_momentum), with momentum_close as the epilogue; per-tile partial sums of
 // the diagnostics into diag_part[q * stride + tile].  A staged particle takes
-// 73 bytes, so that one workgroup fills a CU's LDS: four waves, one per SIMD,
-// with all of its registers (eight staged records per thread in flight).
+// 73 bytes, so that one workgroup fills a CU's LDS and takes every P-th tile
+// (P workgroups, one per CU).  Its eight waves divide the work: four, one per
+// SIMD, take the tile's targets, the other four meanwhile hold the next tile's
+// records (18 registers each, eight per thread) and the cell ranges of the one
+// after in registers and store them when the four are done.  The loads wait in
+// waves of their own, since a wave's loads return in order and the pair loops
+// would wait for them.
+constexpr int kMom64Threads = 2 * CfgD::kThreads;
 template <int S, int KERNEL>
-__global__ __launch_bounds__(CfgD::kThreads, 1) void k_tile_momentum64(
+__global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
     int n, Grid G, PairConst<double> C, Tiles TL, int cap_union, const double4* __restrict__ pos,
     const double4* __restrict__ vel, const double2* __restrict__ rp,
     const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
@@ -1065,102 +1136,154 @@ __global__ __launch_bounds__(CfgD::kThreads, 1) void k_tile_momentum64(
     const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
     uint32_t* __restrict__ key, uint32_t* __restrict__ counts, uint32_t* __restrict__ flags,
     double* __restrict__ diag_part, int stride) {
-    __shared__ TileMeta<CfgD> M;
-    __shared__ uint16_t cellof[CfgD::kCap];
-    __shared__ double4 P[CfgD::kCap];
+    __shared__ TileMeta<CfgD> MM[2];
+    __shared__ uint16_t cellofs[2][CfgD::kCap];
+    __shared__ PosD P;
     __shared__ double2 Vxy[CfgD::kCap];
     __shared__ double2 RP[CfgD::kCap];
     __shared__ double Vz[CfgD::kCap];
     __shared__ uint8_t W[CfgD::kCap];
-    const int blk = xcd_block();
-    int c0[3];
-    tile_origin(TL, blk, c0);
-    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
-    double dsum[4] = {0.0, 0.0, 0.0, 0.0};
-    const bool empty = tile_empty(G, TL, c0, cstart, cend);
-    const uint32_t total =
-        empty ? 0u : tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
-    if (!empty && total <= (uint32_t)cap_union) {
-        struct Rc {
-            double4 p;
-            double2 vxy;
-            double vz;
-            double2 rp;
-        };
-        tile_stage(
-            TL, M, cellof,
-            [&](uint32_t j) {
-                const double4 v = vel[j];
-                return Rc{pos[j], make_double2(v.x, v.y), v.z, rp[j]};
-            },
-            [&](uint32_t u, const Rc& r, int ux, int uy, int uz) {
-                P[u] = r.p;
-                Vxy[u] = r.vxy;
-                Vz[u] = r.vz;
-                RP[u] = r.rp;
-                W[u] = (uint8_t)tile_image(G, TL, c0, ux, uy, uz);
-            });
-        __syncthreads();
-        const bool wraps = tile_wraps(G, TL, c0);
-        for (uint32_t tt = threadIdx.x; tt < M.ntargets; tt += CfgD::kThreads) {
-            uint32_t ui, i;
-            int uc[3];
-            tile_target(TL, M, tt, &ui, &i, uc);
-            const uint32_t cnt = ncnt[i];
-            const bool fluid = type[i] == 0;
-            const ListHead head = tile_list_head(list, i, cap);
-            const CloseIn ci = close_load<3>((int)i, St, drift, diag_part != nullptr);
-            if (cnt > cap) continue;  // the fallback's
-            double acc[3] = {0.0, 0.0, 0.0};
-            if (fluid) {
-                const double4 pi = P[ui];
-                double4 vi;
-                vi.x = Vxy[ui].x;
-                vi.y = Vxy[ui].y;
-                vi.z = Vz[ui];
-                vi.w = 0.0;
-                const double2 rpi = RP[ui];
-                double ax = C.g[0], ay = C.g[1], az = C.g[2];
-                struct Nb {
-                    double4 p;
-                    double2 vxy;
-                    double vz;
-                    double2 rp;
-                    uint32_t w;
-                };
-                auto sum = [&](auto wrap) {
-                    constexpr bool kWrap = decltype(wrap)::value;
-                    tile_list_loop<4>(
-                        list, i, cap, cnt, head,
-                        [&](uint32_t u) {
-                            return Nb{P[u], Vxy[u], Vz[u], RP[u], kWrap ? (uint32_t)W[u] : 0u};
-                        },
-                        [&](const Nb& b) {
-                            const Geom<double> g = tile_geom<kWrap>(pi, b.p, b.w, C);
-                            double4 vj;
-                            vj.x = b.vxy.x;
-                            vj.y = b.vxy.y;
-                            vj.z = b.vz;
-                            vj.w = 0.0;
-                            momentum_add<3, KERNEL, double>(ax, ay, az, g, rec_mass(b.p), vi, rpi,
-                                                            vj, b.rp, C);
-                        });
-                };
-                if (wraps)
-                    sum(BoolC<true>());
-                else
-                    sum(BoolC<false>());
-                acc[0] = ax;
-                acc[1] = ay;
-                acc[2] = az;
-            }
-            double dv[4] = {0.0, 0.0, 0.0, 0.0};
-            momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, key, counts,
-                                      flags, diag_part != nullptr, dv, &ci);
-            for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
+    // set-up and staging thread: 0 .. 255 in the loader waves, the others take
+    // part in the set-up's barriers
+    const int tid = (int)(threadIdx.x ^ (unsigned)CfgD::kThreads);
+    // uniform over a wave, and known to be
+    const bool loader = __builtin_amdgcn_readfirstlane(tid) < CfgD::kThreads;
+    const int NP = (int)gridDim.x;
+    const int t0 = xcd_block();
+    const int t1 = TL.ntiles;
+    if (t0 >= t1) return;  // the whole workgroup
+    struct Rc {
+        double4 p;
+        double2 vxy;
+        double vz;
+        double2 rp;
+    };
+    auto load_rc = [&](uint32_t j) {
+        const double4 v = vel[j];
+        return Rc{pos[j], make_double2(v.x, v.y), v.z, rp[j]};
+    };
+    int cs[3] = {0, 0, 0};  // origin of the tile being stored
+    auto store_rc = [&](uint32_t u, const Rc& r, int ux, int uy, int uz) {
+        P.put(u, r.p);
+        Vxy[u] = r.vxy;
+        Vz[u] = r.vz;
+        RP[u] = r.rp;
+        W[u] = (uint8_t)tile_image(G, TL, cs, ux, uy, uz);
+    };
+    auto fits = [&](const TileMeta<CfgD>& M) { return M.total <= (uint32_t)cap_union; };
+    // prologue (t = t0 - NP): tile t0 set up; the loop's first round stages it
+    tile_origin(TL, t0, cs);
+    tile_setup(G, TL, cs, cstart, cend, n, MM[0], tid);
+    tile_cellof<CfgD, kMom64Threads>(TL, MM[0], cellofs[0]);
+    // set-up of the tile after the next one into the meta that tile t leaves,
+    // by all waves (the loaders hold its cell ranges); publishes the staging
+    auto set_up = [&](int t, int cur, const SetupLoads& sl) {
+        if (t + 2 * NP < t1) {
+            int c2[3];
+            tile_origin(TL, t + 2 * NP, c2);
+            tile_setup_finish(G, TL, c2, n, sl, MM[cur], tid);
+            tile_cellof<CfgD, kMom64Threads>(TL, MM[cur], cellofs[cur]);
+        } else {
+            __syncthreads();
         }
+    };
+    // the two roles meet at the same barriers: one for the diagnostics' sums,
+    // one when tile t's records, meta and cell table are free, and set_up's
+    if (loader) {
+        int cur = 1;
+        for (int t = t0 - NP; t < t1; t += NP, cur ^= 1) {
+            const TileMeta<CfgD>& MN = MM[cur ^ 1];
+            const bool stage_next = t + NP < t1 && fits(MN);
+            SetupLoads sl{};
+            if (t + 2 * NP < t1) {
+                int c2[3];
+                tile_origin(TL, t + 2 * NP, c2);
+                sl = tile_setup_loads(G, TL, c2, cstart, cend, tid);
+            }
+            StageRegs<CfgD, Rc> R;
+            if (stage_next) tile_stage_loads(MN, cellofs[cur ^ 1], load_rc, R, tid);
+            if (diag_part && t >= 0) __syncthreads();
+            __syncthreads();
+            if (stage_next) {
+                tile_origin(TL, t + NP, cs);
+                tile_stage_store(TL, MN, cellofs[cur ^ 1], R, store_rc, tid);
+            }
+            set_up(t, cur, sl);
+        }
+        return;
     }
-    if (diag_part) tile_block_sum<4, CfgD::kThreads>(dsum, diag_part, blk, stride);
+    int cur = 1;
+    for (int t = t0 - NP; t < t1; t += NP, cur ^= 1) {
+        const TileMeta<CfgD>& M = MM[cur];
+        double dsum[4] = {0.0, 0.0, 0.0, 0.0};
+        if (t >= 0 && fits(M)) {
+            int c0[3];
+            tile_origin(TL, t, c0);
+            const bool wraps = tile_wraps(G, TL, c0);
+            for (uint32_t tt = (uint32_t)(tid - CfgD::kThreads); tt < M.ntargets;
+                 tt += CfgD::kThreads) {
+                uint32_t ui, i;
+                int uc[3];
+                tile_target(TL, M, tt, &ui, &i, uc);
+                const uint32_t cnt = ncnt[i];
+                const bool fluid = type[i] == 0;
+                const ListHead head = tile_list_head(list, i, cap);
+                const CloseIn ci = close_load<3>((int)i, St, drift, diag_part != nullptr);
+                if (cnt > cap) continue;  // the fallback's
+                double acc[3] = {0.0, 0.0, 0.0};
+                if (fluid) {
+                    const double4 pi = P.get(ui);
+                    double4 vi;
+                    vi.x = Vxy[ui].x;
+                    vi.y = Vxy[ui].y;
+                    vi.z = Vz[ui];
+                    vi.w = 0.0;
+                    const double2 rpi = RP[ui];
+                    double ax = C.g[0], ay = C.g[1], az = C.g[2];
+                    struct Nb {
+                        double4 p;
+                        double2 vxy;
+                        double vz;
+                        double2 rp;
+                        uint32_t w;
+                    };
+                    auto sum = [&](auto wrap) {
+                        constexpr bool kWrap = decltype(wrap)::value;
+                        // (the target itself adds exact zeros, see momentum_add)
+                        tile_list_whole(
+                            list, i, cap, cnt, head,
+                            [&](uint32_t u) {
+                                return Nb{P.get(u), Vxy[u], Vz[u], RP[u], kWrap ? (uint32_t)W[u] : 0u};
+                            },
+                            [&](const Nb& b, uint32_t) {
+                                const Geom<double> g = tile_geom<kWrap>(pi, b.p, b.w, C);
+                                double4 vj;
+                                vj.x = b.vxy.x;
+                                vj.y = b.vxy.y;
+                                vj.z = b.vz;
+                                vj.w = 0.0;
+                                momentum_add<3, KERNEL, double>(ax, ay, az, g, rec_mass(b.p), vi, rpi,
+                                                                vj, b.rp, C);
+                            });
+                    };
+                    if (wraps)
+                        sum(BoolC<true>());
+                    else
+                        sum(BoolC<false>());
+                    acc[0] = ax;
+                    acc[1] = ay;
+                    acc[2] = az;
+                }
+                double dv[4] = {0.0, 0.0, 0.0, 0.0};
+                momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, key, counts,
+                                          flags, diag_part != nullptr, dv, &ci);
+                for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
+            }
+        }
+        if (diag_part && t >= 0) tile_block_sum<4, CfgD::kThreads>(dsum, diag_part, t, stride);
+        __syncthreads();
+        set_up(t, cur, SetupLoads{});
+    }
 }
 
 // Fallback density: the targets the tile build left (count above cap, or
