@@ -7,11 +7,14 @@ using namespace sph_host;
 
 #include <mutex>
 
-// Static workspace of sph_step_noalloc: one copy per device.  Host code never
+constexpr size_t kScratchBytes = SPH_NOALLOC_SCRATCH_BYTES + ((size_t)32 << 20);
+// Static workspace of sph_step_noalloc: SPH_NOALLOC_SCRATCH_BYTES and a
+// margin for the arrays the layout has gained since, so that every size that
+// was taken still is; one copy per device.  Host code never
 // passes this name to a kernel (in host code it is a stand-in, not a device
 // address); it uses the address hipGetSymbolAddress returns for the current
 // device, kept per device below.
-static __device__ __align__(256) unsigned char scratch[SPH_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -154,9 +157,9 @@ int sph_step_noalloc(const sph_params* prm, sph_particles* pa, int64_t nsteps, i
     int64_t ncells;
     SPH_TRY(make_grid(prm, &G, &ncells));
     const Layout L = make_layout(prm, G, pa->n, ncells, 0);
-    if (L.bytes > SPH_NOALLOC_SCRATCH_BYTES)
+    if (L.bytes > kScratchBytes)
         return fail(SPH_EWORKSPACE, "the step needs %zu bytes of workspace, the static scratch holds %zu",
-                    L.bytes, (size_t)SPH_NOALLOC_SCRATCH_BYTES);
+                    L.bytes, kScratchBytes);
     void* ws = nullptr;
     SPH_TRY(scratch_address(&ws));
     // the flag words and interaction counters start at zero (a fill kernel,
@@ -166,7 +169,7 @@ int sph_step_noalloc(const sph_params* prm, sph_particles* pa, int64_t nsteps, i
     launch(K_FILL, sph::k_fill_u32, blocks_for(words), st, words, 0u, (uint32_t*)ws);
     SPH_TRY(launch_check("k_fill_u32"));
     return dispatch(prm, [&](auto A) {
-        return decltype(A)::step(prm, pa, nsteps, prime_accel, ws, (size_t)SPH_NOALLOC_SCRATCH_BYTES,
+        return decltype(A)::step(prm, pa, nsteps, prime_accel, ws, kScratchBytes,
                                  diag, stream);
     });
 }

@@ -60,14 +60,15 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + sph::kBlock - 1) 
 // Opt-in per-kernel event timing (benchmark instrumentation)
 
 enum KernelId {
-    K_FILL, K_HASH, K_CHUNK_SUM, K_CHUNK_SCAN, K_SCATTER, K_RANK_GATHER, K_PACK, K_DENSITY,
-    K_MOMENTUM, K_EOS, K_NBR_COUNT, K_NBR_FILL, K_CELL_RANGES, K_COPY, K_DIAG, K_ADJ_SEED,
+    K_FILL, K_HASH, K_CHUNK_SUM, K_CHUNK_SCAN, K_CELL_SUMS, K_CELL_PLACE, K_CELL_GATHER, K_PACK, K_DENSITY,
+    K_MOMENTUM, K_EOS, K_NBR_COUNT, K_NBR_FILL, K_DIAG, K_ADJ_SEED,
     K_ADJ_PAIR1, K_ADJ_PAIR2, K_ADJ_REDUCE, K_ADJ_KICK, K_NLIST, K_CONT, K_TILE_BUILD,
     K_TILE_DENSITY, K_TILE_MOMENTUM, K_TILE_FALLBACK, K_COUNT
 };
 inline const char* const kKernelNames[K_COUNT] = {
-    "fill", "drift_hash", "chunk_sum", "chunk_scan", "scatter", "rank_gather", "pack",
-    "density", "momentum", "eos", "nbr_count", "nbr_fill", "cell_ranges", "copy_state", "diag",
+    "fill", "drift_hash", "chunk_sum", "chunk_scan", "cell_sums", "cell_place", "cell_gather",
+    "pack",
+    "density", "momentum", "eos", "nbr_count", "nbr_fill", "diag",
     "adj_seed", "adj_pair1", "adj_pair2", "adj_reduce", "adj_kick", "nlist", "cont_momentum",
     "tile_build", "tile_density", "tile_momentum", "tile_fallback"};
 
@@ -384,14 +385,50 @@ struct StateOff {
     size_t x, u, a, m, type, id, rho, p, arho;
 };
 
+// Shape of the sort.  A cell's row in the table (1 << shift slots) holds
+// nearly twice the particles of a lattice at h = 1.3 dx (2D 16 slots for
+// 6.8 particles, 3D half-size cells 8 for 2.2, whole ones 32 for 17.6);
+// grids so sparse that the table would take more than 128 bytes per particle
+// do with chains.  The last launch's cells per wave: about one particle per
+// lane (sparse grids have many empty cells beside full ones, so that the
+// lattice counts where the mean is below it).
+// Grids of up to kDirectCells cells count the particles before a wave in the
+// wave itself (16 bytes a lane and round); above, k_cell_sums does.
+constexpr int64_t kDirectCells = 4096;
+struct SortShape {
+    int shift, cpw;
+    int64_t ngroups;
+    int nblocks;
+    bool sparse;  // k_cell_place and k_slot_gather
+};
+inline SortShape sort_shape(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells) {
+    double occ = 1.0;
+    for (int k = 0; k < p->dim; ++k) occ *= 1.3 * G.cs[k] / p->h;
+    int shift = 3;
+    while (shift < 6 && (double)(1 << shift) < 1.8 * occ) ++shift;  // 4 rows: 64 kSortRounds
+    occ = std::max(occ, (double)n / (double)ncells);
+    int cpw = 4;
+    while (cpw < 64 && 2 * cpw * occ <= 75.0 && (2 * cpw) << shift <= 64 * sph::kSortRounds)
+        cpw *= 2;
+    if ((ncells << shift) > 32 * n) shift = -1;
+    while (cpw < 64 && ncells / cpw > ((int64_t)1 << 25)) {
+        cpw *= 2;
+        shift = -1;
+    }
+    const int64_t groups = (ncells + cpw - 1) / cpw;
+    const int64_t blocks = (groups + sph::kBlock / 64 - 1) / (sph::kBlock / 64);
+    return {shift, cpw, groups, (int)blocks, ncells > n && ncells > kDirectCells};
+}
+
 // One recompute-tape slot: the pair records and sort results of one step.
 struct SlotOff {
     size_t pos, vel, rp, skey, perm, type, start;
 };
 
 struct Layout {
-    size_t flags, counts, start, chunks, key, tmp, perm, skey, ncnt, lcnt, list;
+    size_t flags, counts, counts2, head, table, start, chunks, sub, next, tmp, perm, skey, lcnt, list;
     uint32_t cap;
+    SortShape sort;
     sph::Tiles tiles;
     StateOff s1, s2;
     size_t pos, vel, rp, diag;
@@ -478,13 +515,17 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
     L.flags = take(16 + 8 * std::max<size_t>(std::max(nlist_shape(n, ncells).blocks, blocks_for(n)),
                                              ntiles));
     L.counts = take(4 * (size_t)ncells);
+    L.counts2 = take(4 * (size_t)ncells);
+    L.head = take(4 * (size_t)ncells);
+    L.sort = sort_shape(p, G, n, ncells);
+    L.table = take(L.sort.shift < 0 ? 0 : (size_t)4 * ((size_t)ncells << L.sort.shift));
     L.start = take(4 * ((size_t)ncells + 1));
     L.chunks = take(8 * nchunks);
-    L.key = take(4 * N);
-    L.tmp = take(4 * N);
+    L.sub = take(4 * (size_t)L.sort.ngroups);
+    L.next = take(4 * N);
+    L.tmp = take(L.sort.sparse ? 4 * N : 0);
     L.perm = take(4 * N);
     L.skey = take(4 * N);
-    L.ncnt = take(4 * N);
     L.cap = list_cap(p, n);
     L.lcnt = take(4 * N);
     L.list = take(4 * (size_t)L.cap * (size_t)sph::kListTile *
@@ -632,11 +673,16 @@ struct Engine {
 
     uint32_t* flags() const { return (uint32_t*)(ws + L.flags); }
     unsigned long long* pairs() const { return (unsigned long long*)(ws + L.flags + 16); }
-    uint32_t* counts() const { return (uint32_t*)(ws + L.counts); }
     uint64_t* chunks() const { return (uint64_t*)(ws + L.chunks); }
-    uint32_t* key() const { return (uint32_t*)(ws + L.key); }
-    uint32_t* tmp() const { return (uint32_t*)(ws + L.tmp); }
-    uint32_t* ncnt() const { return (uint32_t*)(ws + L.ncnt); }
+    // two buffers of cell counts: a sort reads one and clears the other, which
+    // the next hash fills
+    int cbuf = 0;
+    uint32_t* counts(int b) const { return (uint32_t*)(ws + (b ? L.counts2 : L.counts)); }
+    sph::CellList cells() const {
+        return {counts(cbuf), (uint32_t*)(ws + L.table), (uint32_t*)(ws + L.head),
+                (uint32_t*)(ws + L.next), L.sort.shift};
+    }
+    sph::DiagJob diag_job{0, nullptr, nullptr};  // not yet summed
     uint32_t* lcnt() const { return (uint32_t*)(ws + L.lcnt); }
     uint32_t* list() const { return (uint32_t*)(ws + L.list); }
 
@@ -686,13 +732,14 @@ struct Engine {
     }
 
     int zero_counts() {
-        launch(K_FILL, sph::k_fill_u32, blocks_for(ncells), st, ncells, 0u, counts());
+        cbuf = 0;
+        launch(K_FILL, sph::k_fill_u32, blocks_for(ncells), st, ncells, 0u, counts(0));
         return launch_check("k_fill_u32");
     }
 
     // exclusive scan of `len` u32 counts into out[0..len] (short arrays, e.g.
-    // the cells of a 512^2 lattice, in chunks of 1,024 so that both launches
-    // have several times more blocks)
+    // the particles of a 512^2 lattice, in chunks of 1,024 so that both
+    // launches have several times more blocks)
     template <typename OUT>
     int scan(const uint32_t* in, int64_t len, OUT* out) {
         if (len <= sph::kScanShortMax) return scan_items<OUT, sph::kScanItemsShort>(in, len, out);
@@ -702,43 +749,103 @@ struct Engine {
     int scan_items(const uint32_t* in, int64_t len, OUT* out) {
         constexpr int64_t chunk = (int64_t)sph::kBlock * ITEMS;
         const unsigned nch = (unsigned)((len + chunk - 1) / chunk);
-        {
         launch(K_CHUNK_SUM, sph::k_chunk_sum<ITEMS>, nch, st, in, len, chunks());
         SPH_TRY(launch_check("k_chunk_sum"));
-        }
         launch(K_CHUNK_SCAN, sph::k_chunk_scan<OUT, ITEMS>, nch, st, in, len, chunks(), out);
         return launch_check("k_chunk_scan");
     }
 
-    // hash (with the opening half kick + drift if drift), counting sort, and
-    // gather of src into dst in sorted order with pair records packed.
-    // hashed: src already holds the drifted positions with keys and counts
-    // (from the epilogue of the previous momentum launch).
-    // eos: gather rho, and form p and the (rho, p/rho^2) records from it
-    // (continuity scheme); predict: records of u + predict a and the EOS at
-    // rho + predict arho (the predictor-corrector's predicted end state);
-    // kick_rho: the opening drift also kicks rho by dt/2 arho.
-    int sort_into(const sph::State& src, const sph::State& dst, bool drift, bool copy_derived,
-                  bool hashed = false, bool eos = false, double predict = 0.0,
-                  bool kick_rho = false) {
-        const unsigned nb = blocks_for(n);
-        using TA = T;
-        if (!hashed) {
-            launch(K_HASH, sph::k_drift_hash<DIM, TA>, nb, st,
-                n, src, G, 0.5 * prm->dt, prm->dt, drift ? 1 : 0, kick_rho ? 1 : 0, key(),
-                counts(), flags());
+    // Sums the diagnostics of the last pass, if that is still to be done.
+    int flush_diag() {
+        if (!diag_job.nparts) return SPH_OK;
+        launch(K_DIAG, sph::k_diag_final<DIM>, 1, st, diag_job);
+        diag_job.nparts = 0;
+        return launch_check("k_diag_final");
+    }
+
+    // What one sort does besides sorting.
+    struct SortOp {
+        const sph::State* from = nullptr;  // the hash reads this state and copies it into src
+        int copy = 0;               // ... (kCopy bits)
+        bool drift = false;         // opening half kick and drift
+        bool kick_rho = false;      // ... which also kicks rho by dt/2 arho
+        bool hashed = false;        // src already holds the drifted positions and the cell lists
+                                    // (from the epilogue of the previous momentum launch)
+        bool copy_derived = false;  // gather a, rho, p, arho as they are
+        bool records = true;        // pack the pair records
+        bool want_perm = false;     // keep the permutation (the adjoint's)
+        bool eos = false;           // gather rho, and form p and the (rho, p/rho^2) records from
+                                    // it (continuity scheme)
+        double predict = 0.0;       // records of u + predict a and the EOS at rho + predict arho
+                                    // (the predictor-corrector's predicted end state)
+        uint32_t *cs = nullptr, *ce = nullptr;  // cell ranges for the caller
+    };
+
+    // Hash, counting sort, and gather of src into dst in sorted order.
+    int sort_into(const sph::State& src, const sph::State& dst, const SortOp& op) {
+        if (!op.hashed) {
+            launch(K_HASH, sph::k_drift_hash<DIM, T>, blocks_for(n), st, n,
+                   op.from ? *op.from : src, src, G, 0.5 * prm->dt, prm->dt, op.drift ? 1 : 0,
+                   op.kick_rho ? 1 : 0, op.from ? op.copy : 0, cells(), flags());
             SPH_TRY(launch_check("k_drift_hash"));
         }
-        SPH_TRY(scan<uint32_t>(counts(), ncells, start()));
-        {
-        launch(K_SCATTER, sph::k_scatter, nb, st, n, key(), start(), counts(), tmp());
-        SPH_TRY(launch_check("k_scatter"));
+        const SortShape& sh = L.sort;
+        sph::SortGrid SG;
+        SG.ncells = ncells;
+        SG.cpw = sh.cpw;
+        SG.nblocks = sh.nblocks;
+        SG.chunk_cells = 1;
+        SG.scanned = 0;
+        SG.sums = SG.sub = nullptr;
+        SG.clear = counts(cbuf ^ 1);
+        SG.cs = op.cs;
+        SG.ce = op.ce;
+        if (ncells > kDirectCells || sh.sparse) {
+            // chunks of 1,024 cells up to 64 chunks, of 4,096 above
+            if (ncells <= 64 * sph::kBlock * sph::kScanItemsShort)
+                SPH_TRY(cell_sums<sph::kScanItemsShort>(&SG));
+            else
+                SPH_TRY(cell_sums<sph::kScanItems>(&SG));
         }
-        launch(K_RANK_GATHER, sph::k_rank_gather<DIM, T>, nb, st, n, tmp(), key(), start(), src, dst, G,
-                                                             perm(), skey(), pos(), vel(),
-                                                             copy_derived ? 1 : 0, typetape, C,
-                                                             rp(), eos ? 1 : 0, predict);
-        return launch_check("k_rank_gather");
+        const sph::GatherOp go{op.records ? 1 : 0, op.copy_derived ? 1 : 0, op.eos ? 1 : 0,
+                               op.predict};
+        if (sh.sparse) {
+            launch(K_CELL_PLACE, sph::k_cell_place<DIM>, blocks_for(ncells), st, SG, cells(),
+                   start(), skey(), (uint32_t*)(ws + L.tmp));
+            SPH_TRY(launch_check("k_cell_place"));
+            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n), st, n,
+                   (const uint32_t*)(ws + L.tmp), start(), src, dst, G, perm(),
+                   op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(), go);
+            cbuf ^= 1;
+            return launch_check("k_slot_gather");
+        }
+        // the diagnostics of the step before go to one more block (of the
+        // first launch of the sort)
+        const bool dg = diag_job.nparts > 0;
+        launch(K_CELL_GATHER, sph::k_cell_gather<DIM, T>, (unsigned)sh.nblocks + (dg ? 1u : 0u), st,
+               n, SG, cells(), src, dst, G, start(), perm(), op.want_perm ? 1 : 0, skey(), pos(),
+               vel(), typetape, C, rp(), go, diag_job);
+        diag_job.nparts = 0;
+        cbuf ^= 1;
+        return launch_check("k_cell_gather");
+    }
+    template <int ITEMS>
+    int cell_sums(sph::SortGrid* SG) {
+        SG->chunk_cells = sph::kBlock * ITEMS;
+        const int nch = (int)((ncells + SG->chunk_cells - 1) / SG->chunk_cells);
+        uint32_t* sums = (uint32_t*)chunks();
+        uint32_t* sub = (uint32_t*)(ws + L.sub);
+        const bool dg = diag_job.nparts > 0;
+        launch(K_CELL_SUMS, sph::k_cell_sums<DIM, ITEMS>, (unsigned)nch + (dg ? 1u : 0u), st,
+               counts(cbuf), ncells, SG->cpw, nch, sums, sub, diag_job);
+        SPH_TRY(launch_check("k_cell_sums"));
+        diag_job.nparts = 0;
+        SG->sums = sums;
+        SG->sub = sub;
+        SG->scanned = nch > sph::kWaveSums;
+        if (!SG->scanned) return SPH_OK;
+        launch(K_CELL_SUMS, sph::k_sums_scan, 1, st, nch, sums);
+        return launch_check("k_sums_scan");
     }
 
     // Neighbour lists of the current records (count_pairs: add the number
@@ -837,26 +944,25 @@ struct Engine {
                     launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum64<S, KERNEL>, wgs,
                              sph::kMom64Threads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
                              cs, ce, tcap(), (const uint4*)list(), lcnt(), s, kick ? 1 : 0,
-                             drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(), part,
+                             drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(), part,
                              stride);
                 else
                     launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<S, KERNEL>, wgs, Cfg::kThreads,
                              st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type, cs, ce, tcap(),
                              (const uint4*)list(), lcnt(), s, kick ? 1 : 0, drift ? 1 : 0,
-                             0.5 * prm->dt, prm->dt, key(), counts(), flags(), part, stride);
+                             0.5 * prm->dt, prm->dt, cells(), flags(), part, stride);
             });
             SPH_TRY(launch_check("k_tile_momentum"));
             with_reach([&](auto R) {
                 launch(K_TILE_FALLBACK,
                        sph::k_tile_fallback_momentum<decltype(R)::value, KERNEL, T>, fb, st, n, G, C,
                        skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(), s, kick ? 1 : 0,
-                       drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(),
+                       drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(),
                        part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword());
             });
             SPH_TRY(launch_check("k_tile_fallback_momentum"));
-            if (!diag_out) return SPH_OK;
-            launch(K_DIAG, sph::k_diag_final<DIM>, 1, st, stride, part, diag_out);
-            return launch_check("k_diag_final");
+            if (diag_out) diag_job = {stride, part, diag_out};
+            return SPH_OK;
         }
         return fail(SPH_EINVAL, "tiled passes need 3D");
     }
@@ -886,13 +992,12 @@ struct Engine {
                 launch(K_MOMENTUM, sph::k_momentum<DIM, decltype(R)::value, KERNEL, T>, nb, st,
                     n, G, C, skey(), pos(), vel(), rp(), s.type, cs, ce, list_or_null(), lcnt(),
                     L.cap, s, kick ? 1 : 0,
-                    drift ? 1 : 0, 0.5 * prm->dt, prm->dt, key(), counts(), flags(), part);
+                    drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(), part);
             });
             SPH_TRY(launch_check("k_momentum"));
         }
-        if (!diag_out) return SPH_OK;
-        launch(K_DIAG, sph::k_diag_final<DIM>, 1, st, (int)nb, part, diag_out);
-        return launch_check("k_diag_final");
+        if (diag_out) diag_job = {(int)nb, part, diag_out};
+        return SPH_OK;
     }
 
     int pack(const sph::State& s, bool with_rp) {
@@ -901,21 +1006,23 @@ struct Engine {
         return launch_check("k_pack");
     }
 
-    int copy(const sph::State& src, const sph::State& dst) {
-        launch(K_COPY, sph::k_copy_state<DIM, T>, blocks_for(n), st, n, src, dst);
-        return launch_check("k_copy_state");
-    }
-
     // --- entry points ---------------------------------------------------
 
+    // The hash copies every field into the workspace and the gather brings
+    // them back in order, with the cell ranges.
     int bin_sort(sph_particles* pa, uint32_t* cs_out, uint32_t* ce_out) {
         const sph::State user = user_state(pa, prm);
         const sph::State tmp_state = ws_state(ws, L.s1, prm, n);
         SPH_TRY(zero_counts());
-        SPH_TRY(sort_into(user, tmp_state, false, true));
-        SPH_TRY(copy(tmp_state, user));
-        launch(K_CELL_RANGES, sph::k_cell_ranges, blocks_for(ncells), st, ncells, start(), cs_out, ce_out);
-        return launch_check("k_cell_ranges");
+        SortOp op;
+        op.from = &user;
+        op.copy = sph::kCopyBase | sph::kCopyAccel | sph::kCopyRho | sph::kCopyP |
+                  (user.arho ? sph::kCopyArho : 0);
+        op.copy_derived = true;
+        op.records = false;
+        op.cs = cs_out;
+        op.ce = ce_out;
+        return sort_into(tmp_state, user, op);
     }
 
     int density_only(sph_particles* pa, const uint32_t* cs, const uint32_t* ce) {
@@ -947,11 +1054,11 @@ struct Engine {
         {
         with_reach([&](auto R) {
             launch(K_NBR_COUNT, sph::k_nbr_count<DIM, decltype(R)::value, T>, blocks_for(n), st,
-                n, G, C, skey(), pos(), cs, ce, ncnt());
+                n, G, C, skey(), pos(), cs, ce, lcnt());
         });
         SPH_TRY(launch_check("k_nbr_count"));
         }
-        SPH_TRY(scan<int64_t>(ncnt(), n, offsets));
+        SPH_TRY(scan<int64_t>(lcnt(), n, offsets));
         int64_t tot = 0;
         SPH_HIP(hipMemcpyAsync(&tot, offsets + n, sizeof tot, hipMemcpyDeviceToHost, st));
         SPH_HIP(hipStreamSynchronize(st));
@@ -967,31 +1074,37 @@ struct Engine {
         return launch_check("k_nbr_fill");
     }
 
+    // Every evaluation sorts from one state into the other, so that an even
+    // number of them ends in the user's arrays; with an odd number the first
+    // hash writes its state to the workspace.
     int step(sph_particles* pa, int64_t nsteps, int prime, double* diag_out) {
         const sph::State user = user_state(pa, prm);
         const sph::State wst = ws_state(ws, L.s1, prm, n);
-        sph::State cur = user, nxt = wst;
+        const bool odd = ((nsteps + (prime ? 1 : 0)) & 1) != 0;
+        sph::State cur = odd ? wst : user, nxt = odd ? user : wst;
         const uint32_t* cs = start();
         const uint32_t* ce = start() + 1;
         SPH_TRY(zero_counts());
-        bool hashed = false;  // cur already drifted and hashed by a fused epilogue
+        SortOp op;
+        if (odd) op.from = &user;
+        op.copy = sph::kCopyBase;
         if (prime) {
-            SPH_TRY(sort_into(cur, nxt, false, false));
+            SPH_TRY(sort_into(cur, nxt, op));
             SPH_TRY(density(nxt, cs, ce, true));
             SPH_TRY(momentum(nxt, cs, ce, false, nsteps > 0));
             std::swap(cur, nxt);
-            hashed = nsteps > 0;
+            op.hashed = true;  // cur is drifted and hashed by the epilogue
         }
+        op.drift = true;
         for (int64_t s = 0; s < nsteps; ++s) {
             const bool last = s == nsteps - 1;
-            SPH_TRY(sort_into(cur, nxt, true, false, hashed));
+            SPH_TRY(sort_into(cur, nxt, op));
             SPH_TRY(density(nxt, cs, ce, true));
             SPH_TRY(momentum(nxt, cs, ce, true, !last, diag_out ? diag_out + s * (1 + DIM) : nullptr));
             std::swap(cur, nxt);
-            hashed = !last;
+            op.hashed = true;
         }
-        if (cur.m != user.m) SPH_TRY(copy(cur, user));
-        return SPH_OK;
+        return flush_diag();
     }
 
     // Continuity scheme: lists, then one pass for drho/dt and a with the
@@ -1004,12 +1117,11 @@ struct Engine {
             launch(K_CONT, sph::k_cont_momentum<DIM, decltype(R)::value, KERNEL, T>, nb, st, n, G,
                    C, skey(), pos(), vel(), rp(), (const uint8_t*)s.type, start(), start() + 1,
                    list_or_null(), lcnt(), L.cap, s, euler ? 1 : 0, kick ? 1 : 0, drift ? 1 : 0,
-                   prm->dt, key(), counts(), flags(), part, L.cap ? 0 : 1, pairs());
+                   prm->dt, cells(), flags(), part, L.cap ? 0 : 1, pairs());
         });
         SPH_TRY(launch_check("k_cont_momentum"));
-        if (!diag_out) return SPH_OK;
-        launch(K_DIAG, sph::k_diag_final<DIM>, 1, st, (int)nb, part, diag_out);
-        return launch_check("k_diag_final");
+        if (diag_out) diag_job = {(int)nb, part, diag_out};
+        return SPH_OK;
     }
 
     // Euler stage (the paper's dam-break example): per step, sort with rho
@@ -1019,32 +1131,37 @@ struct Engine {
     int step_continuity(sph_particles* pa, int64_t nsteps, int prime, double* diag_out) {
         const sph::State user = user_state(pa, prm);
         const sph::State wst = ws_state(ws, L.s1, prm, n);
-        sph::State cur = user, nxt = wst;
         const bool euler = prm->integrator == SPH_INTEGRATOR_EULER;
         const double hdt = 0.5 * prm->dt;
+        prime = prime && !euler;
+        // as step(): an odd number of sorts starts from the workspace
+        const bool odd = ((nsteps + (prime ? 1 : 0)) & 1) != 0;
+        sph::State cur = odd ? wst : user, nxt = odd ? user : wst;
         SPH_TRY(zero_counts());
-        bool hashed = false;  // cur already opened and hashed by a fused epilogue
-        if (!euler && prime) {
-            SPH_TRY(sort_into(cur, nxt, false, false, false, true));
+        SortOp op;
+        if (odd) op.from = &user;
+        op.copy = sph::kCopyBase | sph::kCopyRho;
+        op.eos = true;
+        if (prime) {
+            SPH_TRY(sort_into(cur, nxt, op));
             SPH_TRY(cont_pass(nxt, false, false, nsteps > 0, nullptr));
             std::swap(cur, nxt);
-            hashed = nsteps > 0;
+            op.hashed = true;
+        }
+        if (!euler) {
+            op.copy |= sph::kCopyAccel | sph::kCopyArho;
+            op.drift = op.kick_rho = true;
+            op.predict = hdt;
         }
         for (int64_t s = 0; s < nsteps; ++s) {
             const bool last = s == nsteps - 1;
             double* dg = diag_out ? diag_out + s * (1 + DIM) : nullptr;
-            if (euler) {
-                SPH_TRY(sort_into(cur, nxt, false, false, s > 0, true));
-                SPH_TRY(cont_pass(nxt, true, false, !last, dg));
-            } else {
-                SPH_TRY(sort_into(cur, nxt, true, false, hashed, true, hdt, true));
-                SPH_TRY(cont_pass(nxt, false, true, !last, dg));
-            }
+            SPH_TRY(sort_into(cur, nxt, op));
+            SPH_TRY(cont_pass(nxt, euler, !euler, !last, dg));
             std::swap(cur, nxt);
-            hashed = !last;
+            op.hashed = true;
         }
-        if (cur.m != user.m) SPH_TRY(copy(cur, user));
-        return SPH_OK;
+        return flush_diag();
     }
 
     // (dA/dx)^T lhat -> lxd, (dA/dv)^T lhat -> lvd, (dA/dnu)^T lhat added to
@@ -1093,12 +1210,16 @@ struct Engine {
         const sph::State user = user_state(ck, prm);
         const sph::State s1 = ws_state(ws, L.s1, prm, n);
         const sph::State s2 = ws_state(ws, L.s2, prm, n);
-        SPH_TRY(copy(user, s2));
         sph::State cur = s2, nxt = s1;
         SPH_TRY(zero_counts());
+        SortOp op;
+        op.from = &user;
+        op.copy = sph::kCopyBase;
+        op.drift = op.want_perm = true;
         for (int64_t s = 0; s < k; ++s) {
             tape_records(s);
-            SPH_TRY(sort_into(cur, nxt, true, false, s > 0));
+            op.hashed = s > 0;
+            SPH_TRY(sort_into(cur, nxt, op));
             SPH_TRY(density(nxt, start(), start() + 1, true));
             SPH_TRY(momentum(nxt, start(), start() + 1, true, s < k - 1));
             std::swap(cur, nxt);
@@ -1129,7 +1250,9 @@ struct Engine {
         const sph::State s1 = ws_state(ws, L.s1, prm, n);
         default_records();
         SPH_TRY(zero_counts());
-        SPH_TRY(sort_into(user, s1, false, false));
+        SortOp op;
+        op.want_perm = true;
+        SPH_TRY(sort_into(user, s1, op));
         SPH_TRY(density(s1, start(), start() + 1, true));
         // the adjoint passes read global-format lists: rebuilt if the density
         // went through the tiles

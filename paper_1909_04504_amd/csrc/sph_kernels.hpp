@@ -10,10 +10,11 @@
 //  * Particles are kept sorted by cell key, so the particles of a stencil row
 //    of cells are contiguous and every cell walk reads contiguous,
 //    cache-resident slot ranges.  The sort is a counting sort on cell keys:
-//    integer atomics count particles per cell, a two-kernel scan turns counts
-//    into cell offsets, an atomic scatter groups particles by cell and a
-//    per-cell rank (number of smaller previous indices in the same cell)
-//    makes the result identical to a stable sort, hence deterministic.
+//    integer atomics count the particles of each cell and chain them, and one
+//    launch (two on large grids) turns counts into cell offsets, follows the
+//    chains of a block's cells and gathers their particles; a per-cell rank
+//    (number of smaller previous indices in the same cell) makes the result
+//    identical to a stable sort, hence deterministic.
 //  * Pair records are packed per sorted slot: the position record, the
 //    velocity as a 4-vector and (rho, P = p/rho^2) as a 2-vector (in 2D
 //    (rho, P) ride in the velocity record and the particle type in the
@@ -903,38 +904,53 @@ __device__ __forceinline__ void for_each_neighbor(
 }
 
 // ---------------------------------------------------------------------------
-// Lanes of the wave holding the same key (active lanes only): the group's
-// leader lane, this lane's rank in the group (lane order) and the group size.
-// The particles of a wave are consecutive in the previous sorted order, so a
-// wave holds ~dim-dependent few distinct cells and the loop runs once per
-// distinct key; one atomic per group replaces one per particle.
-__device__ __forceinline__ void wave_group(uint32_t key, int* leader, int* rank, int* size) {
+// Particles by cell for the next sort, in no particular order (the sort
+// ranks them): counts[c] particles, the first `slots` of them in row c of
+// table, any further ones (a cell far fuller than the lattice's) chained from
+// head[c] by next[i].  Chains are followed for a known number of steps, so
+// only counts has to be cleared.
+struct CellList {
+    uint32_t* __restrict__ counts;
+    uint32_t* __restrict__ table;
+    uint32_t* __restrict__ head;
+    uint32_t* __restrict__ next;
+    int shift;  // slots = 1 << shift, or 0 for shift < 0 (chains only)
+};
+
+// Adds particle i to its cell (active lanes of the wave).  Lanes with the
+// same cell form a group: its first lane takes the group's places with one
+// addition.  The particles of a wave are consecutive in the previous sorted
+// order, so a wave holds few distinct cells and the loop runs once per cell.
+__device__ __forceinline__ void cell_push(uint32_t key, uint32_t i, const CellList& cl) {
     const int lane = __lane_id();
-    unsigned long long rem = __ballot(1);
+    unsigned long long rem = __ballot(1), mine = 0;
     while (rem) {
         const int l = __ffsll((long long)rem) - 1;
         const uint32_t lk = __builtin_amdgcn_readlane(key, l);
         const unsigned long long m = __ballot(key == lk);
-        if (key == lk) {
-            *leader = l;
-            *rank = __popcll(m & ((1ull << lane) - 1ull));
-            *size = __popcll(m);
-        }
+        if (key == lk) mine = m;
         rem &= ~m;
     }
+    const int rank = __popcll(mine & ((1ull << lane) - 1ull));
+    uint32_t old = 0;
+    if (rank == 0) old = atomicAdd(&cl.counts[key], (uint32_t)__popcll(mine));
+    old = (uint32_t)__shfl((int)old, __ffsll((long long)mine) - 1, 64) + (uint32_t)rank;
+    if (cl.shift >= 0 && old < (1u << cl.shift))
+        cl.table[((size_t)key << cl.shift) + old] = i;
+    else
+        cl.next[i] = atomicExch(&cl.head[key], i);
 }
 
 // ---------------------------------------------------------------------------
 // Opening half kick + drift + periodic wrap of one particle (fluid only;
-// walls keep x and get v = 0), then its cell key and one count for the sort:
-//   v = u + dt/2 a;  x <- wrap(x + dt v);  key = cell(x);  counts[key] += 1.
-// With drift = false only the key and count of the current x; with
+// walls keep x and get v = 0), then its cell's list for the sort:
+//   v = u + dt/2 a;  x <- wrap(x + dt v);  push into the list of cell(x).
+// With drift = false only the list of the current x; with
 // hash = false only the motion and the domain checks.
 template <int DIM>
 __device__ __forceinline__ void drift_and_hash(int i, const State& S, const Grid& G, bool fluid,
                                                const double* u, const double* a, double hdt,
-                                               double dt, bool drift, uint32_t* __restrict__ key,
-                                               uint32_t* __restrict__ counts,
+                                               double dt, bool drift, CellList cl,
                                                uint32_t* __restrict__ flags, bool hash = true,
                                                const double* x_in = nullptr) {
 #pragma clang fp contract(off)
@@ -964,34 +980,50 @@ __device__ __forceinline__ void drift_and_hash(int i, const State& S, const Grid
     if (outside) atomicOr(flags, kFlagOutside);
     if (nonfinite) atomicOr(flags, kFlagNonFinite);
     if (!hash) return;
-    const uint32_t kk = cell_key(c, G);
-    key[i] = kk;
-    int leader = 0, rank = 0, size = 1;
-    wave_group(kk, &leader, &rank, &size);
-    if (rank == 0) atomicAdd(&counts[kk], (uint32_t)size);
+    cell_push(cell_key(c, G), (uint32_t)i, cl);
 }
+
+// What the standalone hash copies into another state (kCopy bits).
+enum : int { kCopyBase = 1, kCopyAccel = 2, kCopyRho = 4, kCopyArho = 8, kCopyP = 16 };
 
 // Standalone hash (first step of a call, or a plain sort).
 // kick_rho: the opening half kick of the continuity scheme's density,
-// rho <- rho + dt/2 arho, for every particle.
+// rho <- rho + dt/2 arho, for every particle.  With copy, the fields that the
+// sort gathers go to dst (the user's arrays stay as they are, or are where
+// the sort ends); else dst is src.
 template <int DIM, typename TA>
-__global__ __launch_bounds__(kBlock) void k_drift_hash(int n, State S, Grid G, double hdt,
-                                                       double dt, int drift, int kick_rho,
-                                                       uint32_t* __restrict__ key,
-                                                       uint32_t* __restrict__ counts,
+__global__ __launch_bounds__(kBlock) void k_drift_hash(int n, State src, State dst, Grid G,
+                                                       double hdt, double dt, int drift,
+                                                       int kick_rho, int copy, CellList cl,
                                                        uint32_t* __restrict__ flags) {
 #pragma clang fp contract(off)
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    double u[3] = {0.0, 0.0, 0.0}, a[3] = {0.0, 0.0, 0.0};
-    if (drift)
+    double u[3] = {0.0, 0.0, 0.0}, a[3] = {0.0, 0.0, 0.0}, x[3] = {0.0, 0.0, 0.0};
+    const uint8_t type = src.type[i];
+    for (int k = 0; k < DIM; ++k) {
+        x[k] = src.x[k][i];
+        if (drift || copy) u[k] = src.u[k][i];
+        if (drift || (copy & kCopyAccel)) a[k] = (double)((const TA*)src.a[k])[i];
+    }
+    if (copy) {
         for (int k = 0; k < DIM; ++k) {
-            u[k] = S.u[k][i];
-            a[k] = (double)((const TA*)S.a[k])[i];
+            if (!drift || type != 0) dst.x[k][i] = x[k];  // (else drift_and_hash does)
+            if (!drift) dst.u[k][i] = u[k];
+            if (copy & kCopyAccel) ((TA*)dst.a[k])[i] = (TA)a[k];
         }
-    if (drift && kick_rho)
-        store_rho<TA>(S.rho, i, load_rho<TA>(S.rho, i, S.rho64) + hdt * S.arho[i], S.rho64);
-    drift_and_hash<DIM>(i, S, G, S.type[i] == 0, u, a, hdt, dt, drift != 0, key, counts, flags);
+        dst.m[i] = src.m[i];
+        dst.type[i] = type;
+        dst.id[i] = src.id[i];
+        if (copy & kCopyArho) dst.arho[i] = src.arho[i];
+        if (copy & kCopyP) ((TA*)dst.p)[i] = ((const TA*)src.p)[i];
+    }
+    if ((copy & kCopyRho) || (drift && kick_rho)) {
+        double rho = load_rho<TA>(src.rho, i, src.rho64);
+        if (drift && kick_rho) rho = rho + hdt * src.arho[i];
+        store_rho<TA>(dst.rho, i, rho, dst.rho64);
+    }
+    drift_and_hash<DIM>(i, dst, G, type == 0, u, a, hdt, dt, drift != 0, cl, flags, true, x);
 }
 
 // Block sum of up to four FP64 values per thread into part[q * nparts + b]
@@ -1078,54 +1110,122 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(const uint32_t* __restric
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = (OUT)(offtot + chunk_total);
 }
 
-// Scatter particles into their cell's slot range; counts return to zero.
-static __global__ __launch_bounds__(kBlock) void k_scatter(int n, const uint32_t* __restrict__ key,
-                                                    const uint32_t* __restrict__ start,
-                                                    uint32_t* __restrict__ counts,
-                                                    uint32_t* __restrict__ tmp) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t k = key[i];
-    int leader = 0, rank = 0, size = 1;
-    wave_group(k, &leader, &rank, &size);
-    uint32_t old = 0;
-    if (rank == 0) old = atomicSub(&counts[k], (uint32_t)size);
-    old = (uint32_t)__shfl((int)old, leader, 64);
-    // the group takes slots [start + old - size, start + old)
-    tmp[start[k] + old - (uint32_t)size + (uint32_t)rank] = (uint32_t)i;
+// Sums of the diagnostics' partials (kBlock threads, fixed order):
+// out[q] = sum_b part[q * nparts + b], q <= DIM.
+template <int DIM>
+__device__ __forceinline__ void diag_sum(int nparts, const double* __restrict__ part,
+                                         double* __restrict__ out) {
+    __shared__ double wsum[1 + DIM][kBlock / 64];
+#pragma unroll
+    for (int q = 0; q < 1 + DIM; ++q) {
+        const double* __restrict__ p = part + (int64_t)q * nparts;
+        // eight sums per thread: a cube's tens of thousands of partials are
+        // then a few rounds of loads (75 us one load at a time)
+        double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        int b = threadIdx.x;
+        for (; b + 7 * kBlock < nparts; b += 8 * kBlock)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += p[b + e * kBlock];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (b + e * kBlock < nparts) v[e] += p[b + e * kBlock];
+        double t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
+        if ((threadIdx.x & 63) == 0) wsum[q][threadIdx.x >> 6] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 1 + DIM) {
+        double t = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) t += wsum[threadIdx.x][w];
+        out[threadIdx.x] = t;
+    }
+}
+// The diagnostics of the step before, summed by one more block of a sort's
+// first launch (nparts = 0: none) instead of a launch of their own.
+struct DiagJob {
+    int nparts;
+    const double* part;
+    double* out;
+};
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_diag_final(DiagJob job) {
+    diag_sum<DIM>(job.nparts, job.part, job.out);
 }
 
-// Stable order inside each cell: slot s holds particle i = tmp[s]; its final
-// slot is start[key] + (number of particles of the same cell with a smaller
-// index).  Gathers the state into that slot and packs the pair records
-// (with eos, also rho and the EOS records of the continuity scheme).
+// Counting sort, first of two launches (large grids): chunk b of
+// kBlock * ITEMS cells: sums[b] = its particles, sub[c / cpw] = particles of
+// the chunk before cell c, for every cpw-th cell c.
+template <int DIM, int ITEMS>
+__global__ __launch_bounds__(kBlock) void k_cell_sums(const uint32_t* __restrict__ counts,
+                                                      int64_t ncells, int cpw, int nchunks,
+                                                      uint32_t* __restrict__ sums,
+                                                      uint32_t* __restrict__ sub, DiagJob job) {
+    if ((int)blockIdx.x == nchunks) {
+        diag_sum<DIM>(job.nparts, job.part, job.out);
+        return;
+    }
+    const int64_t base = (int64_t)blockIdx.x * (kBlock * ITEMS) + (int64_t)threadIdx.x * ITEMS;
+    uint32_t v[ITEMS], s = 0;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        v[k] = base + k < ncells ? counts[base + k] : 0u;
+        s += v[k];
+    }
+    uint32_t tot;
+    uint32_t run = block_exclusive_scan<uint32_t>(s, &tot);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        if (base + k < ncells && ((base + k) & (cpw - 1)) == 0) sub[(base + k) / cpw] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+}
+
+// Many chunk sums (more than kWaveSums): their exclusive scan, in place, by
+// one block, so that the waves of k_cell_gather read one each.
+constexpr int kWaveSums = 256;
+static __global__ __launch_bounds__(kBlock) void k_sums_scan(int nchunks,
+                                                             uint32_t* __restrict__ sums) {
+    uint32_t run = 0;
+    for (int b = 0; b < nchunks; b += kBlock * 8) {
+        uint32_t v[8], s = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int c = b + (int)threadIdx.x * 8 + k;
+            v[k] = c < nchunks ? sums[c] : 0u;
+            s += v[k];
+        }
+        uint32_t tot;
+        uint32_t at = run + block_exclusive_scan<uint32_t>(s, &tot);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int c = b + (int)threadIdx.x * 8 + k;
+            if (c < nchunks) sums[c] = at;
+            at += v[k];
+        }
+        run += tot;
+    }
+}
+
+// What the sort's gather does with particle i of src, whose slot is d and
+// cell key `key`: its state to dst, its pair records, and with eos the EOS.
+struct GatherOp {
+    int records, copy_derived, eos;
+    double predict;
+};
 template <int DIM, typename T>
-__global__ __launch_bounds__(kBlock) void k_rank_gather(int n, const uint32_t* __restrict__ tmp,
-                                                        const uint32_t* __restrict__ key,
-                                                        const uint32_t* __restrict__ start,
-                                                        State src, State dst, Grid G,
-                                                        uint32_t* __restrict__ perm,
-                                                        uint32_t* __restrict__ skey,
-                                                        typename Rec<T>::type* __restrict__ pos,
-                                                        typename Vec4<T>::type* __restrict__ vel,
-                                                        int copy_derived,
-                                                        uint8_t* __restrict__ type_tape,
-                                                        PairConst<T> C,
-                                                        typename Vec2<T>::type* __restrict__ rp,
-                                                        int eos, double predict) {
+__device__ __forceinline__ void gather_one(uint32_t i, uint32_t d, uint32_t key, const State& src,
+                                           const State& dst, const Grid& G,
+                                           typename Rec<T>::type* __restrict__ pos,
+                                           typename Vec4<T>::type* __restrict__ vel,
+                                           uint8_t* __restrict__ type_tape,
+                                           const PairConst<T>& C,
+                                           typename Vec2<T>::type* __restrict__ rp,
+                                           const GatherOp& op) {
 #pragma clang fp contract(off)
-    const int s = blockIdx.x * kBlock + threadIdx.x;
-    if (s >= n) return;
-    const uint32_t i = tmp[s];
-    const uint32_t k = key[i];
-    const uint32_t b = start[k], e = start[k + 1];
-    uint32_t rank = 0;
-    for (uint32_t t = b; t < e; ++t) rank += tmp[t] < i ? 1u : 0u;
-    const uint32_t d = b + rank;
-    perm[d] = i;
-    skey[d] = k;
     int c[3];
-    decode_key(k, G, c);
+    decode_key(key, G, c);
     double xs[3] = {0.0, 0.0, 0.0};
     T vv[3] = {T(0), T(0), T(0)};
     for (int q = 0; q < DIM; ++q) {
@@ -1133,11 +1233,11 @@ __global__ __launch_bounds__(kBlock) void k_rank_gather(int n, const uint32_t* _
         const double u = src.u[q][i];
         dst.x[q][d] = x;
         dst.u[q][d] = u;
-        if (copy_derived) ((T*)dst.a[q])[d] = ((const T*)src.a[q])[i];
+        if (op.copy_derived) ((T*)dst.a[q])[d] = ((const T*)src.a[q])[i];
         xs[q] = x;
         // with predict, the pair records carry u + predict a (the predicted
         // end-of-step velocity of the continuity scheme's corrector)
-        vv[q] = predict != 0.0 ? (T)(u + predict * (double)((const T*)src.a[q])[i]) : (T)u;
+        vv[q] = op.predict != 0.0 ? (T)(u + op.predict * (double)((const T*)src.a[q])[i]) : (T)u;
     }
     const double m = src.m[i];
     dst.m[d] = m;
@@ -1145,7 +1245,7 @@ __global__ __launch_bounds__(kBlock) void k_rank_gather(int n, const uint32_t* _
     dst.type[d] = ty;
     if (type_tape) type_tape[d] = ty;
     dst.id[d] = src.id[i];
-    if (copy_derived) {
+    if (op.copy_derived) {
         store_rho<T>(dst.rho, d, load_rho<T>(src.rho, i, src.rho64), dst.rho64);
         ((T*)dst.p)[d] = ((const T*)src.p)[i];
         if (src.arho && dst.arho) dst.arho[d] = src.arho[i];
@@ -1153,12 +1253,12 @@ __global__ __launch_bounds__(kBlock) void k_rank_gather(int n, const uint32_t* _
     typename Vec2<T>::type v2;
     v2.x = T(0);
     v2.y = T(0);
-    if (eos) {
+    if (op.eos) {
         // density is a state (continuity scheme): gather it, and the EOS
         // (eq. eos) gives p and P = p / rho^2, in FP64 as in the density pass,
         // at rho + predict arho (the predicted end-of-step density)
         const double rho = load_rho<T>(src.rho, i, src.rho64);
-        const double rs = predict != 0.0 ? rho + predict * src.arho[i] : rho;
+        const double rs = op.predict != 0.0 ? rho + op.predict * src.arho[i] : rho;
         const double p = tait64<T>(rs, C);
         store_rho<T>(dst.rho, d, rho, dst.rho64);
         ((T*)dst.p)[d] = (T)p;
@@ -1172,8 +1272,263 @@ __global__ __launch_bounds__(kBlock) void k_rank_gather(int n, const uint32_t* _
     vr.x = vv[0]; vr.y = vv[1];
     vr.z = DIM == 2 ? v2.x : vv[2];
     vr.w = DIM == 2 ? v2.y : T(0);
-    pos[d] = make_rec<T>(xs, c, m, (int)ty, G, DIM);
-    vel[d] = vr;
+    if (op.records) {
+        pos[d] = make_rec<T>(xs, c, m, (int)ty, G, DIM);
+        vel[d] = vr;
+    }
+}
+
+// Counting sort, last launch: a wave sorts and gathers the particles of cells
+// [g cpw, (g + 1) cpw), stably (by cell, then by previous index), on its own
+// (no barrier, so that a CU keeps many waves' loads in flight, and a wave of
+// empty cells is gone after one round of loads).
+//  * Its first slot is the number of particles in the cells before: from the
+//    chunk sums of k_cell_sums (scanned by k_sums_scan if there are many), or
+//    (sums == nullptr, small grids) counted here, which costs less than a
+//    launch.
+//  * The cells' lists go to LDS (to skey, which is written last, if the wave
+//    has more than kSortEntries particles): the table's rows lane by lane,
+//    then lane t < cpw follows what cell t has beyond its row.  Each entry's
+//    rank in its cell is the number of smaller ones.
+//  * The slots are then taken in order: the state is gathered from src into
+//    dst, with the pair records packed (records) and, with eos, rho and the
+//    EOS records of the continuity scheme formed.
+// Writes start (first slot of every cell, and n), and clears the counts of
+// the other buffer for the next sort's chains.
+constexpr int kSortEntries = 384;
+constexpr int kSortRounds = 4;  // table entries of a wave's cells: at most 64 kSortRounds
+struct SortGrid {
+    int64_t ncells;
+    int cpw;             // cells per wave (a power of two in [4, 64])
+    int nblocks;
+    int chunk_cells;     // cells per chunk of sums
+    int scanned;         // sums are scanned
+    const uint32_t* sums;
+    const uint32_t* sub;
+    uint32_t* clear;     // the other buffer of counts
+    uint32_t *cs, *ce;   // cell ranges for the caller (may be null)
+};
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v += (uint32_t)__shfl_xor((int)v, d, 64);
+    return v;
+}
+// The wave's earlier writes (LDS or memory) are visible to its later reads.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+template <int DIM, typename T>
+__global__ __launch_bounds__(kBlock) void k_cell_gather(
+    int n, SortGrid SG, CellList cl, State src, State dst, Grid G, uint32_t* __restrict__ start,
+    uint32_t* perm, int want_perm, uint32_t* skey, typename Rec<T>::type* __restrict__ pos,
+    typename Vec4<T>::type* __restrict__ vel, uint8_t* __restrict__ type_tape, PairConst<T> C,
+    typename Vec2<T>::type* __restrict__ rp, GatherOp op, DiagJob job) {
+    constexpr int kWaves = kBlock / 64;
+    __shared__ uint32_t ent_[kWaves][kSortEntries], sorted_[kWaves][kSortEntries];
+    __shared__ uint8_t cellof_[kWaves][kSortEntries];
+    __shared__ uint32_t lo_[kWaves][65];
+    if ((int)blockIdx.x == SG.nblocks) {
+        diag_sum<DIM>(job.nparts, job.part, job.out);
+        return;
+    }
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    uint32_t* const ent = ent_[w];
+    uint32_t* const sorted = sorted_[w];
+    uint8_t* const cellof = cellof_[w];
+    uint32_t* const lo = lo_[w];
+    const int64_t g = (int64_t)blockIdx.x * kWaves + w;
+    const int64_t c0 = g * SG.cpw;
+    if (c0 >= SG.ncells) return;
+    const bool mine = lane < SG.cpw && c0 + lane < SG.ncells;
+    const uint32_t cnt = mine ? cl.counts[c0 + lane] : 0u;
+    // particles in the cells before this group's (summed over the lanes)
+    uint32_t first = 0;
+    if (SG.sums) {
+        const int chunk = (int)(c0 / SG.chunk_cells);
+        if (SG.scanned) {
+            if (lane == 0) first = SG.sums[chunk];
+        } else {
+#pragma unroll
+            for (int q = 0; q < kWaveSums / 64; ++q)  // all in flight
+                if (q * 64 + lane < chunk) first += SG.sums[q * 64 + lane];
+        }
+        if (lane == 0) first += SG.sub[g];
+    } else {
+        const uint4* __restrict__ c4 = reinterpret_cast<const uint4*>(cl.counts);
+#pragma unroll 4
+        for (int k = lane; k < (int)(c0 / 4); k += 64) {
+            const uint4 v = c4[k];
+            first += (v.x + v.y) + (v.z + v.w);
+        }
+    }
+    first = wave_sum(first);
+    uint32_t off = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_up((int)off, d, 64);
+        if (lane >= d) off += o;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)off, 63);
+    off -= cnt;
+    if (mine) {
+        start[c0 + lane] = first + off;
+        SG.clear[c0 + lane] = 0u;
+        if (SG.cs) {
+            SG.cs[c0 + lane] = first + off;
+            SG.ce[c0 + lane] = first + off + cnt;
+        }
+        if (c0 + lane == SG.ncells - 1) start[SG.ncells] = first + off + cnt;
+    }
+    if (total == 0) return;
+    lo[lane] = off;
+    if (lane == 0) lo[64] = total;
+    const bool fits = total <= (uint32_t)kSortEntries;
+    auto put = [&](uint32_t at, uint32_t i, int cell) {
+        if (fits) {
+            ent[at] = i;
+            cellof[at] = (uint8_t)cell;
+        } else {
+            skey[first + at] = i;
+        }
+    };
+    const uint32_t row = cl.shift >= 0 ? 1u << cl.shift : 0u;
+    if (row) {
+        wave_sync();  // lo
+        uint32_t v[kSortRounds];
+#pragma unroll
+        for (int q = 0; q < kSortRounds; ++q) {
+            const uint32_t e = (uint32_t)(q * 64 + lane), c = e >> cl.shift;
+            const uint32_t k = e & (row - 1u);
+            if (c < (uint32_t)SG.cpw && k < lo[c + 1] - lo[c])
+                v[q] = cl.table[((size_t)c0 << cl.shift) + e];
+        }
+#pragma unroll
+        for (int q = 0; q < kSortRounds; ++q) {
+            const uint32_t e = (uint32_t)(q * 64 + lane), c = e >> cl.shift;
+            const uint32_t k = e & (row - 1u);
+            if (c < (uint32_t)SG.cpw && k < lo[c + 1] - lo[c]) put(lo[c] + k, v[q], (int)c);
+        }
+    }
+    if (cnt > row) {
+        uint32_t i = cl.head[c0 + lane];
+        for (uint32_t k = row; k < cnt; ++k) {
+            put(off + k, i, lane);
+            i = cl.next[i];
+        }
+    }
+    wave_sync();
+    // cell of slot s of a wave whose entries are not in LDS
+    auto find = [&](uint32_t s) {
+        int a = 0, b = 64;
+        while (b - a > 1) {
+            const int m = (a + b) >> 1;
+            if (lo[m] <= s) a = m; else b = m;
+        }
+        return a;
+    };
+    for (uint32_t s = lane; s < total; s += 64) {
+        const int t = fits ? cellof[s] : find(s);
+        const uint32_t b = lo[t], e = lo[t + 1];
+        uint32_t rank = 0;
+        if (fits) {
+            const uint32_t v = ent[s];
+            for (uint32_t k = b; k < e; ++k) rank += ent[k] < v ? 1u : 0u;
+            sorted[b + rank] = v;
+        } else {
+            const uint32_t v = skey[first + s];
+            for (uint32_t k = b; k < e; ++k) rank += skey[first + k] < v ? 1u : 0u;
+            perm[first + b + rank] = v;
+        }
+    }
+    wave_sync();
+    for (uint32_t s = lane; s < total; s += 64) {
+        const uint32_t i = fits ? sorted[s] : perm[first + s];
+        const uint32_t key = (uint32_t)c0 + (uint32_t)(fits ? cellof[s] : find(s));
+        const uint32_t d = first + s;
+        if (fits && want_perm) perm[d] = i;
+        skey[d] = key;
+        gather_one<DIM, T>(i, d, key, src, dst, G, pos, vel, type_tape, C, rp, op);
+    }
+}
+
+// Sparse grids (more cells than particles): the last launch in two, since
+// k_cell_gather would be mostly waves of empty cells (a workgroup costs about
+// 2 ns however little it does: 2D dam break at dx = 0.1/32, 351k cells for
+// 217k particles, 20.4 us in one launch).  k_cell_place: one cell per thread,
+// start, and the cell's list to its slots of tmp with the cell key in skey;
+// k_slot_gather: one slot per thread, ranked among its cell's.
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_cell_place(SortGrid SG, CellList cl,
+                                                       uint32_t* __restrict__ start,
+                                                       uint32_t* __restrict__ skey,
+                                                       uint32_t* __restrict__ tmp) {
+    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool mine = c < SG.ncells;
+    const uint32_t cnt = mine ? cl.counts[c] : 0u;
+    // particles before the block: of the chunks, and of the chunk's cells
+    const int64_t c0 = (int64_t)blockIdx.x * kBlock;
+    const int chunk = (int)(c0 / SG.chunk_cells);
+    uint32_t first = 0;
+    if (SG.scanned) {
+        if (threadIdx.x == 0) first = SG.sums[chunk];
+    } else if ((int)threadIdx.x < chunk) {  // at most kWaveSums = kBlock of them
+        first = SG.sums[threadIdx.x];
+    }
+    static_assert(kWaveSums <= kBlock, "one sum per thread");
+    if (threadIdx.x == 0) first += SG.sub[c0 / SG.cpw];
+    // both sums in one scan: the offsets in the low half, the total in the high
+    uint64_t total;
+    const uint64_t at =
+        block_exclusive_scan<uint64_t>(((uint64_t)first << 32) | (uint64_t)cnt, &total);
+    const uint32_t b = (uint32_t)(total >> 32) + (uint32_t)at;
+    if (!mine) return;
+    start[c] = b;
+    SG.clear[c] = 0u;
+    if (SG.cs) {
+        SG.cs[c] = b;
+        SG.ce[c] = b + cnt;
+    }
+    if (c == SG.ncells - 1) start[SG.ncells] = b + cnt;
+    if (cnt == 0) return;
+    const uint32_t row = cl.shift >= 0 ? 1u << cl.shift : 0u;
+    const uint32_t m = cnt < row ? cnt : row;
+    const uint4* __restrict__ r4 =
+        reinterpret_cast<const uint4*>(cl.table + (row ? (size_t)c << cl.shift : 0));
+    for (uint32_t k = 0; k < m; k += 4) {  // rows are 32 bytes at least
+        const uint4 v = r4[k / 4];
+        tmp[b + k] = v.x;
+        if (k + 1 < m) tmp[b + k + 1] = v.y;
+        if (k + 2 < m) tmp[b + k + 2] = v.z;
+        if (k + 3 < m) tmp[b + k + 3] = v.w;
+    }
+    if (cnt > row) {
+        uint32_t i = cl.head[c];
+        for (uint32_t k = row; k < cnt; ++k) {
+            tmp[b + k] = i;
+            i = cl.next[i];
+        }
+    }
+    for (uint32_t k = 0; k < cnt; ++k) skey[b + k] = (uint32_t)c;
+}
+template <int DIM, typename T>
+__global__ __launch_bounds__(kBlock) void k_slot_gather(
+    int n, const uint32_t* __restrict__ tmp, const uint32_t* __restrict__ start, State src,
+    State dst, Grid G, uint32_t* __restrict__ perm, int want_perm,
+    const uint32_t* __restrict__ skey, typename Rec<T>::type* __restrict__ pos,
+    typename Vec4<T>::type* __restrict__ vel, uint8_t* __restrict__ type_tape, PairConst<T> C,
+    typename Vec2<T>::type* __restrict__ rp, GatherOp op) {
+    const int s = blockIdx.x * kBlock + threadIdx.x;
+    if (s >= n) return;
+    const uint32_t i = tmp[s];
+    const uint32_t key = skey[s];
+    const uint32_t b = start[key], e = start[key + 1];
+    uint32_t rank = 0;
+    for (uint32_t t = b; t < e; ++t) rank += tmp[t] < i ? 1u : 0u;
+    const uint32_t d = b + rank;
+    if (want_perm) perm[d] = i;
+    gather_one<DIM, T>(i, d, key, src, dst, G, pos, vel, type_tape, C, rp, op);
 }
 
 // Pack pair records of an already sorted state (standalone evaluations):
@@ -1727,8 +2082,7 @@ __device__ __forceinline__ CloseIn close_load(int i, const State& S, int drift, 
 template <int DIM, typename T>
 __device__ __forceinline__ void momentum_close(int i, const T acc[3], bool fluid, const State& S,
                                                const Grid& G, int kick, int drift, double hdt,
-                                               double dt, uint32_t* __restrict__ key,
-                                               uint32_t* __restrict__ counts,
+                                               double dt, CellList cl,
                                                uint32_t* __restrict__ flags, bool diag,
                                                double dv[1 + DIM], const CloseIn* ci = nullptr) {
     for (int k = 0; k < DIM; ++k) ((T*)S.a[k])[i] = acc[k];
@@ -1751,7 +2105,7 @@ __device__ __forceinline__ void momentum_close(int i, const T acc[3], bool fluid
         }
     }
     if (drift) {
-        drift_and_hash<DIM>(i, S, G, fluid, u, a, hdt, dt, true, key, counts, flags, true,
+        drift_and_hash<DIM>(i, S, G, fluid, u, a, hdt, dt, true, cl, flags, true,
                             ci ? ci->x : nullptr);
     } else if (kick) {
         for (int k = 0; k < DIM; ++k) S.u[k][i] = u[k];
@@ -1767,8 +2121,7 @@ __device__ __forceinline__ void momentum_one(
     const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, int n,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap,
-    const State& S, int kick, int drift, double hdt, double dt, uint32_t* __restrict__ key,
-    uint32_t* __restrict__ counts, uint32_t* __restrict__ flags, bool diag,
+    const State& S, int kick, int drift, double hdt, double dt, CellList cl, uint32_t* __restrict__ flags, bool diag,
     double dv[1 + DIM]) {
     const bool fluid = type[i] == 0;
     T acc[3] = {T(0), T(0), T(0)};
@@ -1796,7 +2149,7 @@ __device__ __forceinline__ void momentum_one(
         acc[1] = ay;
         acc[2] = az;
     }
-    momentum_close<DIM, T>(i, acc, fluid, S, G, kick, drift, hdt, dt, key, counts, flags, diag,
+    momentum_close<DIM, T>(i, acc, fluid, S, G, kick, drift, hdt, dt, cl, flags, diag,
                            dv);
 }
 
@@ -1811,7 +2164,7 @@ __global__ __launch_bounds__(kBlock) void k_momentum(
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap, State S,
     int kick,
-    int drift, double hdt, double dt, uint32_t* __restrict__ key, uint32_t* __restrict__ counts,
+    int drift, double hdt, double dt, CellList cl,
     uint32_t* __restrict__ flags, double* __restrict__ diag_part) {
     const int blk = xcd_block();
     const int i = blk * kBlock + threadIdx.x;
@@ -1819,7 +2172,7 @@ __global__ __launch_bounds__(kBlock) void k_momentum(
     for (int q = 0; q <= DIM; ++q) dv[q] = 0.0;
     if (i < n)
         momentum_one<DIM, SR, KERNEL, T>(i, G, C, skey, pos, vel, rp, type, cstart, cend, n, list,
-                                         ncnt, cap, S, kick, drift, hdt, dt, key, counts, flags,
+                                         ncnt, cap, S, kick, drift, hdt, dt, cl, flags,
                                          diag_part != nullptr, dv);
     if (diag_part) block_sum4<1 + DIM>(dv, diag_part, blk, gridDim.x);
 }
@@ -1845,8 +2198,7 @@ __global__ __launch_bounds__(kBlock) void k_cont_momentum(
     const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap, State S,
-    int euler, int kick, int drift, double dt, uint32_t* __restrict__ key,
-    uint32_t* __restrict__ counts, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
+    int euler, int kick, int drift, double dt, CellList cl, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
     int count_pairs,
     unsigned long long* __restrict__ pairs) {
     const int blk = xcd_block();
@@ -1932,13 +2284,13 @@ __global__ __launch_bounds__(kBlock) void k_cont_momentum(
                 // x += dt u with the new u: the drift of drift_and_hash with a
                 // zero half kick
                 const double zero[3] = {0.0, 0.0, 0.0};
-                drift_and_hash<DIM>(i, S, G, fluid, u, zero, 0.0, dt, true, key, counts, flags,
+                drift_and_hash<DIM>(i, S, G, fluid, u, zero, 0.0, dt, true, cl, flags,
                                     drift != 0);
                 store_rho<T>(S.rho, i, rho, S.rho64);
             } else {
                 if (drift) {
                     rho = rho + hdt * arho;
-                    drift_and_hash<DIM>(i, S, G, fluid, u, a, hdt, dt, true, key, counts, flags);
+                    drift_and_hash<DIM>(i, S, G, fluid, u, a, hdt, dt, true, cl, flags);
                 } else if (kick) {
                     for (int k = 0; k < DIM; ++k) S.u[k][i] = u[k];
                 }
@@ -2003,56 +2355,6 @@ static __global__ __launch_bounds__(kBlock) void k_fill_u32(int64_t len, uint32_
                                                      uint32_t* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < len) out[i] = v;
-}
-
-// cell_start / cell_end from the scanned offsets.
-static __global__ __launch_bounds__(kBlock) void k_cell_ranges(int64_t ncells,
-                                                        const uint32_t* __restrict__ start,
-                                                        uint32_t* __restrict__ cs,
-                                                        uint32_t* __restrict__ ce) {
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c >= ncells) return;
-    cs[c] = start[c];
-    ce[c] = start[c + 1];
-}
-
-// Copy a state (all fields) slot by slot.
-template <int DIM, typename T>
-__global__ __launch_bounds__(kBlock) void k_copy_state(int n, State src, State dst) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    for (int q = 0; q < DIM; ++q) {
-        dst.x[q][i] = src.x[q][i];
-        dst.u[q][i] = src.u[q][i];
-        ((T*)dst.a[q])[i] = ((const T*)src.a[q])[i];
-    }
-    dst.m[i] = src.m[i];
-    dst.type[i] = src.type[i];
-    dst.id[i] = src.id[i];
-    store_rho<T>(dst.rho, i, load_rho<T>(src.rho, i, src.rho64), dst.rho64);
-    ((T*)dst.p)[i] = ((const T*)src.p)[i];
-    if (src.arho && dst.arho) dst.arho[i] = src.arho[i];
-}
-
-// ---------------------------------------------------------------------------
-// FP64 diagnostics: KE = sum m |u|^2 / 2 and momentum sum m u, as fixed-order
-// tree sums: per-block partials (momentum epilogue), then one block over them.
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_diag_final(int nparts, const double* __restrict__ part,
-                                                       double* __restrict__ out) {
-    __shared__ double sh[4][kBlock];
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nparts; b += kBlock)
-        for (int q = 0; q < 1 + DIM; ++q) v[q] += part[(int64_t)q * nparts + b];
-    for (int q = 0; q < 1 + DIM; ++q) sh[q][threadIdx.x] = v[q];
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int q = 0; q < 1 + DIM; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int q = 0; q < 1 + DIM; ++q) out[q] = sh[q][0];
 }
 
 }  // namespace sph

@@ -869,7 +869,7 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
     const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
     const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
-    uint32_t* __restrict__ key, uint32_t* __restrict__ counts, uint32_t* __restrict__ flags,
+    CellList cl, uint32_t* __restrict__ flags,
     double* __restrict__ diag_part, int stride) {
     __shared__ TileMeta<CfgF> MM[2];
     __shared__ uint16_t cellofs[2][CfgF::kCap];
@@ -980,7 +980,7 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
                 }
                 double dv[4] = {0.0, 0.0, 0.0, 0.0};
                 momentum_close<3, float>((int)i, acc, cur_t.fluid, St, G, kick, drift, hdt, dt,
-                                         key, counts, flags, diag_part != nullptr, dv,
+                                         cl, flags, diag_part != nullptr, dv,
                                          &cur_t.ci);
                 for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
             }
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
     const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
     const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
-    uint32_t* __restrict__ key, uint32_t* __restrict__ counts, uint32_t* __restrict__ flags,
+    CellList cl, uint32_t* __restrict__ flags,
     double* __restrict__ diag_part, int stride) {
     __shared__ TileMeta<CfgD> MM[2];
     __shared__ uint16_t cellofs[2][CfgD::kCap];
@@ -1275,8 +1275,7 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
                     acc[2] = az;
                 }
                 double dv[4] = {0.0, 0.0, 0.0, 0.0};
-                momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, key, counts,
-                                          flags, diag_part != nullptr, dv, &ci);
+                momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, cl, flags, diag_part != nullptr, dv, &ci);
                 for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
             }
         }
@@ -1319,8 +1318,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_momentum(
     const typename Rec<T>::type* __restrict__ pos, const typename Vec4<T>::type* __restrict__ vel,
     const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, const uint32_t* __restrict__ ncnt, uint32_t cap, State St,
-    int kick, int drift, double hdt, double dt, uint32_t* __restrict__ key,
-    uint32_t* __restrict__ counts, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
+    int kick, int drift, double hdt, double dt, CellList cl, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
     int stride, uint32_t epoch, const uint32_t* __restrict__ fallback) {
     double dsum[4] = {0.0, 0.0, 0.0, 0.0};
     if (*fallback == epoch) {
@@ -1328,8 +1326,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_momentum(
             if (ncnt[i] <= cap) continue;
             double dv[4] = {0.0, 0.0, 0.0, 0.0};
             momentum_one<3, S, KERNEL, T>(i, G, C, skey, pos, vel, rp, type, cstart, cend, n,
-                                          nullptr, ncnt, cap, St, kick, drift, hdt, dt, key,
-                                          counts, flags, diag_part != nullptr, dv);
+                                          nullptr, ncnt, cap, St, kick, drift, hdt, dt, cl, flags, diag_part != nullptr, dv);
             for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
         }
     }
