@@ -118,7 +118,7 @@ typedef struct {
                            * (default), < 0 = never (lists read from global
                            * memory), k > 0 = used wherever they apply, with at
                            * most k staged particles per box (3072 at most,
-                           * 1920 in FP64;
+                           * 2000 in FP64;
                            * larger boxes take the cell walk).  Results do not
                            * depend on it. */
     int32_t cell_order;   /* sort key of the cells (Section 2.2): 0 = row-major,

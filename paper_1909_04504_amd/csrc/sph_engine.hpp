@@ -265,6 +265,39 @@ inline uint32_t list_cap(const sph_params* p, int64_t n) {
     return p->dim == 2 ? 64u : 192u;
 }
 
+// Tile geometry from the box (S, tw, th, td set); ntiles = 0 if it exceeds
+// the configuration.
+inline void tile_geometry(const sph_params* p, const sph::Grid& G, sph::Tiles* Tp, int max_cells,
+                          int max_tcells) {
+    sph::Tiles& T = *Tp;
+    T.uw = T.tw + 2 * T.S;
+    T.uh = T.th + 2 * T.S;
+    T.ud = T.td + 2 * T.S;
+    int64_t nt = 1;
+    for (int k = 0; k < 3; ++k) {
+        const int t = k == 0 ? T.tw : (k == 1 ? T.th : T.td);
+        T.nt[k] = (G.nc[k] + t - 1) / t;
+        nt *= T.nt[k];
+        T.csf[k] = (float)G.cs[k];
+        T.inv_csf[k] = (float)(1.0 / G.cs[k]);
+    }
+    T.inv_uw = 1.0f / (float)T.uw;
+    T.inv_uwh = 1.0f / (float)(T.uw * T.uh);
+    T.cen[0] = T.uw / 2;
+    T.cen[1] = T.uh / 2;
+    T.cen[2] = T.ud / 2;
+    const double R = support_radius(p);
+    T.rclip2 = (float)(R * R * (1.0 + 1e-4));
+    T.clip_pad = (float)(1e-4 * std::min(G.cs[0], std::min(G.cs[1], G.cs[2])));
+        if (nt > (int64_t)1 << 30 || T.uw > sph::kTileUnionAxisMax || T.uh > sph::kTileUnionAxisMax ||
+        T.ud > sph::kTileUnionAxisMax || T.uw * T.uh * T.ud > max_cells ||
+        T.tw * T.th * T.td > max_tcells) {
+        std::memset(&T, 0, sizeof T);
+        return;
+    }
+    T.ntiles = (int)nt;
+}
+
 // Box of the FP64 tiles: the first of a list (by the share of the union that
 // is targets) whose union is expected to fit the staging with 8% to spare.
 // The expected particles per cell are the grid's mean where every axis is
@@ -323,36 +356,31 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
     } else {
         T.tw = 2; T.th = 2; T.td = 2;
     }
-    T.uw = T.tw + 2 * T.S;
-    T.uh = T.th + 2 * T.S;
-    T.ud = T.td + 2 * T.S;
-    int64_t nt = 1;
-    for (int k = 0; k < 3; ++k) {
-        const int t = k == 0 ? T.tw : (k == 1 ? T.th : T.td);
-        T.nt[k] = (G.nc[k] + t - 1) / t;
-        nt *= T.nt[k];
-        T.csf[k] = (float)G.cs[k];
-        T.inv_csf[k] = (float)(1.0 / G.cs[k]);
-    }
-    T.inv_uw = 1.0f / (float)T.uw;
-    T.inv_uwh = 1.0f / (float)(T.uw * T.uh);
-    T.cen[0] = T.uw / 2;
-    T.cen[1] = T.uh / 2;
-    T.cen[2] = T.ud / 2;
-    const double R = support_radius(p);
-    T.rclip2 = (float)(R * R * (1.0 + 1e-4));
-    T.clip_pad = (float)(1e-4 * std::min(G.cs[0], std::min(G.cs[1], G.cs[2])));
     T.cap = p->pair_tiles > 0 ? std::min(p->pair_tiles, cfg_cap) : cfg_cap;
-    if (nt > (int64_t)1 << 30 || T.uw > sph::kTileUnionAxisMax || T.uh > sph::kTileUnionAxisMax ||
-        T.ud > sph::kTileUnionAxisMax ||
-        T.uw * T.uh * T.ud > (f64 ? sph::CfgD::kCells : sph::CfgF::kCells) ||
-        T.tw * T.th * T.td > (f64 ? sph::CfgD::kTCells : sph::CfgF::kTCells)) {
-        std::memset(&T, 0, sizeof T);
-        return T;
-    }
-    T.ntiles = (int)nt;
+    tile_geometry(p, G, &T, f64 ? sph::CfgD::kCells : sph::CfgF::kCells,
+                  f64 ? sph::CfgD::kTCells : sph::CfgF::kTCells);
     return T;
 }
+// Tiles of the global-format list build (k_tile_nlist), 3D half-size cells,
+// both precisions; ntiles = 0: the walk build (whole cells, where a wave's
+// particles share a cell and its candidates, so that the walk's loads are
+// broadcasts: 100^3 cube FP64 1.44 ms walked, 1.62 to 3.05 tiled; half-size
+// cells 1.19 walked, 1.10 tiled, and 48^3, where the walk has too few waves,
+// 0.182 and 0.070).  Sparse grids walk (most boxes hold few particles).
+// pair_tiles < 0 asks for no tiles.
+inline sph::Tiles make_list_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
+                                  int64_t ncells) {
+    sph::Tiles T;
+    std::memset(&T, 0, sizeof T);
+    if (p->dim != 3 || G.S != 2 || p->pair_tiles < 0 || list_cap(p, n) == 0) return T;
+    if (p->pair_tiles == 0 && n < ncells) return T;
+    T.S = G.S;
+    if (!box64(p, G, (double)n / (double)ncells, &T)) return T;
+    T.cap = p->pair_tiles > 0 ? std::min(p->pair_tiles, sph::CfgD::kCap) : sph::CfgD::kCap;
+    tile_geometry(p, G, &T, sph::CfgD::kCells, sph::CfgD::kTCells);
+    return T;
+}
+constexpr unsigned kTileNlistBlocks = 512;  // workgroups of k_tile_nlist (two per CU)
 inline unsigned fallback_blocks(int64_t n) {
     return std::min<unsigned>((unsigned)sph::kFallbackBlocks, blocks_for(n));
 }
@@ -429,7 +457,7 @@ struct Layout {
     size_t flags, counts, counts2, head, table, start, chunks, sub, next, tmp, perm, skey, lcnt, list;
     uint32_t cap;
     SortShape sort;
-    sph::Tiles tiles;
+    sph::Tiles tiles, ltiles;
     StateOff s1, s2;
     size_t pos, vel, rp, diag;
     // adjoint (present when adj_k > 0; the tape is the last region)
@@ -513,7 +541,8 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
     // or k_density without lists) from offset 16
     // (and the tile passes' fallback epoch at offset 4)
     L.flags = take(16 + 8 * std::max<size_t>(std::max(nlist_shape(n, ncells).blocks, blocks_for(n)),
-                                             ntiles));
+                                             std::max<size_t>(ntiles, kTileNlistBlocks)));
+    L.ltiles = make_list_tiles(p, G, n, ncells);
     L.counts = take(4 * (size_t)ncells);
     L.counts2 = take(4 * (size_t)ncells);
     L.head = take(4 * (size_t)ncells);
@@ -852,6 +881,9 @@ struct Engine {
     // of interactions to the counters).  Every pair pass reads the lists
     // built last, so each change of records is followed by this launch.
     int nlist(const uint32_t* cs, const uint32_t* ce, bool count_pairs) {
+        if constexpr (DIM == 3) {
+            if (L.ltiles.ntiles > 0) return tile_nlist(cs, ce, count_pairs);
+        }
         with_reach([&](auto R) {
             // cell-cooperative build in 2D with cells of 2h (about 7 targets
             // and 61 candidates per cell); the walk build elsewhere, where a
@@ -874,6 +906,16 @@ struct Engine {
             }
         });
         return launch_check("k_nlist");
+    }
+    int tile_nlist(const uint32_t* cs, const uint32_t* ce, bool count_pairs) {
+        const sph::Tiles& TL = L.ltiles;
+        const unsigned wgs = std::min<unsigned>((unsigned)TL.ntiles, kTileNlistBlocks);
+        with_reach([&](auto R) {
+            launch_b(K_NLIST, sph::k_tile_nlist<decltype(R)::value, T>, wgs, sph::CfgD::kThreads, st,
+                     n, G, C, TL, skey(), pos(), cs, ce, L.cap, list(), lcnt(),
+                     count_pairs ? 1 : 0, pairs());
+        });
+        return launch_check("k_tile_nlist");
     }
     const uint32_t* list_or_null() const { return L.cap ? list() : nullptr; }
 
@@ -1051,12 +1093,26 @@ struct Engine {
                   int64_t* offsets, int32_t* nbr, int64_t* total) {
         const sph::State user = user_state(pa, prm);
         SPH_TRY(pack(user, false));
-        {
-        with_reach([&](auto R) {
-            launch(K_NBR_COUNT, sph::k_nbr_count<DIM, decltype(R)::value, T>, blocks_for(n), st,
-                n, G, C, skey(), pos(), cs, ce, lcnt());
-        });
-        SPH_TRY(launch_check("k_nbr_count"));
+        // counts from the lists (filled from them below), or without lists
+        // from a walk of the cells
+        if (tiled()) {
+            SPH_TRY(tile_lists(user, cs, ce, false, false, false));
+            if constexpr (kTileable) {
+                with_reach([&](auto R) {
+                    launch(K_TILE_FALLBACK, sph::k_tile_fallback_count<decltype(R)::value, T>,
+                           fallback_blocks(n), st, n, G, C, skey(), pos(), cs, ce, lcnt(),
+                           tile_epoch, fbword());
+                });
+                SPH_TRY(launch_check("k_tile_fallback_count"));
+            }
+        } else if (L.cap) {
+            SPH_TRY(nlist(cs, ce, false));
+        } else {
+            with_reach([&](auto R) {
+                launch(K_NBR_COUNT, sph::k_nbr_count<DIM, decltype(R)::value, T>, blocks_for(n), st,
+                       n, G, C, skey(), pos(), cs, ce, lcnt());
+            });
+            SPH_TRY(launch_check("k_nbr_count"));
         }
         SPH_TRY(scan<int64_t>(lcnt(), n, offsets));
         int64_t tot = 0;
@@ -1067,9 +1123,30 @@ struct Engine {
             return fail(SPH_ECAPACITY, "neighbour list needs %lld entries, capacity %lld",
                         (long long)tot, (long long)capacity);
         if (tot > 0 && !nbr) return fail(SPH_EINVAL, "nbr is NULL");
+        if constexpr (kTileable) {
+            if (tiled()) {
+                launch_b(K_NBR_FILL, sph::k_tile_expand<Cfg>, (unsigned)L.tiles.ntiles,
+                         Cfg::kThreads, st, n, G, L.tiles, L.tiles.cap, cs, ce, tcap(),
+                         (const uint4*)list(), lcnt(), (const int64_t*)offsets, nbr);
+                SPH_TRY(launch_check("k_tile_expand"));
+                with_reach([&](auto R) {
+                    launch(K_TILE_FALLBACK, sph::k_tile_fallback_fill<decltype(R)::value, T>,
+                           fallback_blocks(n), st, n, G, C, skey(), pos(), cs, ce, tcap(),
+                           (const uint4*)list(), lcnt(), (const int64_t*)offsets, nbr, tile_epoch,
+                           fbword());
+                });
+                return launch_check("k_tile_fallback_fill");
+            }
+        }
         with_reach([&](auto R) {
-            launch(K_NBR_FILL, sph::k_nbr_fill<DIM, decltype(R)::value, T>, blocks_for(n), st,
-                n, G, C, skey(), pos(), cs, ce, offsets, nbr);
+            constexpr int S = decltype(R)::value;
+            if (L.cap)
+                launch(K_NBR_FILL, sph::k_nbr_expand<DIM, S, T>, blocks_for(n), st, n, G, C, skey(),
+                       pos(), cs, ce, (const uint32_t*)list(), lcnt(), L.cap,
+                       (const int64_t*)offsets, nbr);
+            else
+                launch(K_NBR_FILL, sph::k_nbr_fill<DIM, S, T>, blocks_for(n), st, n, G, C, skey(),
+                       pos(), cs, ce, (const int64_t*)offsets, nbr);
         });
         return launch_check("k_nbr_fill");
     }

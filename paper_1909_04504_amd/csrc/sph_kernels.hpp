@@ -2340,6 +2340,63 @@ __global__ __launch_bounds__(kBlock) void k_nbr_fill(int n, Grid G, PairConst<T>
                                   });
 }
 
+// The CSR lists from the stored ones (sph_neighbors): a wave takes 64 slots,
+// reads their lists as rows of 64 entries, 16 rows at a time, and writes each
+// slot's 16 entries together through LDS; the slots with more neighbours than
+// the capacity walk the cells.  (A second walk of every cell writes each lane's
+// entries on their own.)
+template <int DIM, int SR, typename T>
+__global__ __launch_bounds__(kBlock) void k_nbr_expand(
+    int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
+    const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, const uint32_t* __restrict__ list,
+    const uint32_t* __restrict__ ncnt, uint32_t cap, const int64_t* __restrict__ off,
+    int32_t* __restrict__ nbr) {
+    using Code = NbrCode<DIM, SR, T>;
+    constexpr int kRows = 16;
+    __shared__ uint32_t sh_[kBlock / 64][64][kRows + 1];
+    __shared__ int64_t at_[kBlock / 64][64];
+    __shared__ uint32_t left_[kBlock / 64][64];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    const int i = xcd_block() * kBlock + (int)threadIdx.x;
+    const bool in = i < n;
+    const uint32_t cnt = in ? ncnt[i] : 0u;
+    const bool listed = cnt <= cap;
+    const uint32_t m = listed ? cnt : 0u;
+    at_[w][lane] = in ? off[i] : 0;
+    left_[w][lane] = m;
+    uint32_t most = m;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, 64));
+    const uint32_t* __restrict__ col = list + list_column((uint32_t)(in ? i : 0), cap);
+    for (uint32_t k = 0; k < most; k += kRows) {
+        uint32_t v[kRows];
+#pragma unroll
+        for (int e = 0; e < kRows; ++e)
+            v[e] = k + (uint32_t)e < m ? col[(k + (uint32_t)e) * kListTile] : 0u;
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) sh_[w][lane][e] = v[e] >> Code::kBits;
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < 64 / (64 / kRows); ++r) {
+            const int t = r * (64 / kRows) + lane / kRows;
+            const uint32_t e = k + (uint32_t)(lane % kRows);
+            if (e < left_[w][t]) nbr[at_[w][t] + e] = (int32_t)sh_[w][t][lane % kRows];
+        }
+        wave_sync();
+    }
+    if (in && !listed) {
+        const typename Rec<T>::type ri = pos[i];
+        int64_t at = off[i];
+        const int64_t end = off[i + 1];
+        walk_pairs<DIM, SR, T>(G, C, skey[i], ri, pos, skey, cstart, cend, (uint32_t)n, NoPayload(),
+                               [&](uint32_t j, const typename Rec<T>::type&, int, const Geom<T>&,
+                                   uint32_t) {
+                                   if (at < end) nbr[at++] = (int32_t)j;
+                               });
+    }
+}
+
 // Tait EOS alone (sph_eos).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_eos(int n, PairConst<T> C, const void* __restrict__ rho,

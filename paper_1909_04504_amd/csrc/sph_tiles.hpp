@@ -47,7 +47,7 @@ struct TileCfg {
     static_assert(CELLS <= 2 * THREADS && TCELLS <= THREADS, "cells per thread");
 };
 using CfgF = TileCfg<512, 1024, 160, 3072>;  // mixed precision
-using CfgD = TileCfg<256, 512, 64, 1920>;    // FP64
+using CfgD = TileCfg<256, 512, 64, 2000>;    // FP64
 template <typename T> struct TileCfgOf;
 template <> struct TileCfgOf<float> { using type = CfgF; };
 template <> struct TileCfgOf<double> { using type = CfgD; };
@@ -311,14 +311,26 @@ __device__ __forceinline__ void tile_target(const Tiles& TL, const TileMeta<CFG>
     union_coords(TL, c, uc);
 }
 
-// Marks every target of the tile for the fallback (its union does not fit).
+// Octet k8 (entries 8 k8 .. 8 k8 + 7) of slot i's list.
+__device__ __forceinline__ size_t tile_octet(uint32_t i, uint32_t cap, uint32_t k8) {
+    return ((size_t)(i >> 6) * (cap >> 3) + k8) * 64 + (i & 63);
+}
+
+// Marks every target of the tile for the fallback (its union does not fit):
+// in its count, and in its first octet, where the mark outlives the count
+// (kNoIndex is no union index).
+constexpr uint32_t kNoIndex = 0xffffu;
 template <typename CFG>
 __device__ __forceinline__ void tile_mark_overflow(const TileMeta<CFG>& M,
-                                                   uint32_t* __restrict__ ncnt) {
+                                                   uint32_t* __restrict__ ncnt,
+                                                   uint4* __restrict__ list, uint32_t cap) {
     for (int r = 0; r < M.ntcells; ++r) {
         const uint32_t len = M.tpre[r + 1] - M.tpre[r];
-        for (uint32_t k = threadIdx.x; k < len; k += CFG::kThreads)
-            ncnt[M.gs[M.tc[r]] + k] = kTileOverflow;
+        for (uint32_t k = threadIdx.x; k < len; k += CFG::kThreads) {
+            const uint32_t i = M.gs[M.tc[r]] + k;
+            ncnt[i] = kTileOverflow;
+            list[tile_octet(i, cap, 0)] = make_uint4(~0u, ~0u, ~0u, ~0u);
+        }
     }
 }
 
@@ -395,10 +407,6 @@ __device__ __forceinline__ int4 tile_rec(const int4& r, int ux, int uy, int uz) 
     return p;
 }
 
-// Octet k8 (entries 8 k8 .. 8 k8 + 7) of slot i's list.
-__device__ __forceinline__ size_t tile_octet(uint32_t i, uint32_t cap, uint32_t k8) {
-    return ((size_t)(i >> 6) * (cap >> 3) + k8) * 64 + (i & 63);
-}
 __device__ __forceinline__ uint32_t half_of(const uint4& v, int e) {
     const uint32_t w = e < 2 ? v.x : (e < 4 ? v.y : (e < 6 ? v.z : v.w));
     return (e & 1) ? (w >> 16) : (w & 0xffffu);
@@ -611,15 +619,119 @@ __device__ __forceinline__ bool tile_inside(const double4&, const float4& f, con
     return in(f.x, 0) && in(f.y, 1) && in(f.z, 2);
 }
 
+// Octet k8 of a thread's ring of RING entries.
+template <int RING>
+__device__ __forceinline__ uint4 ring_octet(const uint2* myring, uint32_t k8) {
+    const uint32_t o = 2 * (k8 & (uint32_t)(RING / 8 - 1));
+    const uint2 lo = myring[o], hi = myring[o + 1];
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+// The neighbours of one target (float copy pf, union cell uc) among the staged
+// union, in walk order: their union indices go through the ring, and their
+// number is returned.  group(before, now) is called after each group of at
+// most four, row(now) after each row of the stencil, with the counts;
+// entries they leave in the ring are the caller's.  exact(u) is the predicate
+// inside the band.  Entries are appended without branches: every candidate is
+// written at the next free place and the count advances only for accepted
+// ones.
+template <int S, int RING, typename T, typename CFG, typename Exact, typename Group,
+          typename Row>
+__device__ __forceinline__ uint32_t tile_candidates(const Tiles& TL, const TileMeta<CFG>& M,
+                                                    const float4* Pf, const PairConst<T>& C,
+                                                    const float4& pf, const int uc[3], bool clip,
+                                                    uint2* myring, Exact&& exact, Group&& group,
+                                                    Row&& row) {
+    // the octets are read back as uint2: the halves may alias them
+    typedef uint16_t __attribute__((may_alias)) Half;
+    Half* const my = (Half*)myring;
+    const float cxf = (float)TL.cen[0], cyf = (float)TL.cen[1], czf = (float)TL.cen[2];
+    uint32_t cnt = 0;
+    // the (2S+1)^2 stencil rows in walk order (z planes, then y rows);
+    // loops, not unrolled, so the kernel's code stays small enough for the
+    // instruction cache.  A plane's distance is taken once for its rows,
+    // and the x range in cell units from px_c, the target's x in cells
+    // shifted by the union centre and 1/2 (the clip keeps its margins:
+    // roundings of these forms move it by far less than clip_pad)
+    constexpr int NR = 2 * S + 1;
+    const float px_c = pf.x * TL.inv_csf[0] + (cxf + 0.5f);
+#pragma unroll 1
+    for (int iz = 0; iz < NR; ++iz) {
+        const int uz = uc[2] + iz - S;
+        const float dz =
+            fmaxf(fabsf(pf.z - ((float)uz - czf) * TL.csf[2]) - 0.5f * TL.csf[2], 0.f);
+        const float w2z = TL.rclip2 - dz * dz;
+        if (clip && !(w2z > 0.f)) continue;
+        const int planec = TL.uw * TL.uh * uz;
+#pragma unroll 1
+        for (int iy = 0; iy < NR; ++iy) {
+            const int uy = uc[1] + iy - S;
+            const float dy =
+                fmaxf(fabsf(pf.y - ((float)uy - cyf) * TL.csf[1]) - 0.5f * TL.csf[1], 0.f);
+            const float w2 = w2z - dy * dy;
+            if (clip && !(w2 > 0.f)) continue;
+            int xa = uc[0] - S, xb = uc[0] + S;
+            if (clip) {
+                const float wc = (__builtin_amdgcn_sqrtf(w2) + TL.clip_pad) * TL.inv_csf[0];
+                xa = max(xa, (int)floorf(px_c - wc));
+                xb = min(xb, (int)floorf(px_c + wc));
+                if (xa > xb) continue;
+            }
+            const int rowc = planec + TL.uw * uy;
+            const uint32_t ua = M.off[rowc + xa], ue = M.off[rowc + xb + 1];
+            // candidates four at a time, the next four loaded while these
+            // are tested; those past the row's end (read from the padding or
+            // the next row) are infinitely far
+            uint32_t u = ua;
+            float4 c[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] = Pf[u + q];
+#pragma unroll 1
+            for (; u < ue; u += 4) {
+                const uint32_t lim = ue - u;  // candidates left in the row
+                float r2[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float dx = pf.x - c[q].x, ddy = pf.y - c[q].y, ddz = pf.z - c[q].z;
+                    r2[q] = dx * dx + ddy * ddy + ddz * ddz;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[q] = Pf[u + 4 + q];
+                uint32_t acc[4];
+                bool band[4];
+                bool anyband = false;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float x = (uint32_t)q < lim ? r2[q] : __builtin_huge_valf();
+                    acc[q] = x < C.R2_lo ? 1u : 0u;
+                    band[q] = fabsf(x - C.R2_mid) < C.R2_w;
+                    anyband |= band[q];
+                }
+                if (__builtin_amdgcn_ballot_w64(anyband)) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (band[q]) acc[q] = exact(u + q) ? 1u : 0u;
+                }
+                const uint32_t before = cnt;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    my[cnt & (RING - 1)] = (Half)(u + q);
+                    cnt += acc[q];
+                }
+                group(before, cnt);
+            }
+            row(cnt);
+        }
+    }
+    return cnt;
+}
+
 // Neighbour lists of the tile's targets: ncnt[i] = |N(i)|, entries while the
 // count is within cap; targets with more are left to the fallback, as are all
 // targets of a tile whose union exceeds cap_union.  count_pairs: the
 // interactions of the counted targets go to the tile's counter.  Only the
 // float copy of the union is staged (so that several workgroups share a CU);
 // the exact predicate inside the band reads the candidate's record from global
-// memory.  Entries are appended without branches: every candidate is written
-// at the next free place of a 16-entry ring and the count advances only for
-// accepted ones; a completed octet is stored at once.
+// memory.  A completed octet is stored at once.
 template <int S, typename T>
 __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
     int n, Grid G, PairConst<T> C, Tiles TL, int cap_union,
@@ -667,7 +779,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
             __syncthreads();
     }
     if (overflow) {
-        tile_mark_overflow(M, ncnt);
+        tile_mark_overflow(M, ncnt, list, cap);
         if (threadIdx.x == 0 && M.ntargets) *fallback = epoch;
         // the counter is still touched: tile 0 raises the number of counters
         // the reader sums
@@ -675,16 +787,8 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
         return;
     }
     uint2* const myring = &ringbuf[threadIdx.x * kRingStride];
-    // the octets are read back as uint2: the halves may alias them
-    typedef uint16_t __attribute__((may_alias)) Half;
-    Half* my = (Half*)myring;
-    auto ring_octet = [&](uint32_t k8) {
-        const uint2 lo = myring[2 * (k8 & 1)], hi = myring[2 * (k8 & 1) + 1];
-        return make_uint4(lo.x, lo.y, hi.x, hi.y);
-    };
     uint32_t counted = 0;
     bool need_fb = false;
-    const float cxf = (float)TL.cen[0], cyf = (float)TL.cen[1], czf = (float)TL.cen[2];
     for (uint32_t t = threadIdx.x; t < M.ntargets; t += NT) {
         uint32_t ui, i;
         int uc[3];
@@ -702,86 +806,15 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
             union_coords(TL, c, cu);
             return tile_exact(ri, uc, pos[M.gs[c] + (u - M.off[c])], cu, c0, G, TL, C);
         };
-        uint32_t cnt = 0;
-        // the (2S+1)^2 stencil rows in walk order (z planes, then y rows);
-        // loops, not unrolled, so the kernel's code stays small enough for the
-        // instruction cache.  A plane's distance is taken once for its rows,
-        // and the x range in cell units from px_c, the target's x in cells
-        // shifted by the union centre and 1/2 (the clip keeps its margins:
-        // roundings of these forms move it by far less than clip_pad)
-        constexpr int NR = 2 * S + 1;
-        const float px_c = pf.x * TL.inv_csf[0] + (cxf + 0.5f);
-#pragma unroll 1
-        for (int iz = 0; iz < NR; ++iz) {
-            const int uz = uc[2] + iz - S;
-            const float dz =
-                fmaxf(fabsf(pf.z - ((float)uz - czf) * TL.csf[2]) - 0.5f * TL.csf[2], 0.f);
-            const float w2z = TL.rclip2 - dz * dz;
-            if (clip && !(w2z > 0.f)) continue;
-            const int planec = TL.uw * TL.uh * uz;
-#pragma unroll 1
-            for (int iy = 0; iy < NR; ++iy) {
-                const int uy = uc[1] + iy - S;
-                const float dy =
-                    fmaxf(fabsf(pf.y - ((float)uy - cyf) * TL.csf[1]) - 0.5f * TL.csf[1], 0.f);
-                const float w2 = w2z - dy * dy;
-                if (clip && !(w2 > 0.f)) continue;
-                int xa = uc[0] - S, xb = uc[0] + S;
-                if (clip) {
-                    const float wc = (__builtin_amdgcn_sqrtf(w2) + TL.clip_pad) * TL.inv_csf[0];
-                    xa = max(xa, (int)floorf(px_c - wc));
-                    xb = min(xb, (int)floorf(px_c + wc));
-                    if (xa > xb) continue;
-                }
-                const int rowc = planec + TL.uw * uy;
-                const uint32_t ua = M.off[rowc + xa], ue = M.off[rowc + xb + 1];
-                // candidates four at a time, the next four loaded while these
-                // are tested; those past the row's end (read from the padding or
-                // the next row) are infinitely far
-                uint32_t u = ua;
-                float4 c[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) c[q] = Pf[u + q];
-#pragma unroll 1
-                for (; u < ue; u += 4) {
-                    const uint32_t lim = ue - u;  // candidates left in the row
-                    float r2[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float dx = pf.x - c[q].x, ddy = pf.y - c[q].y, ddz = pf.z - c[q].z;
-                        r2[q] = dx * dx + ddy * ddy + ddz * ddz;
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) c[q] = Pf[u + 4 + q];
-                    uint32_t acc[4];
-                    bool band[4];
-                    bool anyband = false;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float x = (uint32_t)q < lim ? r2[q] : __builtin_huge_valf();
-                        acc[q] = x < C.R2_lo ? 1u : 0u;
-                        band[q] = fabsf(x - C.R2_mid) < C.R2_w;
-                        anyband |= band[q];
-                    }
-                    if (__builtin_amdgcn_ballot_w64(anyband)) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (band[q]) acc[q] = exact(u + q) ? 1u : 0u;
-                    }
-                    const uint32_t c_in = cnt;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        my[cnt & 15] = (Half)(u + q);
-                        cnt += acc[q];
-                    }
-                    // an octet completed (at most one per group of four)
-                    if ((cnt ^ c_in) & ~7u) {
-                        const uint32_t k8 = c_in >> 3;
-                        if (k8 < (cap >> 3)) list[tile_octet(i, cap, k8)] = ring_octet(k8);
-                    }
-                }
-            }
-        }
+        const uint32_t cnt = tile_candidates<S, 16>(
+            TL, M, Pf, C, pf, uc, clip, myring, exact,
+            [&](uint32_t before, uint32_t now) {
+                // an octet completed (at most one per group of four)
+                const uint32_t k8 = before >> 3;
+                if (((before ^ now) & ~7u) && k8 < (cap >> 3))
+                    list[tile_octet(i, cap, k8)] = ring_octet<16>(myring, k8);
+            },
+            [](uint32_t) {});
         // the last, partial octet is filled up with the target itself
         if (cnt <= cap && (cnt & 7)) {
             const uint32_t r = cnt & 7;
@@ -789,7 +822,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
                 const uint32_t lo = k < r ? w & 0xffffu : ui;
                 return lo | (k + 1 < r ? w & 0xffff0000u : ui << 16);
             };
-            const uint4 v = ring_octet(cnt >> 3);
+            const uint4 v = ring_octet<16>(myring, cnt >> 3);
             list[tile_octet(i, cap, cnt >> 3)] =
                 make_uint4(fill(v.x, 0), fill(v.y, 2), fill(v.z, 4), fill(v.w, 6));
         }
@@ -799,6 +832,251 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
     }
     if (__syncthreads_or(need_fb) && threadIdx.x == 0) *fallback = epoch;
     if (count_pairs) tile_count<NT>(counted, pairs, blk);
+}
+
+// Neighbour lists in the global format (k_nlist_walk's, entry for entry):
+// candidates from the union staged in LDS instead of a walk of each particle's cells through L1
+// and L2.  Each staged particle has its list word for a target in union cell
+// 0, to which a target adds a constant: the mixed-precision code of a stencil
+// offset is linear in the two cells, the FP64 code is the neighbour's image
+// alone.  Completed octets of union indices are turned into words and stored,
+// 256 bytes apart (rows of 64 slots), after a row of the stencil that leaves
+// some lane with kFlush of them or more, by the lanes of a wave together: at
+// every completed octet some lane or other would take the whole wave through
+// the stores.  The targets of a tile whose union does
+// not fit (or, in FP64, holds a particle far outside its cell) walk the
+// cells.  Workgroup b takes every gridDim-th tile and adds the interactions it
+// counted to pairs[b].
+// Boxes of 4 x 4 x 4 half-size cells and 256 threads, two workgroups per CU.
+template <int S, typename T>
+__global__ __launch_bounds__(CfgD::kThreads, 2) void k_tile_nlist(
+    int n, Grid G, PairConst<T> C, Tiles TL, const uint32_t* __restrict__ skey, const typename Rec<T>::type* __restrict__ pos,
+    const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
+    uint32_t* __restrict__ list, uint32_t* __restrict__ ncnt, int count_pairs,
+    unsigned long long* __restrict__ pairs) {
+    using R = typename Rec<T>::type;
+    using CFG = CfgD;
+    using Code = NbrCode<3, S, T>;
+    constexpr int NT = CFG::kThreads, NR = 2 * S + 1;
+    // each thread's ring of 64 list entries, 136 bytes apart
+    constexpr int kRing = 64, kRingStride = kRing / 4 + 1;  // uint2 per thread
+    constexpr uint32_t kFlush = 24;
+    __shared__ TileMeta<CFG> M;
+    __shared__ float4 Pf[CFG::kCap + 8];
+    __shared__ uint32_t word[CFG::kCap];
+    __shared__ uint2 ringbuf[NT * kRingStride];
+    static_assert(sizeof(ringbuf) >= CFG::kCap * sizeof(uint16_t), "cell table");
+    uint2* const myring = &ringbuf[threadIdx.x * kRingStride];
+    const int blk = xcd_block();
+    uint32_t counted = 0;
+    for (int tile = blk; tile < TL.ntiles; tile += (int)gridDim.x) {
+        int c0[3];
+        tile_origin(TL, tile, c0);
+        const uint32_t total = tile_setup(G, TL, c0, cstart, cend, n, M, (int)threadIdx.x);
+        if (M.ntargets == 0) {
+            __syncthreads();  // M is free
+            continue;
+        }
+        bool overflow = total > (uint32_t)TL.cap;
+        if (!overflow) {
+            bool far = false;
+            tile_cellof(TL, M, (uint16_t*)ringbuf);
+            const uint16_t* cellof = (const uint16_t*)ringbuf;
+            struct Rj {
+                R r;
+                uint32_t j;
+            };
+            StageRegs<CFG, Rj> regs;
+            tile_stage_loads(M, cellof, [&](uint32_t j) { return Rj{pos[j], j}; }, regs,
+                             (int)threadIdx.x);
+            tile_stage_store(
+                TL, M, cellof, regs,
+                [&](uint32_t u, const Rj& r, int ux, int uy, int uz) {
+                    const int uc[3] = {ux, uy, uz};
+                    float4 f = filt_copy(r.r, uc, c0, G, TL, C, &far);
+                    f.w = __int_as_float(ux + TL.uw * (uy + TL.uh * uz));
+                    Pf[u] = f;
+                    const int code =
+                        sizeof(T) == 8
+                            ? Code::row_base(0, 0, tile_wrap(G, 0, c0[0], ux, S),
+                                             tile_wrap(G, 1, c0[1], uy, S),
+                                             tile_wrap(G, 2, c0[2], uz, S))
+                            : ux + NR * (uy + NR * uz);
+                    word[u] = (r.j << Code::kBits) + (uint32_t)code;
+                },
+                (int)threadIdx.x);
+            overflow = __syncthreads_or(sizeof(T) == 8 && far);
+        }
+        for (uint32_t t = threadIdx.x; t < M.ntargets; t += NT) {
+            uint32_t ui, i;
+            int uc[3];
+            tile_target(TL, M, t, &ui, &i, uc);
+            uint32_t* __restrict__ col = list + list_column(i, cap);
+            const R ri = pos[i];
+            uint32_t cnt = 0;
+            if (overflow) {
+                walk_pairs<3, S, T>(G, C, skey[i], ri, pos, skey, cstart, cend, (uint32_t)n,
+                                    NoPayload(),
+                                    [&](uint32_t j, const R&, int, const Geom<T>&, uint32_t code) {
+                                        if (cnt < cap)
+                                            col[cnt * kListTile] = (j << Code::kBits) | code;
+                                        ++cnt;
+                                    });
+            } else {
+                const float4 pf = Pf[ui];
+                const bool clip = tile_inside(ri, pf, uc, TL);
+                // word of a neighbour in union cell u, less that of cell uc
+                const uint32_t base =
+                    sizeof(T) == 8 ? 0u
+                                   : (uint32_t)(S * (1 + NR + NR * NR) -
+                                                (uc[0] + NR * (uc[1] + NR * uc[2])));
+                auto exact = [&](uint32_t u) {
+                    const int c = __float_as_int(Pf[u].w);
+                    int cu[3];
+                    union_coords(TL, c, cu);
+                    return tile_exact(ri, uc, pos[(word[u] + base) >> Code::kBits], cu, c0, G, TL, C);
+                };
+                auto put = [&](uint32_t k8, uint32_t m) {  // m entries of octet k8
+                    const uint4 v = ring_octet<kRing>(myring, k8);
+                    uint32_t* __restrict__ c = col + (size_t)(8 * k8) * kListTile;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if ((uint32_t)e < m) c[e * (int)kListTile] = word[half_of(v, e)] + base;
+                };
+                uint32_t done = 0;  // entries stored (or beyond cap)
+                auto flush = [&](uint32_t now) {
+                    while (done + 8 <= now) {
+                        if (done < cap) put(done >> 3, min(cap - done, 8u));
+                        done += 8;
+                    }
+                };
+                cnt = tile_candidates<S, kRing>(
+                    TL, M, Pf, C, pf, uc, clip, myring, exact,
+                    [&](uint32_t, uint32_t now) {
+                        if (now - done > kRing - 8) flush(now);  // the ring is nearly full
+                    },
+                    [&](uint32_t now) {
+                        if (__builtin_amdgcn_ballot_w64(now - done >= kFlush)) flush(now);
+                    });
+                flush(cnt);
+                if (done < cap && done < cnt) put(done >> 3, min(cap, cnt) - done);
+            }
+            ncnt[i] = cnt;
+            counted += cnt;
+        }
+        __syncthreads();  // the tile's LDS is free
+    }
+    if (count_pairs) tile_count<NT>(counted, pairs, (int)blockIdx.x);
+}
+
+// The CSR lists (sph_neighbors) of the tile's targets with complete lists.  A
+// wave takes 16 targets: it reads their octets as rows of 16 (adjacent slots
+// are adjacent there) into LDS, 16 octets a target at a time, and writes each
+// list as a run, a lane an entry, whose global slot comes from a table of the
+// union in LDS.  off[i]: the first entry of slot i.  (100^3 cube, whole cells,
+// 113M entries: 0.19 ms; a lane reading its entry's half word from memory
+// fetched each octet row four times, 0.46 ms; a second cell walk 1.28 ms.)
+template <typename CFG>
+__global__ __launch_bounds__(CFG::kThreads) void k_tile_expand(
+    int n, Grid G, Tiles TL, int cap_union, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
+    const uint32_t* __restrict__ ncnt, const int64_t* __restrict__ off,
+    int32_t* __restrict__ nbr) {
+    constexpr uint32_t kT = 16, kO = 16;  // targets and octets at a time
+    __shared__ TileMeta<CFG> M;
+    __shared__ uint32_t slot[CFG::kCap];
+    __shared__ uint4 buf_[CFG::kThreads / 64][kT][kO + 1];
+    const int blk = xcd_block();
+    int c0[3];
+    tile_origin(TL, blk, c0);
+    const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
+    if (tile_empty(G, TL, c0, cstart, cend)) return;
+    const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
+    if (total > (uint32_t)cap_union) return;  // every target is the fallback's
+    const int ncu = TL.uw * TL.uh * TL.ud;
+    for (int c = threadIdx.x; c < ncu; c += CFG::kThreads)
+        for (uint32_t u = M.off[c]; u < M.off[c + 1]; ++u) slot[u] = M.gs[c] + (u - M.off[c]);
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t nt = M.ntargets;
+    typedef uint16_t __attribute__((may_alias)) Half;
+    for (uint32_t t0 = w * kT; t0 < nt; t0 += CFG::kThreads / 64 * kT) {
+        // lane l: target t0 + l % 16
+        uint32_t ui, i;
+        int uc[3];
+        const uint32_t tt = t0 + lane % kT;
+        tile_target(TL, M, min(tt, nt - 1), &ui, &i, uc);
+        uint32_t cnt = ncnt[i];
+        const int64_t at = off[i];
+        const uint4* __restrict__ base = list + tile_octet(i, cap, 0);
+        // (left to the fallback: above the capacity or in a marked tile)
+        if (tt >= nt || cnt > cap || half_of(base[0], 0) == kNoIndex) cnt = 0;
+        uint32_t most = cnt;
+#pragma unroll
+        for (int d = kT / 2; d >= 1; d >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, 64));
+        for (uint32_t k0 = 0; k0 < most; k0 += 8 * kO) {
+#pragma unroll
+            for (uint32_t q = 0; q < kO * kT / 64; ++q) {
+                const uint32_t o = q * (64 / kT) + lane / kT;
+                if (k0 + 8 * o < cnt) buf_[w][lane % kT][o] = base[(size_t)(k0 / 8 + o) * 64];
+            }
+            wave_sync();
+#pragma unroll 4
+            for (uint32_t t = 0; t < kT; ++t) {
+                const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, (int)t);
+                const int64_t a =
+                    ((int64_t)__builtin_amdgcn_readlane((int)(at >> 32), (int)t) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)at, (int)t);
+                const Half* e = (const Half*)&buf_[w][t][0];
+#pragma unroll
+                for (uint32_t h = 0; h < 8 * kO / 64; ++h) {
+                    const uint32_t k = lane + 64 * h;
+                    if (k0 + k < c) nbr[a + k0 + k] = (int32_t)slot[e[k]];
+                }
+            }
+            wave_sync();
+        }
+    }
+}
+
+// What the tile build left of the CSR lists: counts of the targets of tiles
+// that did not fit (before the scan), and the entries of those and of targets
+// with more neighbours than the list capacity, by the cell walk.
+template <int S, typename T>
+__global__ __launch_bounds__(kBlock) void k_tile_fallback_count(
+    int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
+    const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, uint32_t* __restrict__ ncnt, uint32_t epoch,
+    const uint32_t* __restrict__ fallback) {
+    if (*fallback != epoch) return;
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        if (ncnt[i] != kTileOverflow) continue;
+        uint32_t c = 0;
+        walk_pairs<3, S, T>(G, C, skey[i], pos[i], pos, skey, cstart, cend, (uint32_t)n, NoPayload(),
+                            [&](uint32_t, const typename Rec<T>::type&, int, const Geom<T>&,
+                                uint32_t) { ++c; });
+        ncnt[i] = c;
+    }
+}
+template <int S, typename T>
+__global__ __launch_bounds__(kBlock) void k_tile_fallback_fill(
+    int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
+    const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
+    const uint32_t* __restrict__ ncnt, const int64_t* __restrict__ off, int32_t* __restrict__ nbr,
+    uint32_t epoch, const uint32_t* __restrict__ fallback) {
+    if (*fallback != epoch) return;
+    const uint16_t* __restrict__ half = reinterpret_cast<const uint16_t*>(list);
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        if (ncnt[i] <= cap && half[8 * tile_octet((uint32_t)i, cap, 0)] != kNoIndex) continue;
+        int64_t at = off[i];
+        const int64_t end = off[i + 1];
+        walk_pairs<3, S, T>(G, C, skey[i], pos[i], pos, skey, cstart, cend, (uint32_t)n, NoPayload(),
+                            [&](uint32_t j, const typename Rec<T>::type&, int, const Geom<T>&,
+                                uint32_t) {
+                                if (at < end) nbr[at++] = (int32_t)j;
+                            });
+    }
 }
 
 // Summation density (eq. 2), and with_eos the Tait EOS (eq. eos), of the
