@@ -89,7 +89,25 @@ __global__ __launch_bounds__(kBlock) void k_adj_seed(int n, const double* __rest
     lhat[s] = r;
 }
 
-// First gather: direct position and velocity adjoints, lam_rho, nu partials.
+// Sum of a value per thread into part[blk] (kBlock threads, fixed order),
+// added to what is there unless `first`.
+__device__ __forceinline__ void block_accum(double v, double* __restrict__ part, int blk,
+                                            int first) {
+    __shared__ double wsum[kBlock / 64];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) t += wsum[w];
+        part[blk] = first ? t : part[blk] + t;
+    }
+}
+
+// First gather: direct position and velocity adjoints, lam_rho; the block's nu
+// gradient goes to its own slot of nupart, which the steps of a segment
+// accumulate (first: the segment's first launch).
 template <int DIM, int SR, int KERNEL, typename T>
 __global__ __launch_bounds__(kBlock) void k_adj_pair1(
     int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
@@ -98,95 +116,145 @@ __global__ __launch_bounds__(kBlock) void k_adj_pair1(
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap,
     double* __restrict__ lx, double* __restrict__ lv, T* __restrict__ lrho,
-    double* __restrict__ nupart) {
-    const int i = xcd_block() * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const typename Rec<T>::type ri = pos[i];
-    const typename Vec4<T>::type vi = vel[i];
-    const typename Vec2<T>::type rpi = load_rp<DIM, T>(vi, rp, (uint32_t)i);
-    const typename Vec4<T>::type li = lhat[i];
-    const T h = p_rcp(C.inv_h);
-    const T mi = rec_mass(ri);
-    T gx = 0, gy = 0, gz = 0, hx = 0, hy = 0, hz = 0, lP = 0, lR = 0, nu_acc = 0;
-    struct Pay {
-        typename Vec4<T>::type v;
-        typename Vec2<T>::type rp;
-        typename Vec4<T>::type l;
-    };
-    for_each_neighbor_p<DIM, SR, T>(
-        i, G, C, ri, pos, skey, cstart, cend, (uint32_t)n, list, ncnt, cap,
-        [&](uint32_t j) {
-            typename Vec4<T>::type v = vel[j];
-            keep_whole<DIM>(v);
-            return Pay{v, load_rp<DIM, T>(v, rp, j), lhat[j]};
-        },
-        [&](uint32_t j, const typename Rec<T>::type& rj, const Pay& pj, const Geom<T>& g) {
-            const T r2 = g.r2;
-            const T dx = g.d[0], dy = g.d[1], dz = g.d[2];
-            if (j == (uint32_t)i || r2 == T(0)) return;
-            const typename Vec4<T>::type vj = pj.v;
-            const typename Vec2<T>::type rpj = pj.rp;
-            const typename Vec4<T>::type lj = pj.l;
-            const T r = p_sqrt(r2);
-            const T inv_r = p_rcp(r);
-            const T q = r * C.inv_h;
-            const T inv_q = h * inv_r;
-            T F, F1;
-            kernel_f_f1<KERNEL, T>(q, inv_q, C.sigma_h2, C.sigma_h4, &F, &F1);
-            const T inv_den = p_rcp(r2 + C.eta_h2);
-            const T Gv = F * r2 * inv_den;
-            const T G1 = F1 * r2 * inv_den + T(2) * F * C.eta_h2 * inv_den * inv_den;
-            const T inv_rs = p_rcp(rpi.x + rpj.x);
-            const T c4 = C.four_nu * inv_rs;
-            const T mj = rec_mass(rj);
-            const T wx = mj * li.x - mi * lj.x;
-            const T wy = mj * li.y - mi * lj.y;
-            const T wz = DIM == 3 ? mj * li.z - mi * lj.z : T(0);
-            const T vx = vi.x - vj.x, vy = vi.y - vj.y, vz = DIM == 3 ? vi.z - vj.z : T(0);
-            const T rw = dx * wx + dy * wy + (DIM == 3 ? dz * wz : T(0));
-            const T vw = vx * wx + vy * wy + (DIM == 3 ? vz * wz : T(0));
-            const T Ps = rpi.y + rpj.y;
-            const T cr = -Ps * F1 * rw + c4 * G1 * vw;
-            const T cw = -Ps * F;
-            gx += cw * wx + cr * dx;
-            gy += cw * wy + cr * dy;
-            const T cv = c4 * Gv;
-            hx += cv * wx;
-            hy += cv * wy;
-            if (DIM == 3) {
-                gz += cw * wz + cr * dz;
-                hz += cv * wz;
-            }
-            lP -= F * rw;
-            lR -= cv * inv_rs * vw;
-            const T lv_ = li.x * vx + li.y * vy + (DIM == 3 ? li.z * vz : T(0));
-            nu_acc += T(4) * mj * Gv * inv_rs * lv_;
-        });
-    // dP/drho = p'(rho)/rho^2 - 2 P / rho,  p'(rho) = 7 B (rho/rho0)^6 / rho0
-    const T rho = rpi.x;
-    const T rr = rho * C.inv_rho0;
-    const T rr2 = rr * rr;
-    const T dP = C.b7 * rr2 * rr2 * rr2 / (rho * rho) - T(2) * rpi.y / rho;
-    lrho[i] = lR + lP * dP;
-    lx[i] = (double)gx;
-    lx[(int64_t)n + i] = (double)gy;
-    lv[i] = (double)hx;
-    lv[(int64_t)n + i] = (double)hy;
-    if (DIM == 3) {
-        lx[2 * (int64_t)n + i] = (double)gz;
-        lv[2 * (int64_t)n + i] = (double)hz;
+    double* __restrict__ nupart, int first) {
+    const int blk = xcd_block();
+    const int i = blk * kBlock + threadIdx.x;
+    T nu_acc = 0;
+    if (i < n) {
+        const typename Rec<T>::type ri = pos[i];
+        const typename Vec4<T>::type vi = vel[i];
+        const typename Vec2<T>::type rpi = load_rp<DIM, T>(vi, rp, (uint32_t)i);
+        const typename Vec4<T>::type li = lhat[i];
+        const T h = p_rcp(C.inv_h);
+        const T mi = rec_mass(ri);
+        T gx = 0, gy = 0, gz = 0, hx = 0, hy = 0, hz = 0, lP = 0, lR = 0;
+        struct Pay {
+            typename Vec4<T>::type v;
+            typename Vec2<T>::type rp;
+            typename Vec4<T>::type l;
+        };
+        for_each_neighbor_p<DIM, SR, T>(
+            i, G, C, ri, pos, skey, cstart, cend, (uint32_t)n, list, ncnt, cap,
+            [&](uint32_t j) {
+                typename Vec4<T>::type v = vel[j];
+                keep_whole<DIM>(v);
+                return Pay{v, load_rp<DIM, T>(v, rp, j), lhat[j]};
+            },
+            [&](uint32_t j, const typename Rec<T>::type& rj, const Pay& pj, const Geom<T>& g) {
+                const T r2 = g.r2;
+                const T dx = g.d[0], dy = g.d[1], dz = g.d[2];
+                if (j == (uint32_t)i || r2 == T(0)) return;
+                const typename Vec4<T>::type vj = pj.v;
+                const typename Vec2<T>::type rpj = pj.rp;
+                const typename Vec4<T>::type lj = pj.l;
+                const T r = p_sqrt(r2);
+                const T inv_r = p_rcp(r);
+                const T q = r * C.inv_h;
+                const T inv_q = h * inv_r;
+                T F, F1;
+                kernel_f_f1<KERNEL, T>(q, inv_q, C.sigma_h2, C.sigma_h4, &F, &F1);
+                const T inv_den = p_rcp(r2 + C.eta_h2);
+                const T Gv = F * r2 * inv_den;
+                const T G1 = F1 * r2 * inv_den + T(2) * F * C.eta_h2 * inv_den * inv_den;
+                const T inv_rs = p_rcp(rpi.x + rpj.x);
+                const T c4 = C.four_nu * inv_rs;
+                const T mj = rec_mass(rj);
+                const T wx = mj * li.x - mi * lj.x;
+                const T wy = mj * li.y - mi * lj.y;
+                const T wz = DIM == 3 ? mj * li.z - mi * lj.z : T(0);
+                const T vx = vi.x - vj.x, vy = vi.y - vj.y, vz = DIM == 3 ? vi.z - vj.z : T(0);
+                const T rw = dx * wx + dy * wy + (DIM == 3 ? dz * wz : T(0));
+                const T vw = vx * wx + vy * wy + (DIM == 3 ? vz * wz : T(0));
+                const T Ps = rpi.y + rpj.y;
+                const T cr = -Ps * F1 * rw + c4 * G1 * vw;
+                const T cw = -Ps * F;
+                gx += cw * wx + cr * dx;
+                gy += cw * wy + cr * dy;
+                const T cv = c4 * Gv;
+                hx += cv * wx;
+                hy += cv * wy;
+                if (DIM == 3) {
+                    gz += cw * wz + cr * dz;
+                    hz += cv * wz;
+                }
+                lP -= F * rw;
+                lR -= cv * inv_rs * vw;
+                const T lv_ = li.x * vx + li.y * vy + (DIM == 3 ? li.z * vz : T(0));
+                nu_acc += T(4) * mj * Gv * inv_rs * lv_;
+            });
+        // dP/drho = p'(rho)/rho^2 - 2 P / rho,  p'(rho) = 7 B (rho/rho0)^6 / rho0
+        const T rho = rpi.x;
+        const T rr = rho * C.inv_rho0;
+        const T rr2 = rr * rr;
+        const T dP = C.b7 * rr2 * rr2 * rr2 / (rho * rho) - T(2) * rpi.y / rho;
+        lrho[i] = lR + lP * dP;
+        lx[i] = (double)gx;
+        lx[(int64_t)n + i] = (double)gy;
+        lv[i] = (double)hx;
+        lv[(int64_t)n + i] = (double)hy;
+        if (DIM == 3) {
+            lx[2 * (int64_t)n + i] = (double)gz;
+            lv[2 * (int64_t)n + i] = (double)hz;
+        }
     }
-    nupart[i] = (double)nu_acc;
+    block_accum((double)nu_acc, nupart, blk, first);
 }
 
-// Second gather: lam_x_i += sum_j (lam_rho_i m_j + lam_rho_j m_i) F r_ij.
-template <int DIM, int SR, int KERNEL, typename T>
+// What k_adj_pair2 does with the position adjoint besides adding its gather:
+// the reverse of the kicks and the drift, written in the order before the
+// sort (d = perm[s]),
+//   lam_x' = lam_x_in + (dA/dx')^T lhat;  lam_v = lam_u_in + (dA/dv)^T lhat + dt lam_x'
+//   out: lam_x = lam_x', lam_u = lam_v, lam_a = dt/2 lam_v   (walls: 0),
+// and, when another step of the segment follows, that step's lhat (its
+// k_adj_seed) instead of lam_a.  Layout of lam buffers: [x (dim arrays)][u (dim
+// arrays)][a (dim arrays)].
+struct AdjKick {
+    const double* lam_in;
+    const double* lvd;
+    const uint8_t* type;
+    const uint32_t* perm;
+    double dt, hdt;
+    double* lam_out;
+    int last;  // the segment's last reverse step: lam_a is written, no lhat
+};
+template <int DIM, typename T>
+__device__ __forceinline__ void adj_kick(int s, const double lx[3], const AdjKick& K, int n,
+                                         typename Vec4<T>::type* __restrict__ lhat) {
+#pragma clang fp contract(off)
+    const int64_t d = K.perm[s];
+    const int64_t N = n;
+    const bool fluid = K.type[s] == 0;
+    T l[3] = {T(0), T(0), T(0)};
+    for (int k = 0; k < DIM; ++k) {
+        double lxp = 0.0, lvv = 0.0;
+        if (fluid) {
+            lxp = K.lam_in[k * N + s] + lx[k];
+            lvv = K.lam_in[(DIM + k) * N + s] + K.lvd[k * N + s];
+            lvv = lvv + K.dt * lxp;
+        }
+        const double la = K.hdt * lvv;
+        K.lam_out[k * N + d] = lxp;
+        K.lam_out[(DIM + k) * N + d] = lvv;
+        if (K.last)
+            K.lam_out[(2 * DIM + k) * N + d] = la;
+        else if (fluid)
+            l[k] = (T)(la + K.hdt * lvv);
+    }
+    if (K.last) return;
+    typename Vec4<T>::type r;
+    r.x = l[0]; r.y = l[1]; r.z = l[2]; r.w = T(0);
+    lhat[d] = r;
+}
+
+// Second gather: lam_x_i += sum_j (lam_rho_i m_j + lam_rho_j m_i) F r_ij;
+// KICK: followed by adj_kick, else added to lx.
+template <int DIM, int SR, int KERNEL, typename T, bool KICK>
 __global__ __launch_bounds__(kBlock) void k_adj_pair2(
     int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
     const typename Rec<T>::type* __restrict__ pos, const T* __restrict__ lrho,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap,
-    double* __restrict__ lx) {
+    double* __restrict__ lx, AdjKick K, typename Vec4<T>::type* __restrict__ lhat) {
     const int i = xcd_block() * kBlock + threadIdx.x;
     if (i >= n) return;
     const typename Rec<T>::type ri = pos[i];
@@ -205,38 +273,13 @@ __global__ __launch_bounds__(kBlock) void k_adj_pair2(
             ay += c * g.d[1];
             if (DIM == 3) az += c * g.d[2];
         });
-    lx[i] += (double)ax;
-    lx[(int64_t)n + i] += (double)ay;
-    if (DIM == 3) lx[2 * (int64_t)n + i] += (double)az;
-}
-
-// Reverse of the kicks and the drift, written in the order before the sort:
-//   lam_x' = lam_x_in + (dA/dx')^T lhat;  lam_v = lam_u_in + (dA/dv)^T lhat + dt lam_x'
-//   out: lam_x = lam_x', lam_u = lam_v, lam_a = dt/2 lam_v   (walls: 0).
-// Layout of lam buffers: [x (dim arrays)][u (dim arrays)][a (dim arrays)].
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_adj_kick(int n, const double* __restrict__ lam_in,
-                                                     const double* __restrict__ lxd,
-                                                     const double* __restrict__ lvd,
-                                                     const uint8_t* __restrict__ type,
-                                                     const uint32_t* __restrict__ perm, double dt,
-                                                     double hdt, double* __restrict__ lam_out) {
-#pragma clang fp contract(off)
-    const int s = blockIdx.x * kBlock + threadIdx.x;
-    if (s >= n) return;
-    const int64_t d = perm[s];
-    const int64_t N = n;
-    const bool fluid = type[s] == 0;
-    for (int k = 0; k < DIM; ++k) {
-        double lxp = 0.0, lvv = 0.0;
-        if (fluid) {
-            lxp = lam_in[k * N + s] + lxd[k * N + s];
-            lvv = lam_in[(DIM + k) * N + s] + lvd[k * N + s];
-            lvv = lvv + dt * lxp;
-        }
-        lam_out[k * N + d] = lxp;
-        lam_out[(DIM + k) * N + d] = lvv;
-        lam_out[(2 * DIM + k) * N + d] = hdt * lvv;
+    const double add[3] = {(double)ax, (double)ay, (double)az};
+    double sum[3] = {0.0, 0.0, 0.0};
+    for (int k = 0; k < DIM; ++k) sum[k] = lx[k * (int64_t)n + i] + add[k];
+    if (KICK) {
+        adj_kick<DIM, T>(i, sum, K, n, lhat);
+    } else {
+        for (int k = 0; k < DIM; ++k) lx[k * (int64_t)n + i] = sum[k];
     }
 }
 
@@ -281,21 +324,7 @@ __global__ __launch_bounds__(kBlock) void k_ke_seed(int n, const double* __restr
     }
 }
 
-// Fixed-order FP64 sum: per-block partials, then one block adds the total
-// to *out.
-static __global__ __launch_bounds__(kBlock) void k_sum_partial(int n, const double* __restrict__ v,
-                                                        double* __restrict__ part) {
-    __shared__ double sh[kBlock];
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    sh[threadIdx.x] = i < n ? v[i] : 0.0;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
+// Fixed-order FP64 sum of per-block partials, added to *out.
 static __global__ __launch_bounds__(kBlock) void k_sum_accum(int nparts, const double* __restrict__ part,
                                                       double* __restrict__ out) {
     __shared__ double sh[kBlock];

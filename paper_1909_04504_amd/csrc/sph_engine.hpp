@@ -420,9 +420,10 @@ struct StateOff {
 // do with chains.  The last launch's cells per wave: about one particle per
 // lane (sparse grids have many empty cells beside full ones, so that the
 // lattice counts where the mean is below it).
-// Grids of up to kDirectCells cells count the particles before a wave in the
-// wave itself (16 bytes a lane and round); above, k_cell_sums does.
-constexpr int64_t kDirectCells = 4096;
+// Grids of up to kDirectCells cells count the particles before a block in the
+// block itself (at most 16 rounds of 16 bytes a thread); above, k_cell_sums
+// does.
+constexpr int64_t kDirectCells = 16384;
 struct SortShape {
     int shift, cpw;
     int64_t ngroups;
@@ -574,7 +575,7 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
         L.lxd = take(8 * d * N);
         L.lvd = take(8 * d * N);
         L.lrho = take(T * N);
-        L.nupart = take(8 * N);
+        L.nupart = take(8 * (size_t)blocks_for(n));
         size_t so = 0;
         auto slot_take = [&](size_t bytes) {
             const size_t o = so;
@@ -1241,47 +1242,54 @@ struct Engine {
         return flush_diag();
     }
 
-    // (dA/dx)^T lhat -> lxd, (dA/dv)^T lhat -> lvd, (dA/dnu)^T lhat added to
-    // *dJ, at the evaluation whose records are current; lhat = lam_a +
-    // hdt lam_u (fluid), read through `gather` (identity if null).
-    int adjoint_rhs(const double* lam_u, const double* lam_a, int64_t ld, double hdt,
-                    const uint8_t* type, const uint32_t* gather, double* dJ, bool build_list) {
+    V4* lhat() const { return (V4*)(ws + L.lhat); }
+    double* lxd() const { return (double*)(ws + L.lxd); }
+    double* lvd() const { return (double*)(ws + L.lvd); }
+    double* nupart() const { return (double*)(ws + L.nupart); }
+
+    // lhat = lam_a + hdt lam_u (fluid), read through `gather` (identity if null).
+    int adjoint_seed(const double* lam_u, const double* lam_a, int64_t ld, double hdt,
+                     const uint8_t* type, const uint32_t* gather) {
+        launch(K_ADJ_SEED, sph::k_adj_seed<DIM, T>, blocks_for(n), st, n, lam_u, lam_a, ld, hdt,
+               type, gather, lhat());
+        return launch_check("k_adj_seed");
+    }
+    // (dA/dx)^T lhat -> lxd, (dA/dv)^T lhat -> lvd, (dA/dnu)^T lhat to the
+    // blocks' partials (first: not added to them), at the evaluation whose
+    // records are current; with kick, the reverse of the step in the second
+    // pass.
+    int adjoint_rhs(bool build_list, bool first, const sph::AdjKick* kick) {
         const unsigned nb = blocks_for(n);
         if (build_list && L.cap) SPH_TRY(nlist(start(), start() + 1, false));
-        V4* lhat = (V4*)(ws + L.lhat);
-        double* lxd = (double*)(ws + L.lxd);
-        double* lvd = (double*)(ws + L.lvd);
         T* lrho = (T*)(ws + L.lrho);
-        double* nup = (double*)(ws + L.nupart);
-        double* part = (double*)(ws + L.diag);
-        {
-            launch(K_ADJ_SEED, sph::k_adj_seed<DIM, T>, nb, st, n, lam_u, lam_a, ld, hdt, type,
-                                                               gather, lhat);
-            SPH_TRY(launch_check("k_adj_seed"));
-        }
-        {
-            with_reach([&](auto R) {
-                launch(K_ADJ_PAIR1, sph::k_adj_pair1<DIM, decltype(R)::value, KERNEL, T>, nb, st,
-                    n, G, C, skey(), pos(), vel(), rp(), lhat, start(), start() + 1,
-                    list_or_null(), lcnt(), L.cap, lxd, lvd, lrho, nup);
-            });
-            SPH_TRY(launch_check("k_adj_pair1"));
-        }
-        {
-            with_reach([&](auto R) {
-                launch(K_ADJ_PAIR2, sph::k_adj_pair2<DIM, decltype(R)::value, KERNEL, T>, nb, st,
-                    n, G, C, skey(), pos(), lrho, start(), start() + 1, list_or_null(), lcnt(),
-                    L.cap, lxd);
-            });
-            SPH_TRY(launch_check("k_adj_pair2"));
-        }
-        launch(K_ADJ_REDUCE, sph::k_sum_partial, nb, st, n, nup, part);
-        SPH_TRY(launch_check("k_sum_partial"));
-        launch(K_ADJ_REDUCE, sph::k_sum_accum, 1, st, (int)nb, part, dJ);
+        with_reach([&](auto R) {
+            launch(K_ADJ_PAIR1, sph::k_adj_pair1<DIM, decltype(R)::value, KERNEL, T>, nb, st,
+                n, G, C, skey(), pos(), vel(), rp(), lhat(), start(), start() + 1,
+                list_or_null(), lcnt(), L.cap, lxd(), lvd(), lrho, nupart(), first ? 1 : 0);
+        });
+        SPH_TRY(launch_check("k_adj_pair1"));
+        with_reach([&](auto R) {
+            constexpr int S = decltype(R)::value;
+            if (kick)
+                launch(K_ADJ_PAIR2, sph::k_adj_pair2<DIM, S, KERNEL, T, true>, nb, st, n, G, C,
+                       skey(), pos(), lrho, start(), start() + 1, list_or_null(), lcnt(), L.cap,
+                       lxd(), *kick, lhat());
+            else
+                launch(K_ADJ_PAIR2, sph::k_adj_pair2<DIM, S, KERNEL, T, false>, nb, st, n, G, C,
+                       skey(), pos(), lrho, start(), start() + 1, list_or_null(), lcnt(), L.cap,
+                       lxd(), sph::AdjKick{}, lhat());
+        });
+        return launch_check("k_adj_pair2");
+    }
+    // Adds the blocks' partials to *dJ.
+    int adjoint_nu(double* dJ) {
+        launch(K_ADJ_REDUCE, sph::k_sum_accum, 1, st, (int)blocks_for(n), nupart(), dJ);
         return launch_check("k_sum_accum");
     }
 
-    // k recomputed steps from the checkpoint, then their reverse.
+    // k recomputed steps from the checkpoint, then their reverse.  The last
+    // recomputed step ends with its density: the reverse needs its records,
+    // not the state after it.
     int step_backward(const sph_particles* ck, int64_t k, const double* lam_in, double* lam_out,
                       double* dJ) {
         const sph::State user = user_state(ck, prm);
@@ -1298,26 +1306,26 @@ struct Engine {
             op.hashed = s > 0;
             SPH_TRY(sort_into(cur, nxt, op));
             SPH_TRY(density(nxt, start(), start() + 1, true));
-            SPH_TRY(momentum(nxt, start(), start() + 1, true, s < k - 1));
+            if (s < k - 1) SPH_TRY(momentum(nxt, start(), start() + 1, true, true));
             std::swap(cur, nxt);
         }
         const int64_t N = n;
         const double hdt = 0.5 * prm->dt;
         double* bufs[2] = {(double*)(ws + L.lamB), (double*)(ws + L.lamC)};
         const double* in = lam_in;
+        SPH_TRY(adjoint_seed(in + DIM * N, in + 2 * DIM * N, N, hdt, typetape, nullptr));
         for (int64_t s = k - 1; s >= 0; --s) {
             tape_records(s);
             double* out = s == 0 ? lam_out : bufs[s & 1];
-            SPH_TRY(adjoint_rhs(in + DIM * N, in + 2 * DIM * N, N, hdt, typetape, nullptr, dJ,
-                                true));
-            launch(K_ADJ_KICK, sph::k_adj_kick<DIM>, blocks_for(n), st,
-                n, in, (const double*)(ws + L.lxd), (const double*)(ws + L.lvd), typetape, perm(),
-                prm->dt, hdt, out);
-            SPH_TRY(launch_check("k_adj_kick"));
+            const sph::AdjKick kick{in,     lvd(), typetape, perm(), prm->dt,
+                                    hdt,    out,   s == 0 ? 1 : 0};
+            // the lists of the last recomputed density are still there (the
+            // tiles' are not in the passes' format)
+            SPH_TRY(adjoint_rhs(s < k - 1 || tiled(), s == k - 1, &kick));
             in = out;
         }
         default_records();
-        return SPH_OK;
+        return adjoint_nu(dJ);
     }
 
     // Adjoint of one acceleration evaluation at the (unsorted) state st.
@@ -1333,10 +1341,11 @@ struct Engine {
         SPH_TRY(density(s1, start(), start() + 1, true));
         // the adjoint passes read global-format lists: rebuilt if the density
         // went through the tiles
-        SPH_TRY(adjoint_rhs(nullptr, lam_a, n, 0.0, s1.type, perm(), dJ, tiled()));
+        SPH_TRY(adjoint_seed(nullptr, lam_a, n, 0.0, s1.type, perm()));
+        SPH_TRY(adjoint_rhs(tiled(), true, nullptr));
+        SPH_TRY(adjoint_nu(dJ));
         launch(K_ADJ_KICK, sph::k_adj_accum<DIM>, blocks_for(n), st,
-            n, (const double*)(ws + L.lxd), (const double*)(ws + L.lvd), s1.type, perm(), lam_x,
-            lam_u);
+            n, (const double*)lxd(), (const double*)lvd(), s1.type, perm(), lam_x, lam_u);
         return launch_check("k_adj_accum");
     }
 };

@@ -1280,12 +1280,12 @@ __device__ __forceinline__ void gather_one(uint32_t i, uint32_t d, uint32_t key,
 
 // Counting sort, last launch: a wave sorts and gathers the particles of cells
 // [g cpw, (g + 1) cpw), stably (by cell, then by previous index), on its own
-// (no barrier, so that a CU keeps many waves' loads in flight, and a wave of
+// (no barrier after the counting, so that a CU keeps many waves' loads in flight, and a wave of
 // empty cells is gone after one round of loads).
 //  * Its first slot is the number of particles in the cells before: from the
 //    chunk sums of k_cell_sums (scanned by k_sums_scan if there are many), or
-//    (sums == nullptr, small grids) counted here, which costs less than a
-//    launch.
+//    (sums == nullptr, small grids) counted here by the block, which costs
+//    less than a launch.
 //  * The cells' lists go to LDS (to skey, which is written last, if the wave
 //    has more than kSortEntries particles): the table's rows lane by lane,
 //    then lane t < cpw follows what cell t has beyond its row.  Each entry's
@@ -1340,6 +1340,21 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(
     uint32_t* const lo = lo_[w];
     const int64_t g = (int64_t)blockIdx.x * kWaves + w;
     const int64_t c0 = g * SG.cpw;
+    __shared__ uint32_t before_[kWaves];
+    if (!SG.sums) {
+        // particles in the cells before the block's, by all of its waves
+        const uint4* __restrict__ c4 = reinterpret_cast<const uint4*>(cl.counts);
+        uint32_t v = 0;
+#pragma unroll 4
+        for (int k = (int)threadIdx.x; k < (int)(blockIdx.x * (unsigned)(kWaves * SG.cpw) / 4);
+             k += kBlock) {
+            const uint4 q = c4[k];
+            v += (q.x + q.y) + (q.z + q.w);
+        }
+        v = wave_sum(v);
+        if (lane == 0) before_[w] = v;
+        __syncthreads();
+    }
     if (c0 >= SG.ncells) return;
     const bool mine = lane < SG.cpw && c0 + lane < SG.ncells;
     const uint32_t cnt = mine ? cl.counts[c0 + lane] : 0u;
@@ -1356,12 +1371,11 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(
         }
         if (lane == 0) first += SG.sub[g];
     } else {
-        const uint4* __restrict__ c4 = reinterpret_cast<const uint4*>(cl.counts);
-#pragma unroll 4
-        for (int k = lane; k < (int)(c0 / 4); k += 64) {
-            const uint4 v = c4[k];
-            first += (v.x + v.y) + (v.z + v.w);
-        }
+        // ... and in the block's cells before the group's (at most 3 cpw)
+        if (lane < kWaves) first = before_[lane];
+#pragma unroll
+        for (int q = 0; q < kWaves - 1; ++q)
+            if (q < w && lane < SG.cpw) first += cl.counts[c0 - (q + 1) * SG.cpw + lane];
     }
     first = wave_sum(first);
     uint32_t off = cnt;
