@@ -629,30 +629,38 @@ __device__ __forceinline__ uint4 ring_octet(const uint2* myring, uint32_t k8) {
 // The neighbours of one target (float copy pf, union cell uc) among the staged
 // union, in walk order: their union indices go through the ring, and their
 // number is returned.  group(before, now) is called after each group of at
-// most four, row(now) after each row of the stencil, with the counts;
-// entries they leave in the ring are the caller's.  exact(u) is the predicate
-// inside the band.  Entries are appended without branches: every candidate is
-// written at the next free place and the count advances only for accepted
-// ones.
-template <int S, int RING, typename T, typename CFG, typename Exact, typename Group,
-          typename Row>
+// most four with the counts; entries it leaves in the ring are the caller's.
+// exact(u) is the predicate inside the band.  Entries are appended without
+// branches: every candidate is written at the next free place and the count
+// advances only for accepted ones.
+// Instruction issue and the LDS bound it (97% and 90% of the build's time), so
+// the groups must fill the lanes: with half-size cells the rows of a stencil
+// plane form a queue in registers, and a lane that ends a row goes on with its
+// next one while others are still in theirs.  A wave of the 256^3 cube then
+// takes 101 groups instead of the 134 of lanes that wait for the longest row
+// (73 if nothing waited; one queue over all planes would take 85, but 25
+// registers to shift): build 5.90 -> 5.27 ms.  With whole cells the rows are
+// longer and the lanes of a cell read them together; the queue's reads meet
+// more bank conflicts there (75^3 quintic lattice: build 0.39 against 0.36
+// ms), so each row is a loop of its own.
+template <int S, int RING, typename T, typename CFG, typename Exact, typename Group>
 __device__ __forceinline__ uint32_t tile_candidates(const Tiles& TL, const TileMeta<CFG>& M,
                                                     const float4* Pf, const PairConst<T>& C,
                                                     const float4& pf, const int uc[3], bool clip,
-                                                    uint2* myring, Exact&& exact, Group&& group,
-                                                    Row&& row) {
+                                                    uint2* myring, Exact&& exact,
+                                                    Group&& group) {
     // the octets are read back as uint2: the halves may alias them
     typedef uint16_t __attribute__((may_alias)) Half;
     Half* const my = (Half*)myring;
     const float cxf = (float)TL.cen[0], cyf = (float)TL.cen[1], czf = (float)TL.cen[2];
     uint32_t cnt = 0;
-    // the (2S+1)^2 stencil rows in walk order (z planes, then y rows);
-    // loops, not unrolled, so the kernel's code stays small enough for the
-    // instruction cache.  A plane's distance is taken once for its rows,
-    // and the x range in cell units from px_c, the target's x in cells
-    // shifted by the union centre and 1/2 (the clip keeps its margins:
-    // roundings of these forms move it by far less than clip_pad)
+    // the (2S+1)^2 stencil rows in walk order (z planes, then y rows).  A
+    // plane's distance is taken once for its rows, and the x range in cell
+    // units from px_c, the target's x in cells shifted by the union centre
+    // and 1/2 (the clip keeps its margins: roundings of these forms move it
+    // by far less than clip_pad)
     constexpr int NR = 2 * S + 1;
+    constexpr int NQ = S == 2 ? NR : 1;  // rows of a queue
     const float px_c = pf.x * TL.inv_csf[0] + (cxf + 0.5f);
 #pragma unroll 1
     for (int iz = 0; iz < NR; ++iz) {
@@ -663,39 +671,59 @@ __device__ __forceinline__ uint32_t tile_candidates(const Tiles& TL, const TileM
         if (clip && !(w2z > 0.f)) continue;
         const int planec = TL.uw * TL.uh * uz;
 #pragma unroll 1
-        for (int iy = 0; iy < NR; ++iy) {
-            const int uy = uc[1] + iy - S;
-            const float dy =
-                fmaxf(fabsf(pf.y - ((float)uy - cyf) * TL.csf[1]) - 0.5f * TL.csf[1], 0.f);
-            const float w2 = w2z - dy * dy;
-            if (clip && !(w2 > 0.f)) continue;
-            int xa = uc[0] - S, xb = uc[0] + S;
-            if (clip) {
-                const float wc = (__builtin_amdgcn_sqrtf(w2) + TL.clip_pad) * TL.inv_csf[0];
-                xa = max(xa, (int)floorf(px_c - wc));
-                xb = min(xb, (int)floorf(px_c + wc));
-                if (xa > xb) continue;
+        for (int iy0 = 0; iy0 < NR; iy0 += NQ) {
+            // rows with candidates, their first union index and end in the
+            // two halves of a word (0: none)
+            uint32_t rq[NQ] = {};
+#pragma unroll
+            for (int iq = NQ - 1; iq >= 0; --iq) {
+                const int uy = uc[1] + iy0 + iq - S;
+                const float dy =
+                    fmaxf(fabsf(pf.y - ((float)uy - cyf) * TL.csf[1]) - 0.5f * TL.csf[1], 0.f);
+                const float w2 = w2z - dy * dy;
+                int xa = uc[0] - S, xb = uc[0] + S;
+                if (clip) {
+                    const float wc =
+                        (__builtin_amdgcn_sqrtf(fmaxf(w2, 0.f)) + TL.clip_pad) * TL.inv_csf[0];
+                    xa = max(xa, (int)floorf(px_c - wc));
+                    xb = min(xb, (int)floorf(px_c + wc));
+                }
+                if (clip && !(w2 > 0.f)) xb = xa - 1;
+                const int rowc = planec + TL.uw * uy;
+                const uint32_t ua = M.off[rowc + xa];
+                const uint32_t ue = M.off[rowc + max(xa, xb + 1)];
+                const bool some = ua < ue;
+#pragma unroll
+                for (int k = NQ - 1 - iq; k > 0; --k) rq[k] = some ? rq[k - 1] : rq[k];
+                rq[0] = some ? ua | ue << 16 : rq[0];
             }
-            const int rowc = planec + TL.uw * uy;
-            const uint32_t ua = M.off[rowc + xa], ue = M.off[rowc + xb + 1];
-            // candidates four at a time, the next four loaded while these
-            // are tested; those past the row's end (read from the padding or
-            // the next row) are infinitely far
-            uint32_t u = ua;
+            // candidates four at a time, the next four (of this row or the
+            // next) loaded while these are tested; those past the row's end
+            // (read from the padding or the next row) are infinitely far
+            uint32_t u = rq[0] & 0xffffu, ue = rq[0] >> 16;
             float4 c[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) c[q] = Pf[u + q];
 #pragma unroll 1
-            for (; u < ue; u += 4) {
-                const uint32_t lim = ue - u;  // candidates left in the row
+            while (u < ue) {
                 float r2[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float dx = pf.x - c[q].x, ddy = pf.y - c[q].y, ddz = pf.z - c[q].z;
                     r2[q] = dx * dx + ddy * ddy + ddz * ddz;
                 }
+                uint32_t un = u + 4, uen = ue;
+                if constexpr (NQ > 1) {
+                    const bool ends = un >= ue;
+                    un = ends ? rq[1] & 0xffffu : un;
+                    uen = ends ? rq[1] >> 16 : ue;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) c[q] = Pf[u + 4 + q];
+                    for (int k = 1; k < NQ; ++k)
+                        rq[k] = ends ? (k + 1 < NQ ? rq[k + 1] : 0u) : rq[k];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[q] = Pf[un + q];
+                const uint32_t lim = ue - u;  // candidates left in the row
                 uint32_t acc[4];
                 bool band[4];
                 bool anyband = false;
@@ -718,8 +746,9 @@ __device__ __forceinline__ uint32_t tile_candidates(const Tiles& TL, const TileM
                     cnt += acc[q];
                 }
                 group(before, cnt);
+                u = un;
+                ue = uen;
             }
-            row(cnt);
         }
     }
     return cnt;
@@ -813,8 +842,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
                 const uint32_t k8 = before >> 3;
                 if (((before ^ now) & ~7u) && k8 < (cap >> 3))
                     list[tile_octet(i, cap, k8)] = ring_octet<16>(myring, k8);
-            },
-            [](uint32_t) {});
+            });
         // the last, partial octet is filled up with the target itself
         if (cnt <= cap && (cnt & 7)) {
             const uint32_t r = cnt & 7;
@@ -840,7 +868,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
 // 0, to which a target adds a constant: the mixed-precision code of a stencil
 // offset is linear in the two cells, the FP64 code is the neighbour's image
 // alone.  Completed octets of union indices are turned into words and stored,
-// 256 bytes apart (rows of 64 slots), after a row of the stencil that leaves
+// 256 bytes apart (rows of 64 slots), after a group of candidates that leaves
 // some lane with kFlush of them or more, by the lanes of a wave together: at
 // every completed octet some lane or other would take the whole wave through
 // the stores.  The targets of a tile whose union does
@@ -953,9 +981,6 @@ __global__ __launch_bounds__(CfgD::kThreads, 2) void k_tile_nlist(
                 cnt = tile_candidates<S, kRing>(
                     TL, M, Pf, C, pf, uc, clip, myring, exact,
                     [&](uint32_t, uint32_t now) {
-                        if (now - done > kRing - 8) flush(now);  // the ring is nearly full
-                    },
-                    [&](uint32_t now) {
                         if (__builtin_amdgcn_ballot_w64(now - done >= kFlush)) flush(now);
                     });
                 flush(cnt);
