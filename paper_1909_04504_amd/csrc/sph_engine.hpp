@@ -990,7 +990,7 @@ struct Engine {
                              drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(), part,
                              stride);
                 else
-                    launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<S, KERNEL>, wgs, Cfg::kThreads,
+                    launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<S, KERNEL>, wgs, sph::kMomThreads,
                              st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type, cs, ce, tcap(),
                              (const uint4*)list(), lcnt(), s, kick ? 1 : 0, drift ? 1 : 0,
                              0.5 * prm->dt, prm->dt, cells(), flags(), part, stride);

@@ -180,16 +180,6 @@ struct SetupLoads {
     uint32_t s[2], e[2];
     bool in[2];
 };
-// Marks a loaded value as used here and not before: the compiler otherwise
-// moves its first use (and the wait for the load) up to where the load was
-// issued, ahead of loads that were meant to overlap it.
-template <typename V>
-__device__ __forceinline__ void keep_in_flight(V& v) {
-    static_assert(sizeof(V) % 4 == 0, "whole registers");
-    uint32_t* w = reinterpret_cast<uint32_t*>(&v);
-#pragma unroll
-    for (int k = 0; k < (int)(sizeof(V) / 4); ++k) asm volatile("" : "+v"(w[k]));
-}
 __device__ __forceinline__ SetupLoads tile_setup_loads(const Grid& G, const Tiles& TL,
                                                        const int c0[3],
                                                        const uint32_t* __restrict__ cstart,
@@ -1157,16 +1147,21 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_density(
 // its records, then its targets' counts and list heads: about 45% of the
 // pass measured without the pair loops).  Each workgroup therefore takes
 // every P-th tile (P workgroups, one per CU, so that the tiles in flight
-// are P consecutive ones) and issues, with the loads of its tile t's
-// targets, the staging loads of its next tile (whose cell ranges were set
-// up before) and the cell-range loads of the one after: the three round
-// trips overlap.  (They cannot reach past the first wait of the pair loops:
-// the vector memory counter is in order.)  After the pair loops the loaded
-// records and ranges go to the LDS that tile t no longer needs; two tile
-// metas and two cell tables alternate.  The pair loops take half octets at
-// a time, which keeps the staging registers clear of spills.
+// are P consecutive ones).  Its sixteen waves divide the work: eight, two per
+// SIMD, take the tile's targets (about 490 in a box of 6 x 6 x 4 cells), the
+// other eight meanwhile hold the next tile's records (10 registers each, six
+// per thread) and the cell ranges of the one after, and store them to the LDS
+// when tile t no longer needs it; two tile metas and two cell tables
+// alternate.  The loads wait in waves of their own since a wave's loads
+// return in order: held by the target waves they stood before the pair loops'
+// first wait, and their 60 registers beside the pair loops'.  The pair loops
+// take half octets at a time and issue instructions 79% of the time.
+// (256^3 cube: 3.83 ms with the loads in the target waves, 3.64 with the loader
+// waves; 75^3 quintic lattice 0.213 and 0.204.  Padded lists without the
+// entry-by-entry tail, as in FP64: 3.55 and 0.209, not taken.)
+constexpr int kMomThreads = 2 * CfgF::kThreads;
 template <int S, int KERNEL>
-__global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
+__global__ __launch_bounds__(kMomThreads) void k_tile_momentum(
     int n, Grid G, PairConst<float> C, Tiles TL, int cap_union, const int4* __restrict__ pos,
     const float4* __restrict__ vel, const float2* __restrict__ rp,
     const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
@@ -1179,10 +1174,12 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
     __shared__ int4 Pi[CfgF::kCap];
     __shared__ float4 V[CfgF::kCap];
     __shared__ float2 RP[CfgF::kCap];
-    const int tid = (int)threadIdx.x;
-    // tiles w, w + P, w + 2P, ... (P workgroups): the tiles in flight at
-    // any time are P consecutive ones, each XCD's a contiguous run of them
-    const int P = (int)gridDim.x;
+    // set-up and staging thread: 0 .. 511 in the loader waves, the others take
+    // part in the set-up's barriers
+    const int tid = (int)(threadIdx.x ^ (unsigned)CfgF::kThreads);
+    // uniform over a wave, and known to be
+    const bool loader = __builtin_amdgcn_readfirstlane(tid) < CfgF::kThreads;
+    const int NP = (int)gridDim.x;
     const int t0 = xcd_block();
     const int t1 = TL.ntiles;
     if (t0 >= t1) return;  // the whole workgroup
@@ -1198,67 +1195,64 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
         RP[u] = r.rp;
     };
     auto fits = [&](const TileMeta<CfgF>& M) { return M.total <= (uint32_t)cap_union; };
+    // prologue (t = t0 - NP): tile t0 set up; the loop's first round stages it
     int c0[3];
-    // prologue: tile t0 set up and staged, tile t0 + 1 set up
     tile_origin(TL, t0, c0);
     tile_setup(G, TL, c0, cstart, cend, n, MM[0], tid);
-    tile_cellof(TL, MM[0], cellofs[0]);
-    if (fits(MM[0])) {
-        StageRegs<CfgF, Rc> R0;
-        tile_stage_loads(MM[0], cellofs[0], load_rc, R0, tid);
-        tile_stage_store(TL, MM[0], cellofs[0], R0, store_rc, tid);
-    }
-    if (t0 + P < t1) {
-        tile_origin(TL, t0 + P, c0);
-        tile_setup(G, TL, c0, cstart, cend, n, MM[1], tid);  // its barriers also publish the staging
-        tile_cellof(TL, MM[1], cellofs[1]);
-    } else {
-        __syncthreads();
-    }
-    int cur = 0;
-    for (int t = t0; t < t1; t += P) {
-        const TileMeta<CfgF>& M = MM[cur];
-        const TileMeta<CfgF>& MN = MM[cur ^ 1];
-        // issued with the targets' loads: the next tile's staging loads and
-        // the cell-range loads of the one after
-        const bool stage_next = t + P < t1 && fits(MN);
-        StageRegs<CfgF, Rc> R;
-        if (stage_next) tile_stage_loads(MN, cellofs[cur ^ 1], load_rc, R, tid);
-        const bool setup_next2 = t + 2 * P < t1;
-        int c2[3] = {0, 0, 0};
-        SetupLoads sl{};
-        if (setup_next2) {
-            tile_origin(TL, t + 2 * P, c2);
-            sl = tile_setup_loads(G, TL, c2, cstart, cend, tid);
+    tile_cellof<CfgF, kMomThreads>(TL, MM[0], cellofs[0]);
+    // set-up of the tile after the next one into the meta that tile t leaves,
+    // by all waves (the loaders hold its cell ranges); publishes the staging
+    auto set_up = [&](int t, int cur, const SetupLoads& sl) {
+        if (t + 2 * NP < t1) {
+            int c2[3];
+            tile_origin(TL, t + 2 * NP, c2);
+            tile_setup_finish(G, TL, c2, n, sl, MM[cur], tid);
+            tile_cellof<CfgF, kMomThreads>(TL, MM[cur], cellofs[cur]);
+        } else {
+            __syncthreads();
         }
+    };
+    // the two roles meet at the same barriers: one for the diagnostics' sums,
+    // one when tile t's records, meta and cell table are free, and set_up's
+    if (loader) {
+        int cur = 1;
+        for (int t = t0 - NP; t < t1; t += NP, cur ^= 1) {
+            const TileMeta<CfgF>& MN = MM[cur ^ 1];
+            const bool stage_next = t + NP < t1 && fits(MN);
+            SetupLoads sl{};
+            if (t + 2 * NP < t1) {
+                int c2[3];
+                tile_origin(TL, t + 2 * NP, c2);
+                sl = tile_setup_loads(G, TL, c2, cstart, cend, tid);
+            }
+            StageRegs<CfgF, Rc> R;
+            if (stage_next) tile_stage_loads(MN, cellofs[cur ^ 1], load_rc, R, tid);
+            if (diag_part && t >= 0) __syncthreads();
+            __syncthreads();
+            if (stage_next) tile_stage_store(TL, MN, cellofs[cur ^ 1], R, store_rc, tid);
+            set_up(t, cur, sl);
+        }
+        return;
+    }
+    int cur = 1;
+    for (int t = t0 - NP; t < t1; t += NP, cur ^= 1) {
+        const TileMeta<CfgF>& M = MM[cur];
         double dsum[4] = {0.0, 0.0, 0.0, 0.0};
-        const uint32_t nt = M.ntargets;
-        if (fits(M) && nt > 0) {
-            // every global load of a target up front (count, type, the list's
-            // first octets, the epilogue's state); those of a thread's next
-            // target while it works on the current one
-            struct Tgt {
-                uint32_t ui, i, cnt;
-                bool fluid;
-                ListHead head;
-                CloseIn ci;
-            };
-            auto target_loads = [&](uint32_t tt) {
-                Tgt g;
+        if (t >= 0 && fits(M)) {
+            for (uint32_t tt = (uint32_t)(tid - CfgF::kThreads); tt < M.ntargets;
+                 tt += CfgF::kThreads) {
+                // every global load of a target up front (count, type, the
+                // list's first octets, the epilogue's state)
+                uint32_t ui, i;
                 int uc[3];
-                tile_target(TL, M, tt, &g.ui, &g.i, uc);
-                g.cnt = ncnt[g.i];
-                g.fluid = type[g.i] == 0;
-                g.head = tile_list_head(list, g.i, cap);
-                g.ci = close_load<3>((int)g.i, St, drift, diag_part != nullptr);
-                return g;
-            };
-            for (uint32_t tt = threadIdx.x; tt < nt; tt += CfgF::kThreads) {
-                const Tgt cur_t = target_loads(tt);
-                const uint32_t ui = cur_t.ui, i = cur_t.i, cnt = cur_t.cnt;
+                tile_target(TL, M, tt, &ui, &i, uc);
+                const uint32_t cnt = ncnt[i];
+                const bool fluid = type[i] == 0;
+                const ListHead head = tile_list_head(list, i, cap);
+                const CloseIn ci = close_load<3>((int)i, St, drift, diag_part != nullptr);
                 if (cnt > cap) continue;  // the fallback's
                 float acc[3] = {0.f, 0.f, 0.f};
-                if (cur_t.fluid) {
+                if (fluid) {
                     const int4 pi = Pi[ui];
                     const float4 vi = V[ui];
                     const float2 rpi = RP[ui];
@@ -1268,7 +1262,7 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
                         float4 v;
                         float2 rp;
                     };
-                    tile_list_loop<4>(list, i, cap, cnt, cur_t.head,
+                    tile_list_loop<4>(list, i, cap, cnt, head,
                                    [&](uint32_t u) { return Nb{Pi[u], V[u], RP[u]}; },
                                    [&](const Nb& b) {
                                        const Geom<float> g =
@@ -1282,28 +1276,14 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_momentum(
                     acc[2] = az;
                 }
                 double dv[4] = {0.0, 0.0, 0.0, 0.0};
-                momentum_close<3, float>((int)i, acc, cur_t.fluid, St, G, kick, drift, hdt, dt,
-                                         cl, flags, diag_part != nullptr, dv,
-                                         &cur_t.ci);
+                momentum_close<3, float>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, cl,
+                                         flags, diag_part != nullptr, dv, &ci);
                 for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
             }
         }
-        if (diag_part) tile_block_sum<4, CfgF::kThreads>(dsum, diag_part, t, stride);
-        __syncthreads();  // tile t's records, meta and cell table are free
-        if (stage_next) {
-#pragma unroll
-            for (int q = 0; q < StageRegs<CfgF, Rc>::kQ; ++q) keep_in_flight(R.v[q]);
-            tile_stage_store(TL, MN, cellofs[cur ^ 1], R, store_rc, tid);
-        }
-        if (setup_next2) {
-            keep_in_flight(sl.s);
-            keep_in_flight(sl.e);
-            tile_setup_finish(G, TL, c2, n, sl, MM[cur], tid);
-            tile_cellof(TL, MM[cur], cellofs[cur]);  // its barrier publishes the staging
-        } else {
-            __syncthreads();
-        }
-        cur ^= 1;
+        if (diag_part && t >= 0) tile_block_sum<4, CfgF::kThreads>(dsum, diag_part, t, stride);
+        __syncthreads();
+        set_up(t, cur, SetupLoads{});
     }
 }
 
