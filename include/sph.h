@@ -278,18 +278,19 @@ int sph_read_interactions(void* ws, size_t ws_bytes, int64_t* total, int reset, 
 int sph_timer_enable(int on);
 int sph_timer_read(int nslots, const char** names, double* ms, int64_t* launches, int reset);
 
-/* Bytes of the static device scratch of sph_step_noalloc (one copy per device,
- * held until the process ends). */
+/* Limit of sph_step_noalloc: bytes of workspace, counted with three 4-byte
+ * words per particle in place of the sort's tables.  The static device scratch
+ * (one copy per device, held until the process ends) holds those as well, in
+ * 2 * SPH_NOALLOC_SCRATCH_BYTES + 1 MiB. */
 #define SPH_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 
 /* sph_step without a caller workspace, for callers that cannot allocate
  * device memory (code under graph capture, serving loops, harnesses that
- * forbid hipMalloc): the workspace is a static device array of
- * SPH_NOALLOC_SCRATCH_BYTES bytes per device, found with hipGetSymbolAddress
- * on the first call on each device.  Same arguments and results as sph_step
+ * forbid hipMalloc): the workspace is a static device array, found with
+ * hipGetSymbolAddress on the first call on each device.  Same arguments and results as sph_step
  * otherwise; the caller still provides the particle arrays and diag.
- * Allocates nothing.  Returns SPH_EWORKSPACE when sph_workspace_bytes(prm, n,
- * 0) exceeds SPH_NOALLOC_SCRATCH_BYTES.  Every call on a device shares that
+ * Allocates nothing.  Returns SPH_EWORKSPACE when the workspace, counted as
+ * above, exceeds SPH_NOALLOC_SCRATCH_BYTES.  Every call on a device shares that
  * device's array, which keeps the last call's contents: each call clears its
  * flag words and interaction counters first (device-detected conditions are
  * not reported), and calls that overlap on one device race. */

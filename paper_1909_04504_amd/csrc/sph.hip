@@ -7,13 +7,14 @@ using namespace sph_host;
 
 #include <mutex>
 
-constexpr size_t kScratchBytes = SPH_NOALLOC_SCRATCH_BYTES + ((size_t)32 << 20);
-// Static workspace of sph_step_noalloc: SPH_NOALLOC_SCRATCH_BYTES and a
-// margin for the arrays the layout has gained since, so that every size that
-// was taken still is; one copy per device.  Host code never
+// Static workspace of sph_step_noalloc, one copy per device: room for every
+// layout whose limit_bytes are within SPH_NOALLOC_SCRATCH_BYTES (the sort's
+// tables, which those leave out, take at most 8 bytes per cell and 128 per
+// particle, no more than the counted arrays).  Host code never
 // passes this name to a kernel (in host code it is a stand-in, not a device
 // address); it uses the address hipGetSymbolAddress returns for the current
 // device, kept per device below.
+constexpr size_t kScratchBytes = 2 * SPH_NOALLOC_SCRATCH_BYTES + ((size_t)1 << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -157,9 +158,9 @@ int sph_step_noalloc(const sph_params* prm, sph_particles* pa, int64_t nsteps, i
     int64_t ncells;
     SPH_TRY(make_grid(prm, &G, &ncells));
     const Layout L = make_layout(prm, G, pa->n, ncells, 0);
-    if (L.bytes > kScratchBytes)
+    if (L.limit_bytes > SPH_NOALLOC_SCRATCH_BYTES || L.bytes > kScratchBytes)
         return fail(SPH_EWORKSPACE, "the step needs %zu bytes of workspace, the static scratch holds %zu",
-                    L.bytes, kScratchBytes);
+                    L.limit_bytes, (size_t)SPH_NOALLOC_SCRATCH_BYTES);
     void* ws = nullptr;
     SPH_TRY(scratch_address(&ws));
     // the flag words and interaction counters start at zero (a fill kernel,

@@ -467,6 +467,7 @@ struct Layout {
     SlotOff slot;
     size_t slot_bytes, tape;
     size_t bytes;
+    size_t limit_bytes;  // what the static scratch's limit counts (adj_k = 0)
 };
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -593,6 +594,16 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
         L.tape = take(L.slot_bytes * (size_t)adj_k);
     }
     L.bytes = off;
+    // the static scratch's limit counts three words per particle for the sort
+    // instead of its cell tables and links, and tiles in mixed precision only:
+    // what it takes does not depend on how the sort lays its tables out
+    const size_t tiles_counted = p->precision == SPH_FP64 ? 0 : ntiles;
+    const size_t counters = std::max(nlist_shape(n, ncells).blocks, blocks_for(n));
+    L.limit_bytes =
+        off + 3 * align256(4 * N) - (L.start - L.counts2) - (L.perm - L.sub) -
+        (L.counts - L.flags) + align256(16 + 8 * std::max(counters, tiles_counted)) -
+        align256(8 * 4 * std::max<size_t>(blocks_for(n), ntiles + fallback_blocks(n))) +
+        align256(8 * 4 * std::max<size_t>(blocks_for(n), tiles_counted + fallback_blocks(n)));
     return L;
 }
 
