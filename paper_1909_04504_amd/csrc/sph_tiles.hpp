@@ -1295,7 +1295,7 @@ __global__ __launch_bounds__(kMomThreads) void k_tile_momentum(
 // (pair_geom's w): a byte per staged particle, read only in tiles whose
 // union reaches over a face.
 // (160^3 cube, h = 1.5 dx, half-size cells, against the walk build and the
-// passes over global lists: build 1.80 against 4.62 ms, density 0.88 against
+// passes over global lists: build 1.63 against 4.62 ms, density 0.88 against
 // 1.93, momentum 1.77 against 3.90; those gather 80 bytes a neighbour through
 // L1 and L2 at 9 TB/s.  Boxes of 4 x 4 x 4 cells are what 72 bytes a staged
 // particle leaves room for.)
