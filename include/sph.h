@@ -281,7 +281,7 @@ int sph_timer_read(int nslots, const char** names, double* ms, int64_t* launches
 /* Limit of sph_step_noalloc: bytes of workspace, counted with three 4-byte
  * words per particle in place of the sort's tables.  The static device scratch
  * (one copy per device, held until the process ends) holds those as well, in
- * 2 * SPH_NOALLOC_SCRATCH_BYTES + 1 MiB. */
+ * 2.125 * SPH_NOALLOC_SCRATCH_BYTES + 1 MiB. */
 #define SPH_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 
 /* sph_step without a caller workspace, for callers that cannot allocate
