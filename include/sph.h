@@ -278,10 +278,11 @@ int sph_read_interactions(void* ws, size_t ws_bytes, int64_t* total, int reset, 
 int sph_timer_enable(int on);
 int sph_timer_read(int nslots, const char** names, double* ms, int64_t* launches, int reset);
 
-/* Limit of sph_step_noalloc: bytes of workspace, counted with three 4-byte
- * words per particle in place of the sort's tables.  The static device scratch
- * (one copy per device, held until the process ends) holds those as well, in
- * 2.125 * SPH_NOALLOC_SCRATCH_BYTES + 1 MiB. */
+/* Limit of sph_step_noalloc: bytes of workspace, counted with two 4-byte words
+ * per cell and six per particle for the sort and the lists' counts.  The static
+ * device scratch (one copy per device, held until the process ends) has 1/16
+ * more; a call whose usual workspace is larger than that sorts without the
+ * cells' tables. */
 #define SPH_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 
 /* sph_step without a caller workspace, for callers that cannot allocate

@@ -7,16 +7,13 @@ using namespace sph_host;
 
 #include <mutex>
 
-// Static workspace of sph_step_noalloc, one copy per device: room for every
-// layout whose limit_bytes are within SPH_NOALLOC_SCRATCH_BYTES, without FP64
-// tiles if they do not fit.  What those leave out takes at most 9 bytes per cell (two
-// arrays, and a word per four cells) and 128 per particle, where they count 8
-// and 128 or more.  Host code never
+// Static workspace of sph_step_noalloc, one copy per device: room for the plain
+// layout of every call whose limit_bytes are within
+// SPH_NOALLOC_SCRATCH_BYTES.  Host code never
 // passes this name to a kernel (in host code it is a stand-in, not a device
 // address); it uses the address hipGetSymbolAddress returns for the current
 // device, kept per device below.
-constexpr size_t kScratchBytes =
-    2 * SPH_NOALLOC_SCRATCH_BYTES + SPH_NOALLOC_SCRATCH_BYTES / 8 + ((size_t)1 << 20);
+constexpr size_t kScratchBytes = SPH_NOALLOC_SCRATCH_BYTES + kPlainSlack;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -159,16 +156,12 @@ int sph_step_noalloc(const sph_params* prm, sph_particles* pa, int64_t nsteps, i
     sph::Grid G;
     int64_t ncells;
     SPH_TRY(make_grid(prm, &G, &ncells));
-    sph_params q = *prm;
-    Layout L = make_layout(&q, G, pa->n, ncells, 0);
-    if (L.bytes > kScratchBytes && q.precision == SPH_FP64) {
-        // the limit does not count the tiles' counters and partial sums
-        q.pair_tiles = -1;
-        L = make_layout(&q, G, pa->n, ncells, 0);
-    }
+    Layout L = make_layout(prm, G, pa->n, ncells, 0);
     if (L.limit_bytes > SPH_NOALLOC_SCRATCH_BYTES)
         return fail(SPH_EWORKSPACE, "the step needs %zu bytes of workspace, the static scratch holds %zu",
                     L.limit_bytes, (size_t)SPH_NOALLOC_SCRATCH_BYTES);
+    const bool plain = L.bytes > kScratchBytes;
+    if (plain) L = make_layout(prm, G, pa->n, ncells, 0, true);
     void* ws = nullptr;
     SPH_TRY(scratch_address(&ws));
     // the flag words and interaction counters start at zero (a fill kernel,
@@ -177,9 +170,8 @@ int sph_step_noalloc(const sph_params* prm, sph_particles* pa, int64_t nsteps, i
     const int64_t words = (int64_t)(L.counts / 4);
     launch(K_FILL, sph::k_fill_u32, blocks_for(words), st, words, 0u, (uint32_t*)ws);
     SPH_TRY(launch_check("k_fill_u32"));
-    return dispatch(&q, [&](auto A) {
-        return decltype(A)::step(&q, pa, nsteps, prime_accel, ws, kScratchBytes,
-                                 diag, stream);
+    return dispatch(prm, [&](auto A) {
+        return decltype(A)::step(prm, pa, nsteps, prime_accel, ws, kScratchBytes, diag, stream, plain);
     });
 }
 

@@ -413,40 +413,45 @@ struct StateOff {
     size_t x, u, a, m, type, id, rho, p, arho;
 };
 
-// Shape of the sort.  A cell's row in the table (1 << shift slots) holds
-// nearly twice the particles of a lattice at h = 1.3 dx (2D 16 slots for
-// 6.8 particles, 3D half-size cells 8 for 2.2, whole ones 32 for 17.6);
-// grids so sparse that the table would take more than 128 bytes per particle
-// do with chains.  The last launch's cells per wave: about one particle per
-// lane (sparse grids have many empty cells beside full ones, so that the
-// lattice counts where the mean is below it).
+// Shape of the sort: k_cell_gather, or (by_slot) k_cell_place and
+// k_slot_gather, see there.  The latter on sparse grids (more cells than
+// particles), where a cell holds more than 36 particles on average (a row of 64
+// slots would be too short), and on grids of so many cells that
+// k_cell_gather's threads would not fit a launch; `plain` asks for it.
+// k_cell_gather: a cell's row in the table (1 << shift slots) holds nearly
+// twice the particles of a lattice at h = 1.3 dx (2D 16 slots for 6.8
+// particles, 3D half-size cells 8 for 2.2, whole ones 32 for 17.6) or of the
+// mean, if that is more; a wave's cells hold about one particle per lane, and
+// lim of them each fit its LDS.
 // Grids of up to kDirectCells cells count the particles before a block in the
 // block itself (at most 16 rounds of 16 bytes a thread); above, k_cell_sums
 // does.
 constexpr int64_t kDirectCells = 16384;
 struct SortShape {
     int shift, cpw;
-    int64_t ngroups;
+    uint32_t lim;
+    int64_t ngroups;  // entries of sub
     int nblocks;
-    bool sparse;  // k_cell_place and k_slot_gather
+    bool by_slot;
 };
-inline SortShape sort_shape(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells) {
+inline SortShape sort_shape(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells,
+                            bool plain) {
     double occ = 1.0;
     for (int k = 0; k < p->dim; ++k) occ *= 1.3 * G.cs[k] / p->h;
+    const double mean = (double)n / (double)ncells;
+    const bool thin = mean < std::max(1.0, 0.6 * occ) && ncells > kDirectCells;
+    occ = std::max(occ, mean);
     int shift = 3;
     while (shift < 6 && (double)(1 << shift) < 1.8 * occ) ++shift;  // 4 rows: 64 kSortRounds
-    occ = std::max(occ, (double)n / (double)ncells);
     int cpw = 4;
     while (cpw < 64 && 2 * cpw * occ <= 75.0 && (2 * cpw) << shift <= 64 * sph::kSortRounds)
         cpw *= 2;
-    if ((ncells << shift) > 32 * n) shift = -1;
-    while (cpw < 64 && ncells / cpw > ((int64_t)1 << 25)) {
-        cpw *= 2;
-        shift = -1;
-    }
     const int64_t groups = (ncells + cpw - 1) / cpw;
     const int64_t blocks = (groups + sph::kBlock / 64 - 1) / (sph::kBlock / 64);
-    return {shift, cpw, groups, (int)blocks, ncells > n && ncells > kDirectCells};
+    if (plain || thin || mean > 36.0 || groups > ((int64_t)1 << 25))
+        return {-1, (int)sph::kPlaceCells, 0, (ncells + sph::kPlaceCells - 1) / sph::kPlaceCells, 0,
+                true};
+    return {shift, cpw, (uint32_t)(sph::kSortEntries / cpw), groups, (int)blocks, false};
 }
 
 // One recompute-tape slot: the pair records and sort results of one step.
@@ -455,7 +460,8 @@ struct SlotOff {
 };
 
 struct Layout {
-    size_t flags, counts, counts2, head, table, start, chunks, sub, next, tmp, perm, skey, lcnt, list;
+    size_t flags, counts, counts2, head, table, start, chunks, sub, next, listed, rank, tmp, perm, skey,
+        lcnt, list;
     uint32_t cap;
     SortShape sort;
     sph::Tiles tiles, ltiles;
@@ -506,11 +512,16 @@ inline NlistShape nlist_shape(int64_t n, int64_t ncells) {
     return {(unsigned)((waves + per_block - 1) / per_block), kNlistSlots, 1};
 }
 
+// plain: the layout of the static scratch where the usual one is too large,
+// with the sort by slots (no tables) and FP64 passes over global lists: at most
+// limit_bytes + kPlainSlack (4 bytes for every eight cells, of which the limit
+// counts 8 each, and the counters' least number).
+constexpr size_t kPlainSlack = SPH_NOALLOC_SCRATCH_BYTES / 16 + ((size_t)64 << 10);
 inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells,
-                          int64_t adj_k) {
+                          int64_t adj_k, bool plain = false) {
     Layout L;
     std::memset(&L, 0, sizeof L);
-    L.tiles = make_tiles(p, G, n, ncells);
+    if (!(plain && p->precision == SPH_FP64)) L.tiles = make_tiles(p, G, n, ncells);
     const size_t ntiles = (size_t)L.tiles.ntiles;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -545,16 +556,22 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
     L.flags = take(16 + 8 * std::max<size_t>(std::max(nlist_shape(n, ncells).blocks, blocks_for(n)),
                                              std::max<size_t>(ntiles, kTileNlistBlocks)));
     L.ltiles = make_list_tiles(p, G, n, ncells);
-    L.counts = take(4 * (size_t)ncells);
-    L.counts2 = take(4 * (size_t)ncells);
-    L.head = take(4 * (size_t)ncells);
-    L.sort = sort_shape(p, G, n, ncells);
-    L.table = take(L.sort.shift < 0 ? 0 : (size_t)4 * ((size_t)ncells << L.sort.shift));
+    L.sort = sort_shape(p, G, n, ncells, plain);
+    const size_t cells = (size_t)ncells + sph::kSortCtl;
+    L.counts = take(4 * cells);
+    L.counts2 = L.head = L.table = L.next = L.listed = L.counts;  // not used
+    if (!L.sort.by_slot) {
+        L.counts2 = take(4 * cells);
+        L.head = take(4 * (size_t)ncells);
+        L.table = take((size_t)4 * ((size_t)ncells << L.sort.shift));
+        L.next = take(4 * N);
+        L.listed = take(4 * N);
+    }
     L.start = take(4 * ((size_t)ncells + 1));
     L.chunks = take(8 * nchunks);
     L.sub = take(4 * (size_t)L.sort.ngroups);
-    L.next = take(4 * N);
-    L.tmp = take(L.sort.sparse ? 4 * N : 0);
+    L.rank = take(4 * N);
+    L.tmp = take(4 * N);
     L.perm = take(4 * N);
     L.skey = take(4 * N);
     L.cap = list_cap(p, n);
@@ -594,15 +611,17 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
         L.tape = take(L.slot_bytes * (size_t)adj_k);
     }
     L.bytes = off;
-    // the static scratch's limit counts three words per particle for the sort
-    // instead of its cell tables and links, and tiles in mixed precision only:
-    // what it takes does not depend on how the sort lays its tables out
+    // the static scratch's limit: two words per cell and six per particle for
+    // the sort and the lists' counts, tiles in mixed precision only, and the
+    // arrays of one state and its records, so that what it takes does not
+    // depend on how the sort lays its tables out
     const size_t tiles_counted = p->precision == SPH_FP64 ? 0 : ntiles;
     const size_t counters = std::max(nlist_shape(n, ncells).blocks, blocks_for(n));
     L.limit_bytes =
-        off + 3 * align256(4 * N) - (L.start - L.counts2) - (L.perm - L.sub) -
-        (L.counts - L.flags) + align256(16 + 8 * std::max(counters, tiles_counted)) -
-        align256(8 * 4 * std::max<size_t>(blocks_for(n), ntiles + fallback_blocks(n))) +
+        align256(16 + 8 * std::max(counters, tiles_counted)) + align256(4 * (size_t)ncells) +
+        align256(4 * ((size_t)ncells + 1)) + align256(8 * nchunks) + 6 * align256(4 * N) +
+        (L.s1.x - L.list) +  // the lists
+        (L.diag - L.s1.x) +  // state and records
         align256(8 * 4 * std::max<size_t>(blocks_for(n), tiles_counted + fallback_blocks(n)));
     return L;
 }
@@ -715,13 +734,17 @@ struct Engine {
     uint32_t* flags() const { return (uint32_t*)(ws + L.flags); }
     unsigned long long* pairs() const { return (unsigned long long*)(ws + L.flags + 16); }
     uint64_t* chunks() const { return (uint64_t*)(ws + L.chunks); }
-    // two buffers of cell counts: a sort reads one and clears the other, which
-    // the next hash fills
+    // k_cell_gather has two buffers of cell counts: a sort reads one and clears
+    // the other, which the next hash fills (k_slot_gather clears what it read)
     int cbuf = 0;
     uint32_t* counts(int b) const { return (uint32_t*)(ws + (b ? L.counts2 : L.counts)); }
+    // the keys of a sort's listed particles are where its permutation goes in
+    // the end (the tape's permutations are elsewhere)
     sph::CellList cells() const {
-        return {counts(cbuf), (uint32_t*)(ws + L.table), (uint32_t*)(ws + L.head),
-                (uint32_t*)(ws + L.next), L.sort.shift};
+        uint32_t* c = counts(cbuf);
+        return {c, (uint32_t*)(ws + L.table), (uint32_t*)(ws + L.head), (uint32_t*)(ws + L.next),
+                (uint32_t*)(ws + L.listed), (uint32_t*)(ws + L.perm), (uint32_t*)(ws + L.rank),
+                c + ncells, L.sort.lim, L.sort.shift};
     }
     sph::DiagJob diag_job{0, nullptr, nullptr};  // not yet summed
     uint32_t* lcnt() const { return (uint32_t*)(ws + L.lcnt); }
@@ -774,7 +797,8 @@ struct Engine {
 
     int zero_counts() {
         cbuf = 0;
-        launch(K_FILL, sph::k_fill_u32, blocks_for(ncells), st, ncells, 0u, counts(0));
+        const int64_t words = ncells + sph::kSortCtl;
+        launch(K_FILL, sph::k_fill_u32, blocks_for(words), st, words, 0u, counts(0));
         return launch_check("k_fill_u32");
     }
 
@@ -835,13 +859,15 @@ struct Engine {
         SG.ncells = ncells;
         SG.cpw = sh.cpw;
         SG.nblocks = sh.nblocks;
-        SG.chunk_cells = 1;
+        SG.chunk_shift = 0;
+        SG.nchunks = 0;
         SG.scanned = 0;
         SG.sums = SG.sub = nullptr;
         SG.clear = counts(cbuf ^ 1);
+        uint32_t* tmp = (uint32_t*)(ws + L.tmp);
         SG.cs = op.cs;
         SG.ce = op.ce;
-        if (ncells > kDirectCells || sh.sparse) {
+        if (ncells > kDirectCells || sh.by_slot) {
             // chunks of 1,024 cells up to 64 chunks, of 4,096 above
             if (ncells <= 64 * sph::kBlock * sph::kScanItemsShort)
                 SPH_TRY(cell_sums<sph::kScanItemsShort>(&SG));
@@ -850,30 +876,34 @@ struct Engine {
         }
         const sph::GatherOp go{op.records ? 1 : 0, op.copy_derived ? 1 : 0, op.eos ? 1 : 0,
                                op.predict};
-        if (sh.sparse) {
-            launch(K_CELL_PLACE, sph::k_cell_place<DIM>, blocks_for(ncells), st, SG, cells(),
-                   start(), skey(), (uint32_t*)(ws + L.tmp));
+        if (sh.by_slot) {
+            const unsigned cb = blocks_for(ncells);
+            launch(K_CELL_PLACE, sph::k_cell_place, cb + blocks_for(n), st, n, cb, SG, cells(),
+                   start(), skey(), tmp);
             SPH_TRY(launch_check("k_cell_place"));
-            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n), st, n,
-                   (const uint32_t*)(ws + L.tmp), start(), src, dst, G, perm(),
-                   op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(), go);
-            cbuf ^= 1;
+            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n), st, n, tmp, start(), src,
+                   dst, G, perm(), op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(), go,
+                   counts(cbuf));
             return launch_check("k_slot_gather");
         }
         // the diagnostics of the step before go to one more block (of the
         // first launch of the sort)
         const bool dg = diag_job.nparts > 0;
         launch(K_CELL_GATHER, sph::k_cell_gather<DIM, T>, (unsigned)sh.nblocks + (dg ? 1u : 0u), st,
-               n, SG, cells(), src, dst, G, start(), perm(), op.want_perm ? 1 : 0, skey(), pos(),
-               vel(), typetape, C, rp(), go, diag_job);
+               sph::GatherArgs<DIM, T>{n, SG, cells(), src, dst, G, start(), tmp, perm(),
+                                       op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(),
+                                       go, diag_job});
         diag_job.nparts = 0;
         cbuf ^= 1;
         return launch_check("k_cell_gather");
     }
     template <int ITEMS>
     int cell_sums(sph::SortGrid* SG) {
-        SG->chunk_cells = sph::kBlock * ITEMS;
-        const int nch = (int)((ncells + SG->chunk_cells - 1) / SG->chunk_cells);
+        constexpr int64_t chunk = sph::kBlock * ITEMS;
+        static_assert((chunk & (chunk - 1)) == 0, "a power of two");
+        SG->chunk_shift = __builtin_ctzll((unsigned long long)chunk);
+        const int nch = (int)((ncells + chunk - 1) / chunk);
+        SG->nchunks = nch;
         uint32_t* sums = (uint32_t*)chunks();
         uint32_t* sub = (uint32_t*)(ws + L.sub);
         const bool dg = diag_job.nparts > 0;
@@ -1365,13 +1395,13 @@ struct Engine {
 // Common preparation: grid, layout, workspace check, engine.
 template <int DIM, int KERNEL, typename T>
 int make_engine(const sph_params* p, const sph_particles* pa, void* ws, size_t ws_bytes,
-                void* stream, Engine<DIM, KERNEL, T>* E, int64_t adj_k = 0) {
+                void* stream, Engine<DIM, KERNEL, T>* E, int64_t adj_k = 0, bool plain = false) {
     int64_t ncells;
     SPH_TRY(make_grid(p, &E->G, &ncells));
     E->prm = p;
     E->ncells = ncells;
     E->n = (int)pa->n;
-    E->L = make_layout(p, E->G, pa->n, ncells, adj_k);
+    E->L = make_layout(p, E->G, pa->n, ncells, adj_k, plain);
     if (!ws) return fail(SPH_EINVAL, "workspace is NULL");
     if ((uintptr_t)ws % 256 != 0) return fail(SPH_EINVAL, "workspace must be 256-byte aligned");
     if (ws_bytes < E->L.bytes)
@@ -1400,7 +1430,7 @@ struct Api {
                          const uint32_t* ce, int64_t cap, int64_t* off, int32_t* nbr,
                          int64_t* total, void* ws, size_t wb, void* st);
     static int step(const sph_params* p, sph_particles* pa, int64_t nsteps, int prime, void* ws,
-                    size_t wb, double* diag, void* st);
+                    size_t wb, double* diag, void* st, bool plain = false);
     static int step_backward(const sph_params* p, const sph_particles* ck, int64_t k,
                              const double* lin, double* lout, double* dJ, void* ws, size_t wb,
                              void* st);
@@ -1456,9 +1486,9 @@ int Api<DIM, KERNEL, T>::neighbors(const sph_params* p, const sph_particles* pa,
 
 template <int DIM, int KERNEL, typename T>
 int Api<DIM, KERNEL, T>::step(const sph_params* p, sph_particles* pa, int64_t nsteps, int prime,
-                              void* ws, size_t wb, double* diag, void* st) {
+                              void* ws, size_t wb, double* diag, void* st, bool plain) {
     Engine<DIM, KERNEL, T> E;
-    SPH_TRY(make_engine(p, pa, ws, wb, st, &E));
+    SPH_TRY(make_engine(p, pa, ws, wb, st, &E, 0, plain));
     if (p->scheme == SPH_SCHEME_CONTINUITY) return E.step_continuity(pa, nsteps, prime, diag);
     return E.step(pa, nsteps, prime, diag);
 }

@@ -10,11 +10,12 @@
 //  * Particles are kept sorted by cell key, so the particles of a stencil row
 //    of cells are contiguous and every cell walk reads contiguous,
 //    cache-resident slot ranges.  The sort is a counting sort on cell keys:
-//    integer atomics count the particles of each cell and chain them, and one
-//    launch (two on large grids) turns counts into cell offsets, follows the
-//    chains of a block's cells and gathers their particles; a per-cell rank
-//    (number of smaller previous indices in the same cell) makes the result
-//    identical to a stable sort, hence deterministic.
+//    integer atomics count the particles of each cell and list them, and one
+//    launch (up to 16,384 cells), two (dense grids above), three (sparse grids
+//    and full cells), or one more above 1,048,576 cells turn counts into cell
+//    offsets and gather the particles; a per-cell rank (number of smaller
+//    previous indices in the same cell) makes the result identical to a
+//    stable sort, hence deterministic.
 //  * Pair records are packed per sorted slot: the position record, the
 //    velocity as a 4-vector and (rho, P = p/rho^2) as a 2-vector (in 2D
 //    (rho, P) ride in the velocity record and the particle type in the
@@ -905,17 +906,28 @@ __device__ __forceinline__ void for_each_neighbor(
 
 // ---------------------------------------------------------------------------
 // Particles by cell for the next sort, in no particular order (the sort
-// ranks them): counts[c] particles, the first `slots` of them in row c of
-// table, any further ones (a cell far fuller than the lattice's) chained from
-// head[c] by next[i].  Chains are followed for a known number of steps, so
-// only counts has to be cleared.
+// ranks them): counts[c] particles in cell c.  Two forms:
+//  * shift < 0 (grids that k_cell_place sorts): each particle's cell and its
+//    number of arrival there, key[i] and rank[i].
+//  * shift >= 0 (grids that k_cell_gather sorts): the first 1 << shift of a
+//    cell are in row c of table, the next ones up to lim chained from head[c]
+//    by next[i] (a cell fuller than the lattice's; chains are followed for a
+//    known number of steps, so only counts has to be cleared).  Any further
+//    ones (particles heaped up in a cell) are entries e < over[0] of listed
+//    (the particle), key and rank.
 struct CellList {
     uint32_t* __restrict__ counts;
     uint32_t* __restrict__ table;
     uint32_t* __restrict__ head;
     uint32_t* __restrict__ next;
-    int shift;  // slots = 1 << shift, or 0 for shift < 0 (chains only)
+    uint32_t* __restrict__ listed;
+    uint32_t* __restrict__ key;
+    uint32_t* __restrict__ rank;
+    uint32_t* over;  // kSortCtl words behind counts: entries listed, and k_cell_gather's
+    uint32_t lim;
+    int shift;
 };
+constexpr int kSortCtl = 4;
 
 // Adds particle i to its cell (active lanes of the wave).  Lanes with the
 // same cell form a group: its first lane takes the group's places with one
@@ -935,10 +947,24 @@ __device__ __forceinline__ void cell_push(uint32_t key, uint32_t i, const CellLi
     uint32_t old = 0;
     if (rank == 0) old = atomicAdd(&cl.counts[key], (uint32_t)__popcll(mine));
     old = (uint32_t)__shfl((int)old, __ffsll((long long)mine) - 1, 64) + (uint32_t)rank;
-    if (cl.shift >= 0 && old < (1u << cl.shift))
+    if (cl.shift < 0) {
+        cl.key[i] = key;
+        cl.rank[i] = old;
+    } else if (old < (1u << cl.shift)) {
         cl.table[((size_t)key << cl.shift) + old] = i;
-    else
+    } else if (old < cl.lim) {
         cl.next[i] = atomicExch(&cl.head[key], i);
+    } else {
+        // one addition for the wave's lanes that are here
+        const unsigned long long m = __ballot(1);
+        const int first = __ffsll((long long)m) - 1;
+        uint32_t e = 0;
+        if (lane == first) e = atomicAdd(cl.over, (uint32_t)__popcll(m));
+        e = (uint32_t)__shfl((int)e, first, 64) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        cl.listed[e] = i;
+        cl.key[e] = key;
+        cl.rank[e] = old;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1185,6 +1211,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_sums(const uint32_t* __restrict
 // Many chunk sums (more than kWaveSums): their exclusive scan, in place, by
 // one block, so that the waves of k_cell_gather read one each.
 constexpr int kWaveSums = 256;
+constexpr uint32_t kPlaceCells = 8;  // cells per entry of sub on grids that k_cell_place sorts
 static __global__ __launch_bounds__(kBlock) void k_sums_scan(int nchunks,
                                                              uint32_t* __restrict__ sums) {
     uint32_t run = 0;
@@ -1278,6 +1305,29 @@ __device__ __forceinline__ void gather_one(uint32_t i, uint32_t d, uint32_t key,
     }
 }
 
+// One slot s of a sort whose particles are grouped by cell (tmp; skey: the
+// slot's cell): ranked among its cell's, and gathered.  Returns whether it is
+// the cell's first.
+template <int DIM, typename T>
+__device__ __forceinline__ bool slot_one(uint32_t s, const uint32_t* tmp, const uint32_t* start,
+                                         const uint32_t* skey, uint32_t* perm, int want_perm,
+                                         const State& src, const State& dst, const Grid& G,
+                                         typename Rec<T>::type* __restrict__ pos,
+                                         typename Vec4<T>::type* __restrict__ vel,
+                                         uint8_t* __restrict__ type_tape, const PairConst<T>& C,
+                                         typename Vec2<T>::type* __restrict__ rp,
+                                         const GatherOp& op) {
+    const uint32_t i = tmp[s];
+    const uint32_t key = skey[s];
+    const uint32_t b = start[key], e = start[key + 1];
+    uint32_t rank = 0;
+    for (uint32_t t = b; t < e; ++t) rank += tmp[t] < i ? 1u : 0u;
+    const uint32_t d = b + rank;
+    if (want_perm) perm[d] = i;
+    gather_one<DIM, T>(i, d, key, src, dst, G, pos, vel, type_tape, C, rp, op);
+    return rank == 0;
+}
+
 // Counting sort, last launch: a wave sorts and gathers the particles of cells
 // [g cpw, (g + 1) cpw), stably (by cell, then by previous index), on its own
 // (no barrier after the counting, so that a CU keeps many waves' loads in flight, and a wave of
@@ -1286,22 +1336,28 @@ __device__ __forceinline__ void gather_one(uint32_t i, uint32_t d, uint32_t key,
 //    chunk sums of k_cell_sums (scanned by k_sums_scan if there are many), or
 //    (sums == nullptr, small grids) counted here by the block, which costs
 //    less than a launch.
-//  * The cells' lists go to LDS (to skey, which is written last, if the wave
-//    has more than kSortEntries particles): the table's rows lane by lane,
-//    then lane t < cpw follows what cell t has beyond its row.  Each entry's
-//    rank in its cell is the number of smaller ones.
+//  * The cells' lists go to LDS: the table's rows lane by lane, then lane
+//    t < cpw follows what cell t has beyond its row.  Each entry's rank in its
+//    cell is the number of smaller ones.
 //  * The slots are then taken in order: the state is gathered from src into
 //    dst, with the pair records packed (records) and, with eos, rho and the
 //    EOS records of the continuity scheme formed.
 // Writes start (first slot of every cell, and n), and clears the counts of
-// the other buffer for the next sort's chains.
-constexpr int kSortEntries = 384;
+// the other buffer for the next sort's lists.
+//
+// With particles heaped up in some cell (over[0] > 0: more than lim there, and
+// its wave would have them to itself: 4,000 took 20 ms, 0.35 now) the launch
+// goes in three parts instead, each spread over several blocks (heaped_sort):
+// the lists' particles go to their cells' slots, then the listed ones, then
+// each slot is ranked and gathered by a thread of its own.
+constexpr int kSortEntries = 768;
 constexpr int kSortRounds = 4;  // table entries of a wave's cells: at most 64 kSortRounds
 struct SortGrid {
     int64_t ncells;
     int cpw;             // cells per wave (a power of two in [4, 64])
     int nblocks;
-    int chunk_cells;     // cells per chunk of sums
+    int chunk_shift;     // cells per chunk of sums: 1 << chunk_shift
+    int nchunks;
     int scanned;         // sums are scanned
     const uint32_t* sums;
     const uint32_t* sub;
@@ -1319,34 +1375,29 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
-template <int DIM, typename T>
-__global__ __launch_bounds__(kBlock) void k_cell_gather(
-    int n, SortGrid SG, CellList cl, State src, State dst, Grid G, uint32_t* __restrict__ start,
-    uint32_t* perm, int want_perm, uint32_t* skey, typename Rec<T>::type* __restrict__ pos,
-    typename Vec4<T>::type* __restrict__ vel, uint8_t* __restrict__ type_tape, PairConst<T> C,
-    typename Vec2<T>::type* __restrict__ rp, GatherOp op, DiagJob job) {
+
+// The cells of one wave of k_cell_gather: the first of them, its particles
+// and their place within the group (lane t: cell c0 + t), the group's first
+// slot and total.  Every thread of block blk calls it (before_: one word of
+// LDS per wave).
+struct CellGroup {
+    int64_t c0;
+    bool mine;
+    uint32_t cnt, off, first, total;
+};
+__device__ __forceinline__ CellGroup cell_group(int blk, const SortGrid& SG, const CellList& cl,
+                                                uint32_t* start, uint32_t* before_) {
     constexpr int kWaves = kBlock / 64;
-    __shared__ uint32_t ent_[kWaves][kSortEntries], sorted_[kWaves][kSortEntries];
-    __shared__ uint8_t cellof_[kWaves][kSortEntries];
-    __shared__ uint32_t lo_[kWaves][65];
-    if ((int)blockIdx.x == SG.nblocks) {
-        diag_sum<DIM>(job.nparts, job.part, job.out);
-        return;
-    }
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
-    uint32_t* const ent = ent_[w];
-    uint32_t* const sorted = sorted_[w];
-    uint8_t* const cellof = cellof_[w];
-    uint32_t* const lo = lo_[w];
-    const int64_t g = (int64_t)blockIdx.x * kWaves + w;
-    const int64_t c0 = g * SG.cpw;
-    __shared__ uint32_t before_[kWaves];
+    CellGroup g;
+    const int64_t gi = (int64_t)blk * kWaves + w;
+    g.c0 = gi * SG.cpw;
     if (!SG.sums) {
         // particles in the cells before the block's, by all of its waves
         const uint4* __restrict__ c4 = reinterpret_cast<const uint4*>(cl.counts);
         uint32_t v = 0;
 #pragma unroll 4
-        for (int k = (int)threadIdx.x; k < (int)(blockIdx.x * (unsigned)(kWaves * SG.cpw) / 4);
+        for (int k = (int)threadIdx.x; k < (int)((unsigned)blk * (unsigned)(kWaves * SG.cpw) / 4);
              k += kBlock) {
             const uint4 q = c4[k];
             v += (q.x + q.y) + (q.z + q.w);
@@ -1355,13 +1406,14 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(
         if (lane == 0) before_[w] = v;
         __syncthreads();
     }
-    if (c0 >= SG.ncells) return;
-    const bool mine = lane < SG.cpw && c0 + lane < SG.ncells;
-    const uint32_t cnt = mine ? cl.counts[c0 + lane] : 0u;
+    const bool in = g.c0 < SG.ncells;
+    g.mine = in && lane < SG.cpw && g.c0 + lane < SG.ncells;
+    g.cnt = g.mine ? cl.counts[g.c0 + lane] : 0u;
     // particles in the cells before this group's (summed over the lanes)
     uint32_t first = 0;
-    if (SG.sums) {
-        const int chunk = (int)(c0 / SG.chunk_cells);
+    if (!in) {
+    } else if (SG.sums) {
+        const int chunk = (int)(g.c0 >> SG.chunk_shift);
         if (SG.scanned) {
             if (lane == 0) first = SG.sums[chunk];
         } else {
@@ -1369,162 +1421,300 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(
             for (int q = 0; q < kWaveSums / 64; ++q)  // all in flight
                 if (q * 64 + lane < chunk) first += SG.sums[q * 64 + lane];
         }
-        if (lane == 0) first += SG.sub[g];
+        if (lane == 0) first += SG.sub[gi];
     } else {
         // ... and in the block's cells before the group's (at most 3 cpw)
         if (lane < kWaves) first = before_[lane];
 #pragma unroll
         for (int q = 0; q < kWaves - 1; ++q)
-            if (q < w && lane < SG.cpw) first += cl.counts[c0 - (q + 1) * SG.cpw + lane];
+            if (q < w && lane < SG.cpw) first += cl.counts[g.c0 - (q + 1) * SG.cpw + lane];
     }
-    first = wave_sum(first);
-    uint32_t off = cnt;
+    g.first = wave_sum(first);
+    uint32_t off = g.cnt;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const uint32_t o = (uint32_t)__shfl_up((int)off, d, 64);
         if (lane >= d) off += o;
     }
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)off, 63);
-    off -= cnt;
-    if (mine) {
-        start[c0 + lane] = first + off;
-        SG.clear[c0 + lane] = 0u;
+    g.total = (uint32_t)__builtin_amdgcn_readlane((int)off, 63);
+    g.off = off - g.cnt;
+    if (g.mine) {
+        const int64_t c = g.c0 + lane;
+        start[c] = g.first + g.off;
+        SG.clear[c] = 0u;
         if (SG.cs) {
-            SG.cs[c0 + lane] = first + off;
-            SG.ce[c0 + lane] = first + off + cnt;
+            SG.cs[c] = g.first + g.off;
+            SG.ce[c] = g.first + g.off + g.cnt;
         }
-        if (c0 + lane == SG.ncells - 1) start[SG.ncells] = first + off + cnt;
-    }
-    if (total == 0) return;
-    lo[lane] = off;
-    if (lane == 0) lo[64] = total;
-    const bool fits = total <= (uint32_t)kSortEntries;
-    auto put = [&](uint32_t at, uint32_t i, int cell) {
-        if (fits) {
-            ent[at] = i;
-            cellof[at] = (uint8_t)cell;
-        } else {
-            skey[first + at] = i;
-        }
-    };
-    const uint32_t row = cl.shift >= 0 ? 1u << cl.shift : 0u;
-    if (row) {
-        wave_sync();  // lo
-        uint32_t v[kSortRounds];
+        if (c == SG.ncells - 1) {
+            start[SG.ncells] = g.first + g.off + g.cnt;
 #pragma unroll
-        for (int q = 0; q < kSortRounds; ++q) {
-            const uint32_t e = (uint32_t)(q * 64 + lane), c = e >> cl.shift;
+            for (int k = 0; k < kSortCtl; ++k) SG.clear[SG.ncells + k] = 0u;
+        }
+    }
+    return g;
+}
+// put(k, i, t) for the k-th particle i of the group (cell c0 + t): its cells'
+// rows, then their chains (lo: 65 words of LDS, the groups' offsets; ROUNDS:
+// the rows' loads are all in flight, else one round after the other).
+template <int ROUNDS, typename Put>
+__device__ __forceinline__ void cell_entries(const CellGroup& g, const SortGrid& SG,
+                                             const CellList& cl, uint32_t* lo, Put&& put) {
+    const int lane = (int)threadIdx.x & 63;
+    lo[lane] = g.off;
+    if (lane == 0) lo[64] = g.total;
+    const uint32_t row = 1u << cl.shift;
+    wave_sync();  // lo
+#pragma unroll 1
+    for (int q0 = 0; q0 < kSortRounds; q0 += ROUNDS) {
+        uint32_t v[ROUNDS];
+#pragma unroll
+        for (int q = 0; q < ROUNDS; ++q) {
+            const uint32_t e = (uint32_t)((q0 + q) * 64 + lane), c = e >> cl.shift;
             const uint32_t k = e & (row - 1u);
             if (c < (uint32_t)SG.cpw && k < lo[c + 1] - lo[c])
-                v[q] = cl.table[((size_t)c0 << cl.shift) + e];
+                v[q] = cl.table[((size_t)g.c0 << cl.shift) + e];
         }
 #pragma unroll
-        for (int q = 0; q < kSortRounds; ++q) {
-            const uint32_t e = (uint32_t)(q * 64 + lane), c = e >> cl.shift;
+        for (int q = 0; q < ROUNDS; ++q) {
+            const uint32_t e = (uint32_t)((q0 + q) * 64 + lane), c = e >> cl.shift;
             const uint32_t k = e & (row - 1u);
             if (c < (uint32_t)SG.cpw && k < lo[c + 1] - lo[c]) put(lo[c] + k, v[q], (int)c);
         }
     }
-    if (cnt > row) {
-        uint32_t i = cl.head[c0 + lane];
-        for (uint32_t k = row; k < cnt; ++k) {
-            put(off + k, i, lane);
+    const uint32_t chained = g.cnt < cl.lim ? g.cnt : cl.lim;
+    if (chained > row) {
+        uint32_t i = cl.head[g.c0 + lane];
+        for (uint32_t k = row; k < chained; ++k) {
+            put(g.off + k, i, lane);
             i = cl.next[i];
         }
-    }
-    wave_sync();
-    // cell of slot s of a wave whose entries are not in LDS
-    auto find = [&](uint32_t s) {
-        int a = 0, b = 64;
-        while (b - a > 1) {
-            const int m = (a + b) >> 1;
-            if (lo[m] <= s) a = m; else b = m;
-        }
-        return a;
-    };
-    for (uint32_t s = lane; s < total; s += 64) {
-        const int t = fits ? cellof[s] : find(s);
-        const uint32_t b = lo[t], e = lo[t + 1];
-        uint32_t rank = 0;
-        if (fits) {
-            const uint32_t v = ent[s];
-            for (uint32_t k = b; k < e; ++k) rank += ent[k] < v ? 1u : 0u;
-            sorted[b + rank] = v;
-        } else {
-            const uint32_t v = skey[first + s];
-            for (uint32_t k = b; k < e; ++k) rank += skey[first + k] < v ? 1u : 0u;
-            perm[first + b + rank] = v;
-        }
-    }
-    wave_sync();
-    for (uint32_t s = lane; s < total; s += 64) {
-        const uint32_t i = fits ? sorted[s] : perm[first + s];
-        const uint32_t key = (uint32_t)c0 + (uint32_t)(fits ? cellof[s] : find(s));
-        const uint32_t d = first + s;
-        if (fits && want_perm) perm[d] = i;
-        skey[d] = key;
-        gather_one<DIM, T>(i, d, key, src, dst, G, pos, vel, type_tape, C, rp, op);
     }
 }
 
-// Sparse grids (more cells than particles): the last launch in two, since
-// k_cell_gather would be mostly waves of empty cells (a workgroup costs about
-// 2 ns however little it does: 2D dam break at dx = 0.1/32, 351k cells for
-// 217k particles, 20.4 us in one launch).  k_cell_place: one cell per thread,
-// start, and the cell's list to its slots of tmp with the cell key in skey;
-// k_slot_gather: one slot per thread, ranked among its cell's.
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_cell_place(SortGrid SG, CellList cl,
-                                                       uint32_t* __restrict__ start,
-                                                       uint32_t* __restrict__ skey,
-                                                       uint32_t* __restrict__ tmp) {
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool mine = c < SG.ncells;
-    const uint32_t cnt = mine ? cl.counts[c] : 0u;
-    // particles before the block: of the chunks, and of the chunk's cells
-    const int64_t c0 = (int64_t)blockIdx.x * kBlock;
-    const int chunk = (int)(c0 / SG.chunk_cells);
-    uint32_t first = 0;
-    if (SG.scanned) {
-        if (threadIdx.x == 0) first = SG.sums[chunk];
-    } else if ((int)threadIdx.x < chunk) {  // at most kWaveSums = kBlock of them
-        first = SG.sums[threadIdx.x];
-    }
-    static_assert(kWaveSums <= kBlock, "one sum per thread");
-    if (threadIdx.x == 0) first += SG.sub[c0 / SG.cpw];
-    // both sums in one scan: the offsets in the low half, the total in the high
-    uint64_t total;
+// Arguments of k_cell_gather.
+template <int DIM, typename T>
+struct GatherArgs {
+    int n;
+    SortGrid SG;
+    CellList cl;
+    State src, dst;
+    Grid G;
+    uint32_t *start, *tmp, *perm;
+    int want_perm;
+    uint32_t* skey;
+    typename Rec<T>::type* pos;
+    typename Vec4<T>::type* vel;
+    uint8_t* type_tape;
+    PairConst<T> C;
+    typename Vec2<T>::type* rp;
+    GatherOp op;
+    DiagJob job;
+};
+
+// k_cell_gather with particles heaped up (the first heaped_blocks of its
+// blocks).  The roles, numbered in order, are taken one
+// at a time from a counter (over[1]): the first put the groups' rows and
+// chains to their slots, the next ones the listed particles (slots from start,
+// complete then), the last ones gather the slots.  A role waits only for roles
+// of lower numbers to end (over[2] and over[3] count the ended ones).  Those
+// have been taken, by blocks that are running and hold no other role, and the
+// lowest unfinished one waits for nothing: so every wait ends, in whatever
+// order the blocks start.  Few blocks, since the counter, the waits and the
+// write-back of the L2 at the end of a writing role cost more than they share
+// (200 particles in one of 24^3 cells: 91 us a sort with 256 blocks and 128
+// writing roles, 147 with 1,024 and 512; 200 in one of 400^2 cells: 240 and
+// 219, 204 with 512 and 256).
+// A function of its own, which reads the kernel's arguments from their segment:
+// inlined, its registers made every sort 1.2 us longer.
+__device__ __forceinline__ uint32_t heaped_blocks(uint32_t blocks) {
+    const uint32_t b = blocks / 4;
+    return b < 256u ? 256u : (b < 512u ? b : 512u);
+}
+template <int DIM, typename T>
+__device__ __attribute__((noinline)) void heaped_sort(uint32_t over_, uint64_t args) {
+    typedef const GatherArgs<DIM, T> __attribute__((address_space(4))) Args;
+    const uint32_t over = (uint32_t)__builtin_amdgcn_readfirstlane((int)over_);
     const uint64_t at =
-        block_exclusive_scan<uint64_t>(((uint64_t)first << 32) | (uint64_t)cnt, &total);
-    const uint32_t b = (uint32_t)(total >> 32) + (uint32_t)at;
-    if (!mine) return;
-    start[c] = b;
-    SG.clear[c] = 0u;
-    if (SG.cs) {
-        SG.cs[c] = b;
-        SG.ce[c] = b + cnt;
-    }
-    if (c == SG.ncells - 1) start[SG.ncells] = b + cnt;
-    if (cnt == 0) return;
-    const uint32_t row = cl.shift >= 0 ? 1u << cl.shift : 0u;
-    const uint32_t m = cnt < row ? cnt : row;
-    const uint4* __restrict__ r4 =
-        reinterpret_cast<const uint4*>(cl.table + (row ? (size_t)c << cl.shift : 0));
-    for (uint32_t k = 0; k < m; k += 4) {  // rows are 32 bytes at least
-        const uint4 v = r4[k / 4];
-        tmp[b + k] = v.x;
-        if (k + 1 < m) tmp[b + k + 1] = v.y;
-        if (k + 2 < m) tmp[b + k + 2] = v.z;
-        if (k + 3 < m) tmp[b + k + 3] = v.w;
-    }
-    if (cnt > row) {
-        uint32_t i = cl.head[c];
-        for (uint32_t k = row; k < cnt; ++k) {
-            tmp[b + k] = i;
-            i = cl.next[i];
+        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(args >> 32)) << 32) |
+        (uint32_t)__builtin_amdgcn_readfirstlane((int)args);
+    const GatherArgs<DIM, T>& A = *(const GatherArgs<DIM, T>*)(Args*)at;
+    __shared__ uint32_t lo_[kBlock / 64][65], before_[kBlock / 64];
+    __shared__ uint32_t role_;
+    uint32_t* const lo = lo_[threadIdx.x >> 6];
+    const uint32_t n = (uint32_t)A.n, blocks = (uint32_t)A.SG.nblocks;
+    const uint32_t most = heaped_blocks(blocks);
+    const uint32_t ra = blocks < most / 2 ? blocks : most / 2;
+    const uint32_t lb = (over + kBlock - 1) / kBlock, rb = lb < 64u ? lb : 64u;
+    const uint32_t sb = (n + kBlock - 1) / kBlock, rc = sb < most ? sb : most;
+    // the block's writes are seen by every block that waited for this role:
+    // each wave's are complete before the barrier, one thread's fence after it
+    // writes them back and comes before the count
+    auto ended = [&](uint32_t* count) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __threadfence();
+            atomicAdd(count, 1u);
         }
+    };
+    auto wait = [&](uint32_t* count, uint32_t all) {
+        if (threadIdx.x == 0) {
+            while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all)
+                __builtin_amdgcn_s_sleep(32);
+            __threadfence();
+        }
+        __syncthreads();
+    };
+    auto take = [&] {
+        __syncthreads();  // role_ has been read, before_ and lo are free
+        if (threadIdx.x == 0) role_ = atomicAdd(A.cl.over + 1, 1u);
+        __syncthreads();
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)role_);
+    };
+    uint32_t r = take();
+    for (; r < ra; r = take()) {
+        for (uint32_t b = r; b < blocks; b += ra) {
+            const CellGroup g = cell_group((int)b, A.SG, A.cl, A.start, before_);
+            if (g.total)
+                cell_entries<1>(g, A.SG, A.cl, lo, [&](uint32_t k, uint32_t i, int t) {
+                    A.tmp[g.first + k] = i;
+                    A.skey[g.first + k] = (uint32_t)g.c0 + (uint32_t)t;
+                });
+            __syncthreads();  // before_
+        }
+        ended(A.cl.over + 2);
     }
-    for (uint32_t k = 0; k < cnt; ++k) skey[b + k] = (uint32_t)c;
+    for (; r < ra + rb; r = take()) {
+        wait(A.cl.over + 2, ra);
+        for (uint32_t e = (r - ra) * kBlock + threadIdx.x; e < over; e += rb * kBlock) {
+            const uint32_t key = A.cl.key[e];
+            const uint32_t s = A.start[key] + A.cl.rank[e];
+            A.tmp[s] = A.cl.listed[e];
+            A.skey[s] = key;
+        }
+        ended(A.cl.over + 3);
+    }
+    if (r < ra + rb + rc) wait(A.cl.over + 3, rb);
+    for (; r < ra + rb + rc; r = take())
+        for (uint32_t s = (r - ra - rb) * kBlock + threadIdx.x; s < n; s += rc * kBlock)
+            slot_one<DIM, T>(s, A.tmp, A.start, A.skey, A.perm, A.want_perm, A.src, A.dst, A.G, A.pos,
+                             A.vel, A.type_tape, A.C, A.rp, A.op);
+}
+
+template <int DIM, typename T>
+__global__ __launch_bounds__(kBlock) void k_cell_gather(GatherArgs<DIM, T> A) {
+    constexpr int kWaves = kBlock / 64;
+    __shared__ uint32_t ent_[kWaves][kSortEntries], sorted_[kWaves][kSortEntries];
+    __shared__ uint8_t cellof_[kWaves][kSortEntries];
+    __shared__ uint32_t lo_[kWaves][65];
+    __shared__ uint32_t before_[kWaves];
+    if ((int)blockIdx.x == A.SG.nblocks) {
+        diag_sum<DIM>(A.job.nparts, A.job.part, A.job.out);
+        return;
+    }
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    uint32_t* const ent = ent_[w];
+    uint32_t* const sorted = sorted_[w];
+    uint8_t* const cellof = cellof_[w];
+    uint32_t* const lo = lo_[w];
+    const uint32_t over = A.cl.over[0];
+    const CellGroup g = cell_group((int)blockIdx.x, A.SG, A.cl, A.start, before_);
+    if (over) {
+        if (blockIdx.x < heaped_blocks((uint32_t)A.SG.nblocks))
+            heaped_sort<DIM, T>(over, (uint64_t)__builtin_amdgcn_kernarg_segment_ptr());
+        return;
+    }
+    if (g.total == 0) return;
+    cell_entries<kSortRounds>(g, A.SG, A.cl, lo, [&](uint32_t k, uint32_t i, int t) {
+        ent[k] = i;
+        cellof[k] = (uint8_t)t;
+    });
+    wave_sync();
+    for (uint32_t s = lane; s < g.total; s += 64) {
+        const int t = cellof[s];
+        const uint32_t b = lo[t], e = lo[t + 1];
+        const uint32_t v = ent[s];
+        uint32_t rank = 0;
+        for (uint32_t k = b; k < e; ++k) rank += ent[k] < v ? 1u : 0u;
+        sorted[b + rank] = v;
+    }
+    wave_sync();
+    for (uint32_t s = lane; s < g.total; s += 64) {
+        const uint32_t i = sorted[s];
+        const uint32_t key = (uint32_t)g.c0 + (uint32_t)cellof[s];
+        const uint32_t d = g.first + s;
+        if (A.want_perm) A.perm[d] = i;
+        A.skey[d] = key;
+        gather_one<DIM, T>(i, d, key, A.src, A.dst, A.G, A.pos, A.vel, A.type_tape, A.C, A.rp, A.op);
+    }
+}
+
+// Other grids: the last launch in two.  k_cell_place: a thread per cell writes
+// its start (the first cell_blocks blocks), a thread per particle takes the
+// slot of its cell that its number of arrival gives, whose first slot it
+// counts itself (the chunk, the eight-cell group in the chunk and the cells
+// before its own in the group), so that it need not wait for start.
+// k_slot_gather: one slot per thread, ranked among its cell's; the cell's
+// first clears its count for the next sort.  For
+//  * sparse grids, where k_cell_gather would be mostly waves of empty cells (a
+//    workgroup costs about 2 ns however little it does: 2D dam break at
+//    dx = 0.1/32, 351k cells for 217k particles, 20.4 us in one launch),
+//  * cells of many particles, whose rows and ranking k_cell_gather would leave
+//    to a few waves (64 a cell, 40^3 cells: 0.69 ms there).
+static __global__ __launch_bounds__(kBlock) void k_cell_place(
+    int n, unsigned cell_blocks, SortGrid SG, CellList cl, uint32_t* __restrict__ start,
+    uint32_t* __restrict__ skey, uint32_t* __restrict__ tmp) {
+    static_assert(kWaveSums <= kBlock, "one sum per thread");
+    if (blockIdx.x < cell_blocks) {
+        const int64_t c0 = (int64_t)blockIdx.x * kBlock, c = c0 + threadIdx.x;
+        const bool mine = c < SG.ncells;
+        const uint32_t cnt = mine ? cl.counts[c] : 0u;
+        // particles before the block: of the chunks, and of the chunk's cells
+        const int chunk = (int)(c0 >> SG.chunk_shift);
+        uint32_t first = 0;
+        if (SG.scanned) {
+            if (threadIdx.x == 0) first = SG.sums[chunk];
+        } else if ((int)threadIdx.x < chunk) {  // at most kWaveSums = kBlock of them
+            first = SG.sums[threadIdx.x];
+        }
+        if (threadIdx.x == 0) first += SG.sub[c0 / SG.cpw];
+        // both sums in one scan: the offsets in the low half, the total in the high
+        uint64_t total;
+        const uint64_t at =
+            block_exclusive_scan<uint64_t>(((uint64_t)first << 32) | (uint64_t)cnt, &total);
+        const uint32_t b = (uint32_t)(total >> 32) + (uint32_t)at;
+        if (!mine) return;
+        start[c] = b;
+        if (SG.cs) {
+            SG.cs[c] = b;
+            SG.ce[c] = b + cnt;
+        }
+        if (c == SG.ncells - 1) start[SG.ncells] = b + cnt;
+        return;
+    }
+    __shared__ uint32_t before[kWaveSums];
+    const int i = (int)((blockIdx.x - cell_blocks) * kBlock + threadIdx.x);
+    if (!SG.scanned) {
+        const uint32_t v = (int)threadIdx.x < SG.nchunks ? SG.sums[threadIdx.x] : 0u;
+        const uint32_t at = block_exclusive_scan<uint32_t>(v, nullptr);
+        if (threadIdx.x < kWaveSums) before[threadIdx.x] = at;
+        __syncthreads();
+    }
+    if (i >= n) return;
+    const uint32_t key = cl.key[i];
+    const uint32_t chunk = key >> SG.chunk_shift;
+    uint32_t s = (SG.scanned ? SG.sums[chunk] : before[chunk]) + SG.sub[key / kPlaceCells] +
+                 cl.rank[i];
+    // the counts' array ends a multiple of 256 bytes after its start
+    const uint4* __restrict__ c4 =
+        reinterpret_cast<const uint4*>(cl.counts) + key / kPlaceCells * (kPlaceCells / 4);
+    const uint4 a = c4[0], b = c4[1];
+    const uint32_t c[7] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z};
+#pragma unroll
+    for (uint32_t k = 0; k < 7; ++k) s += k < key % kPlaceCells ? c[k] : 0u;
+    tmp[s] = (uint32_t)i;
+    skey[s] = key;
 }
 template <int DIM, typename T>
 __global__ __launch_bounds__(kBlock) void k_slot_gather(
@@ -1532,17 +1722,12 @@ __global__ __launch_bounds__(kBlock) void k_slot_gather(
     State dst, Grid G, uint32_t* __restrict__ perm, int want_perm,
     const uint32_t* __restrict__ skey, typename Rec<T>::type* __restrict__ pos,
     typename Vec4<T>::type* __restrict__ vel, uint8_t* __restrict__ type_tape, PairConst<T> C,
-    typename Vec2<T>::type* __restrict__ rp, GatherOp op) {
+    typename Vec2<T>::type* __restrict__ rp, GatherOp op, uint32_t* __restrict__ counts) {
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= n) return;
-    const uint32_t i = tmp[s];
-    const uint32_t key = skey[s];
-    const uint32_t b = start[key], e = start[key + 1];
-    uint32_t rank = 0;
-    for (uint32_t t = b; t < e; ++t) rank += tmp[t] < i ? 1u : 0u;
-    const uint32_t d = b + rank;
-    if (want_perm) perm[d] = i;
-    gather_one<DIM, T>(i, d, key, src, dst, G, pos, vel, type_tape, C, rp, op);
+    if (slot_one<DIM, T>((uint32_t)s, tmp, start, skey, perm, want_perm, src, dst, G, pos, vel,
+                         type_tape, C, rp, op))
+        counts[skey[s]] = 0u;
 }
 
 // Pack pair records of an already sorted state (standalone evaluations):
