@@ -697,7 +697,9 @@ sph::PairConst<T> pair_const(const sph_params* p, const sph::Grid& G) {
     C.inv_h = (T)(1.0 / h);
     C.sigma = (T)sigma;
     C.sigma_h2 = (T)(sigma / (h * h));
-    C.eta_h2 = (T)(std::max(p->eta, 1e-24) * h * h);
+    // never zero: the self pair divides by it (1e-200 is below half a unit in
+    // the last place of every other pair's |r|^2; FP32 has no room for that)
+    C.eta_h2 = (T)(std::max(p->eta, sizeof(T) == 8 ? 1e-200 : 1e-24) * h * h);
     C.four_nu = (T)(4.0 * p->nu);
     for (int k = 0; k < 3; ++k) {
         C.g[k] = (T)p->g[k];

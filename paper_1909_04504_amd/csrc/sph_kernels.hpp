@@ -197,7 +197,7 @@ struct PairConst {
     T inv_h;       // 1/h
     T sigma;       // kernel normalisation (includes h^-dim)
     T sigma_h2;    // sigma / h^2: scale of F = (dW/dr)/r
-    T eta_h2;      // eta h^2, at least 1e-24 h^2
+    T eta_h2;      // eta h^2, at least 1e-200 h^2 (FP32 1e-24 h^2)
     T four_nu;     // 4 nu
     T g[3];        // body acceleration
     T cs[3];       // cell sizes
@@ -238,7 +238,7 @@ __device__ __forceinline__ double geom_r2d(const Geom<float>& g, const PairConst
 // value (over 2^-60 .. 2^20: 0.50, 0.99 and 0.50 units; 1 / sqrt(x) rounded
 // twice 1.49).  The arguments are positive and finite: |r| and |r|^2 of
 // accepted pairs (at least the smallest normal number, tiny_normal), sums of
-// densities and |r|^2 + eta h^2 (at least 1e-24 h^2); an infinite density makes
+// densities and |r|^2 + eta h^2 (at least 1e-200 h^2); an infinite density makes
 // its pressure term NaN in either form.
 __device__ __forceinline__ float p_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double p_sqrt(double x) {
@@ -2174,7 +2174,7 @@ __device__ __forceinline__ void density_add(double& acc, const Geom<T>& g, doubl
 // with F = (dW/dr)/r.  The self pair (j = i) is not skipped: r = 0 and
 // v_i - v_i = 0 multiply finite factors (F is finite at r = 0, and the
 // viscous factor holds |r|^2 = 0 over a positive denominator, eta h^2 being
-// at least 1e-24 h^2), so it adds exactly zero.
+// at least PairConst says), so it adds exactly zero.
 template <int DIM, int KERNEL, typename T>
 __device__ __forceinline__ void momentum_add(T& ax, T& ay, T& az, const Geom<T>& g, T mj,
                                              const typename Vec4<T>::type& vi,
