@@ -289,7 +289,7 @@ inline void tile_geometry(const sph_params* p, const sph::Grid& G, sph::Tiles* T
     const double R = support_radius(p);
     T.rclip2 = (float)(R * R * (1.0 + 1e-4));
     T.clip_pad = (float)(1e-4 * std::min(G.cs[0], std::min(G.cs[1], G.cs[2])));
-        if (nt > (int64_t)1 << 30 || T.uw > sph::kTileUnionAxisMax || T.uh > sph::kTileUnionAxisMax ||
+    if (nt > (int64_t)1 << 30 || T.uw > sph::kTileUnionAxisMax || T.uh > sph::kTileUnionAxisMax ||
         T.ud > sph::kTileUnionAxisMax || T.uw * T.uh * T.ud > max_cells ||
         T.tw * T.th * T.td > max_tcells) {
         std::memset(&T, 0, sizeof T);
@@ -299,19 +299,13 @@ inline void tile_geometry(const sph_params* p, const sph::Grid& G, sph::Tiles* T
 }
 
 // Box of the FP64 tiles: the first of a list (by the share of the union that
-// is targets) whose union is expected to fit the staging with 8% to spare.
-// The expected particles per cell are the grid's mean where every axis is
-// periodic (the fluid fills the box); elsewhere a tank may be partly empty,
-// and at least those of a lattice at h = 1.5 dx are assumed.
-// False: no box fits.
-inline bool box64(const sph_params* p, const sph::Grid& G, double occ, sph::Tiles* T) {
+// is targets) whose union is expected to fit the staging with 8% to spare, at
+// occ particles per cell: the grid's mean, in a box that is not periodic (a
+// tank is partly empty) at least a lattice's at h = 1.5 dx.  Fluid denser than
+// that may exceed it (tile_probe).  False: no box fits.
+inline bool box64(double occ, sph::Tiles* T) {
     static const int half[][3] = {{4, 4, 4}, {4, 4, 3}, {4, 4, 2}, {4, 3, 2}, {3, 3, 2}, {2, 2, 2}};
     static const int whole[][3] = {{4, 2, 2}, {3, 2, 2}, {2, 2, 2}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
-    if (!(p->periodic[0] && p->periodic[1] && p->periodic[2])) {
-        double lattice = 1.0;
-        for (int k = 0; k < 3; ++k) lattice *= G.cs[k] / (p->h / 1.5);
-        occ = std::max(occ, lattice);
-    }
     for (int b = 0; b < 6; ++b) {
         const int* t = T->S == 2 ? half[b] : whole[b];
         const int cells = (t[0] + 2 * T->S) * (t[1] + 2 * T->S) * (t[2] + 2 * T->S);
@@ -322,6 +316,35 @@ inline bool box64(const sph_params* p, const sph::Grid& G, double occ, sph::Tile
         return true;
     }
     return false;
+}
+inline double box_occ(const sph_params* p, const sph::Grid& G, double mean) {
+    if (p->periodic[0] && p->periodic[1] && p->periodic[2]) return mean;
+    double lattice = 1.0;
+    for (int k = 0; k < 3; ++k) lattice *= G.cs[k] / (p->h / 1.5);
+    return std::max(mean, lattice);
+}
+// Whether boxes of T's size hold enough targets, at the grid's mean occupancy,
+// for their 256 threads and their setup, staging and gathers: below, global
+// lists are faster.  Step times over those with global lists, periodic cubes,
+// by targets a box: 4 x 4 x 4 half-size cells 88 1.19, 112 0.88, 146 0.66 at
+// 100^3, 86 1.25, 113 1.16, 143 0.96, 216 0.63 at 64^3 (a last wave of tiles
+// nearly empty weighs more), 64 0.84, 88 0.83 at 40^3; whole cells 4 x 2 x 2
+// 128 1.13, 176 0.78 at 100^3, 128 1.27, 172 1.06, 238 0.71 at 64^3,
+// 2 x 2 x 2 88 1.28, 116 0.93, 146 0.66 at 100^3, 2 x 1 x 1 79 1.04 at 75^3;
+// up to 32^3 any box 0.5 to 0.9, since the passes over lists have too few waves
+// there.
+inline bool enough_targets(const sph::Tiles& T, int64_t n, double mean) {
+    const int cells = T.tw * T.th * T.td;
+    if (n <= 35000) return true;
+    double need = 125.0;
+    if (T.S == 1) need = cells >= 16 ? 200.0 : (cells == 8 ? 110.0 : 125.0);
+    if (cells != 8 && (n > 300000 || n <= 70000)) need *= 0.72;
+    return cells * mean >= need;
+}
+// Neighbours (self included) of a particle at occ particles per cell, 3D.
+inline double expected_neighbours(const sph_params* p, const sph::Grid& G, double occ) {
+    const double R = support_radius(p);
+    return occ * 4.18879 * R * R * R / (G.cs[0] * G.cs[1] * G.cs[2]);
 }
 
 // Tiles of the 3D summation passes (ntiles = 0: not used).  Mixed precision:
@@ -335,7 +358,10 @@ inline bool box64(const sph_params* p, const sph::Grid& G, double occ, sph::Tile
 // average: on a sparse grid most boxes hold few particles, and the lists in
 // global memory stay cache-resident (3D dam break, 2.18M particles on 5.4M
 // cells: 1.72 ms per step with global lists, 4.44 ms tiled); pair_tiles > 0
-// uses them wherever they apply.
+// uses them wherever they apply.  In FP64 by default also only where the boxes
+// hold enough targets (enough_targets) and the lists have room
+// for the neighbours expected (otherwise the build is for nothing: 64^3,
+// h = 1.8 dx, whole cells 3.54 and 2.93 ms).
 inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells) {
     sph::Tiles T;
     std::memset(&T, 0, sizeof T);
@@ -348,7 +374,10 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
     const double occ = (double)n / (double)ncells;
     T.S = G.S;
     if (f64) {
-        if (!box64(p, G, occ, &T)) return T;
+        if (!box64(box_occ(p, G, occ), &T)) return T;
+        if (p->pair_tiles == 0 && (!enough_targets(T, n, occ) ||
+                                   expected_neighbours(p, G, occ) > (double)list_cap(p, n)))
+            return T;
     } else if (T.S == 2) {
         T.tw = 6; T.th = 6; T.td = 4;
     } else if (occ <= 19.0) {
@@ -366,7 +395,8 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
 // particles share a cell and its candidates, so that the walk's loads are
 // broadcasts: 100^3 cube FP64 1.44 ms walked, 1.62 to 3.05 tiled; half-size
 // cells 1.19 walked, 1.10 tiled, and 48^3, where the walk has too few waves,
-// 0.182 and 0.070).  Sparse grids walk (most boxes hold few particles).
+// 0.182 and 0.070).  Sparse grids walk (most boxes hold few particles), and
+// those whose boxes hold few targets (enough_targets).
 // pair_tiles < 0 asks for no tiles.
 inline sph::Tiles make_list_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
                                   int64_t ncells) {
@@ -375,7 +405,9 @@ inline sph::Tiles make_list_tiles(const sph_params* p, const sph::Grid& G, int64
     if (p->dim != 3 || G.S != 2 || p->pair_tiles < 0 || list_cap(p, n) == 0) return T;
     if (p->pair_tiles == 0 && n < ncells) return T;
     T.S = G.S;
-    if (!box64(p, G, (double)n / (double)ncells, &T)) return T;
+    const double mean = (double)n / (double)ncells;
+    if (!box64(box_occ(p, G, mean), &T)) return T;
+    if (p->pair_tiles == 0 && !enough_targets(T, n, mean)) return T;
     T.cap = p->pair_tiles > 0 ? std::min(p->pair_tiles, sph::CfgD::kCap) : sph::CfgD::kCap;
     tile_geometry(p, G, &T, sph::CfgD::kCells, sph::CfgD::kTCells);
     return T;
@@ -460,7 +492,7 @@ struct SlotOff {
 };
 
 struct Layout {
-    size_t flags, counts, counts2, head, table, start, chunks, sub, next, listed, rank, tmp, perm, skey,
+    size_t flags, found, counts, counts2, head, table, start, chunks, sub, next, listed, rank, tmp, perm, skey,
         lcnt, list;
     uint32_t cap;
     SortShape sort;
@@ -555,6 +587,7 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
     // (and the tile passes' fallback epoch at offset 4)
     L.flags = take(16 + 8 * std::max<size_t>(std::max(nlist_shape(n, ncells).blocks, blocks_for(n)),
                                              std::max<size_t>(ntiles, kTileNlistBlocks)));
+    L.found = take(ntiles && p->precision == SPH_FP64 ? 8 * sph::kProbeBlocks : 0);
     L.ltiles = make_list_tiles(p, G, n, ncells);
     L.sort = sort_shape(p, G, n, ncells, plain);
     const size_t cells = (size_t)ncells + sph::kSortCtl;
@@ -878,23 +911,26 @@ struct Engine {
         }
         const sph::GatherOp go{op.records ? 1 : 0, op.copy_derived ? 1 : 0, op.eos ? 1 : 0,
                                op.predict};
+        sph::TileProbe pb = probe();
+        if (!op.records) pb.found = nullptr;
         if (sh.by_slot) {
             const unsigned cb = blocks_for(ncells);
             launch(K_CELL_PLACE, sph::k_cell_place, cb + blocks_for(n), st, n, cb, SG, cells(),
                    start(), skey(), tmp);
             SPH_TRY(launch_check("k_cell_place"));
-            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n), st, n, tmp, start(), src,
-                   dst, G, perm(), op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(), go,
-                   counts(cbuf));
+            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n) + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st,
+                   n, tmp, start(), src, dst, G, perm(), op.want_perm ? 1 : 0, skey(), pos(), vel(),
+                   typetape, C, rp(), go, counts(cbuf), pb);
             return launch_check("k_slot_gather");
         }
         // the diagnostics of the step before go to one more block (of the
         // first launch of the sort)
         const bool dg = diag_job.nparts > 0;
-        launch(K_CELL_GATHER, sph::k_cell_gather<DIM, T>, (unsigned)sh.nblocks + (dg ? 1u : 0u), st,
+        const unsigned nb = (unsigned)sh.nblocks + (dg ? 1u : 0u);
+        launch(K_CELL_GATHER, sph::k_cell_gather<DIM, T>, nb + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st,
                sph::GatherArgs<DIM, T>{n, SG, cells(), src, dst, G, start(), tmp, perm(),
                                        op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(),
-                                       go, diag_job});
+                                       go, diag_job, (int)nb, pb});
         diag_job.nparts = 0;
         cbuf ^= 1;
         return launch_check("k_cell_gather");
@@ -970,20 +1006,31 @@ struct Engine {
     bool tiled() const { return kTileable && L.tiles.ntiles > 0; }
     uint32_t tcap() const { return L.cap & ~7u; }
     uint32_t* fbword() const { return (uint32_t*)(ws + L.flags + 4); }
+    // FP64: what tile_probe found, and the part of the targets that turns the
+    // tile passes off (see tiles_off)
+    uint32_t* found() const { return (uint32_t*)(ws + L.found); }
+    sph::TileProbe probe() const { return {L.tiles, tiled() && kF64 ? found() : nullptr}; }
+    uint32_t off_part() const {
+        const double occ = (double)n / (double)ncells;
+        return (double)n * expected_neighbours(prm, G, occ) > 4e7 ? 4u : 4096u;
+    }
+    bool tiles_listed = false;  // a density pass followed the tile lists
     uint32_t tile_epoch = 0;
 
     // Tile lists of the current records and, with_density, the density (and
     // EOS) over them; then the fallback density of the targets the tiles left.
+    // may_off: the build, too, leaves all targets if the tiles are off.
     int tile_lists(const sph::State& s, const uint32_t* cs, const uint32_t* ce, bool with_density,
-                   bool with_eos, bool count_pairs) {
+                   bool with_eos, bool count_pairs, bool may_off = true) {
         if constexpr (kTileable) {
             tile_epoch = next_tile_epoch();
+            tiles_listed = with_density;
             const sph::Tiles TL = L.tiles;
             with_reach([&](auto R) {
                 launch_b(K_TILE_BUILD, sph::k_tile_build<decltype(R)::value, T>,
                          (unsigned)TL.ntiles, Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce,
                          tcap(), (uint4*)list(), lcnt(), count_pairs ? 1 : 0, pairs(), tile_epoch,
-                         fbword());
+                         fbword(), (const uint32_t*)(may_off ? found() : nullptr), off_part());
             });
             SPH_TRY(launch_check("k_tile_build"));
             if (!with_density) return SPH_OK;
@@ -993,7 +1040,7 @@ struct Engine {
                     launch_b(K_TILE_DENSITY, sph::k_tile_density64<S, KERNEL>, (unsigned)TL.ntiles,
                              Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
                              (const uint4*)list(), lcnt(), (double*)s.rho, (double*)s.p, vel(), rp(),
-                             with_eos ? 1 : 0);
+                             with_eos ? 1 : 0, found(), off_part());
                 else
                     launch_b(K_TILE_DENSITY, sph::k_tile_density<S, KERNEL>, (unsigned)TL.ntiles,
                              Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
@@ -1004,8 +1051,8 @@ struct Engine {
             with_reach([&](auto R) {
                 launch(K_TILE_FALLBACK, sph::k_tile_fallback_density<decltype(R)::value, KERNEL, T>,
                        fallback_blocks(n), st, n, G, C, skey(), pos(), cs, ce, lcnt(), tcap(),
-                       (T*)s.rho, (T*)s.p, vel(), rp(), with_eos ? 1 : 0,
-                       count_pairs ? 1 : 0, pairs(), tile_epoch, fbword());
+                       list(), L.cap, (T*)s.rho, (T*)s.p, vel(), rp(), with_eos ? 1 : 0,
+                       count_pairs ? 1 : 0, pairs(), tile_epoch, fbword(), found(), off_part());
             });
             return launch_check("k_tile_fallback_density");
         }
@@ -1031,7 +1078,7 @@ struct Engine {
                              sph::kMom64Threads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
                              cs, ce, tcap(), (const uint4*)list(), lcnt(), s, kick ? 1 : 0,
                              drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(), part,
-                             stride);
+                             stride, found(), off_part());
                 else
                     launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<S, KERNEL>, wgs, sph::kMomThreads,
                              st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type, cs, ce, tcap(),
@@ -1042,9 +1089,10 @@ struct Engine {
             with_reach([&](auto R) {
                 launch(K_TILE_FALLBACK,
                        sph::k_tile_fallback_momentum<decltype(R)::value, KERNEL, T>, fb, st, n, G, C,
-                       skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(), s, kick ? 1 : 0,
+                       skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(),
+                       (const uint32_t*)(tiles_listed ? list() : nullptr), L.cap, s, kick ? 1 : 0,
                        drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(),
-                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword());
+                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword(), found(), off_part());
             });
             SPH_TRY(launch_check("k_tile_fallback_momentum"));
             if (diag_out) diag_job = {stride, part, diag_out};
@@ -1086,9 +1134,12 @@ struct Engine {
         return SPH_OK;
     }
 
-    int pack(const sph::State& s, bool with_rp) {
-        launch(K_PACK, sph::k_pack<DIM, T>, blocks_for(n), st, n, s, G, skey(), pos(), vel(),
-                                                                  rp(), with_rp ? 1 : 0);
+    // cs, ce: the cells that tile passes will be given, if they may be off.
+    int pack(const sph::State& s, bool with_rp, const uint32_t* cs, const uint32_t* ce) {
+        sph::TileProbe pb = probe();
+        if (!cs) pb.found = nullptr;
+        launch(K_PACK, sph::k_pack<DIM, T>, blocks_for(n) + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st, n, s, G, skey(),
+               pos(), vel(), rp(), with_rp ? 1 : 0, pb, cs, ce);
         return launch_check("k_pack");
     }
 
@@ -1113,13 +1164,13 @@ struct Engine {
 
     int density_only(sph_particles* pa, const uint32_t* cs, const uint32_t* ce) {
         const sph::State user = user_state(pa, prm);
-        SPH_TRY(pack(user, false));
+        SPH_TRY(pack(user, false, cs, ce));
         return density(user, cs, ce, false);
     }
 
     int momentum_only(sph_particles* pa, const uint32_t* cs, const uint32_t* ce) {
         const sph::State user = user_state(pa, prm);
-        SPH_TRY(pack(user, true));
+        SPH_TRY(pack(user, true, cs, ce));
         if (tiled())
             SPH_TRY(tile_lists(user, cs, ce, false, false, false));
         else if (L.cap)
@@ -1136,11 +1187,11 @@ struct Engine {
     int neighbors(const sph_particles* pa, const uint32_t* cs, const uint32_t* ce, int64_t capacity,
                   int64_t* offsets, int32_t* nbr, int64_t* total) {
         const sph::State user = user_state(pa, prm);
-        SPH_TRY(pack(user, false));
+        SPH_TRY(pack(user, false, nullptr, nullptr));
         // counts from the lists (filled from them below), or without lists
         // from a walk of the cells
         if (tiled()) {
-            SPH_TRY(tile_lists(user, cs, ce, false, false, false));
+            SPH_TRY(tile_lists(user, cs, ce, false, false, false, false));
             if constexpr (kTileable) {
                 with_reach([&](auto R) {
                     launch(K_TILE_FALLBACK, sph::k_tile_fallback_count<decltype(R)::value, T>,

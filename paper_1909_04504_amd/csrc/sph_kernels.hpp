@@ -1235,6 +1235,135 @@ static __global__ __launch_bounds__(kBlock) void k_sums_scan(int nchunks,
     }
 }
 
+// ---------------------------------------------------------------------------
+// Geometry of the 3D tile passes, and the FP64 tiles' probe.
+constexpr int kTileCellsMax = 1024;              // of every configuration
+constexpr int kTileUnionAxisMax = 12;            // union cells per axis: 12 * 2^27 + 2^29 < 2^31
+
+// Tile geometry of one grid (host-computed).
+struct Tiles {
+    int S;                 // stencil reach
+    int tw, th, td;        // tile box, cells
+    int uw, uh, ud;        // union box: tile box + S cells on each side
+    int nt[3];             // tiles per axis
+    int ntiles;
+    int cap;               // staged particles per tile (<= the configuration's kCap)
+    float csf[3];          // cell sizes
+    float inv_csf[3];
+    int cen[3];            // union centre in cells (uw/2, uh/2, ud/2): origin of the float copy
+    float rclip2;          // R^2 (1 + 1e-4): rows farther than this hold no neighbour
+    float clip_pad;        // 1e-4 of a cell: padding of a row's clipped x range
+    float inv_uw, inv_uwh; // 1 / uw, 1 / (uw uh): union cell coordinates (union_coords)
+};
+
+// q = floor(c / d) for 0 <= c < 2^10 and 1 <= d <= 144, inv_d = fl(1 / d):
+// (c + 1/2) / d is at least 1/(2d) >= 1/288 away from an integer, and the
+// FP32 product (c + 1/2) inv_d is within 2^-12 of it, so its truncation is
+// exact (a few VALU instructions instead of an integer division).
+static_assert(kTileCellsMax <= 1024 && kTileUnionAxisMax * kTileUnionAxisMax <= 144,
+              "small_quot's range");
+__device__ __forceinline__ int small_quot(int c, float inv_d) {
+    return (int)(((float)c + 0.5f) * inv_d);
+}
+// Coordinates (ux, uy, uz) of union cell c of a tile.
+__device__ __forceinline__ void union_coords(const Tiles& TL, int c, int uc[3]) {
+    const int z = small_quot(c, TL.inv_uwh);
+    const int r = c - z * (TL.uw * TL.uh);
+    const int y = small_quot(r, TL.inv_uw);
+    uc[0] = r - y * TL.uw;
+    uc[1] = y;
+    uc[2] = z;
+}
+
+// Global cell coordinate of union coordinate u along axis k of a tile whose
+// box starts at cell c0; -1 outside a non-periodic grid.
+__device__ __forceinline__ int tile_axis(const Grid& G, int k, int c0, int u, int S) {
+    int c = c0 - S + u;
+    const int nc = G.nc[k];
+    if (c >= 0 && c < nc) return c;
+    if (!G.periodic[k]) return -1;
+    // c lies within a few grid lengths: wrap by steps, not by a division
+    while (c < 0) c += nc;
+    while (c >= nc) c -= nc;
+    return c;
+}
+
+// Tile origin (first cell) of tile t.
+__device__ __forceinline__ void tile_origin(const Tiles& TL, int t, int c0[3]) {
+    c0[0] = (t % TL.nt[0]) * TL.tw;
+    c0[1] = ((t / TL.nt[0]) % TL.nt[1]) * TL.th;
+    c0[2] = (t / (TL.nt[0] * TL.nt[1])) * TL.td;
+}
+
+// What a sort, or the packing of a sorted state, finds out for the FP64 tile
+// passes that follow in kProbeBlocks more blocks (found == nullptr: nothing):
+// how many targets would be in tiles that overflow their staging, in a fluid
+// denser than the mean of its grid.  A wave looks at one tile in
+// every ntiles / 32; block b leaves the targets that overflow and all of them
+// in found[2 b] and found[2 b + 1].
+constexpr int kProbeBlocks = 8;
+struct TileProbe {
+    Tiles TL;
+    uint32_t* found;
+};
+template <typename Count>
+__device__ __forceinline__ void tile_probe(const TileProbe& P, const Grid& G, int b,
+                                           Count&& count) {
+    const Tiles& TL = P.TL;
+    __shared__ uint32_t over_[kBlock / 64], all_[kBlock / 64];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    constexpr int kTiles = kProbeBlocks * kBlock / 64;
+    const int64_t t = (int64_t)(b * (kBlock / 64) + w) * TL.ntiles / kTiles;
+    uint32_t total = 0, targets = 0;
+    int c0[3];
+    tile_origin(TL, (int)t, c0);
+#pragma unroll 4
+    for (int c = lane; c < TL.uw * TL.uh * TL.ud; c += 64) {
+        int uc[3], g[3];
+        union_coords(TL, c, uc);
+        bool in = true, box = true;
+        for (int k = 0; k < 3; ++k) {
+            g[k] = tile_axis(G, k, c0[k], uc[k], TL.S);
+            in = in && g[k] >= 0;
+            const int d = uc[k] - TL.S, tw = k == 0 ? TL.tw : (k == 1 ? TL.th : TL.td);
+            box = box && d >= 0 && d < tw && c0[k] + d < G.nc[k];
+        }
+        const uint32_t m = in ? count(cell_key(g, G)) : 0u;
+        total += m;
+        targets += box ? m : 0u;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        total += (uint32_t)__shfl_xor((int)total, d, 64);
+        targets += (uint32_t)__shfl_xor((int)targets, d, 64);
+    }
+    if (lane == 0) {
+        over_[w] = total > (uint32_t)TL.cap ? targets : 0u;
+        all_[w] = targets;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const uint32_t* v = threadIdx.x == 0 ? over_ : all_;
+        uint32_t sum = 0;
+        for (int k = 0; k < kBlock / 64; ++k) sum += v[k];
+        P.found[2 * b + threadIdx.x] = sum;
+    }
+}
+// Whether the tile passes leave every target to the fallback: more than 1/part
+// of the targets looked at overflow.  The fallback's walks of a few targets take
+// as long as those of many up to some 10^5 (0.33 ms in both passes at
+// h = 1.5 dx), which only the gain of a large problem covers, so the host asks
+// for part = 4 there and for none at all (a large part) elsewhere.
+__device__ __forceinline__ bool tiles_off(const uint32_t* __restrict__ found, uint32_t part) {
+    uint64_t over = 0, all = 0;
+#pragma unroll
+    for (int b = 0; b < kProbeBlocks; ++b) {
+        over += found[2 * b];
+        all += found[2 * b + 1];
+    }
+    return over * part > all;
+}
+
 // What the sort's gather does with particle i of src, whose slot is d and
 // cell key `key`: its state to dst, its pair records, and with eos the EOS.
 struct GatherOp {
@@ -1510,6 +1639,8 @@ struct GatherArgs {
     typename Vec2<T>::type* rp;
     GatherOp op;
     DiagJob job;
+    int probe_block;  // first one of the TileProbe, behind the others
+    TileProbe probe;
 };
 
 // k_cell_gather with particles heaped up (the first heaped_blocks of its
@@ -1609,10 +1740,16 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(GatherArgs<DIM, T> A) {
     __shared__ uint8_t cellof_[kWaves][kSortEntries];
     __shared__ uint32_t lo_[kWaves][65];
     __shared__ uint32_t before_[kWaves];
-    if ((int)blockIdx.x == A.SG.nblocks) {
+    if ((int)blockIdx.x == A.SG.nblocks && A.job.nparts) {
         diag_sum<DIM>(A.job.nparts, A.job.part, A.job.out);
         return;
     }
+    if constexpr (DIM == 3 && sizeof(T) == 8)
+        if ((int)blockIdx.x >= A.probe_block) {
+            const uint32_t* __restrict__ counts = A.cl.counts;
+            tile_probe(A.probe, A.G, (int)blockIdx.x - A.probe_block, [&](uint32_t key) { return counts[key]; });
+            return;
+        }
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
     uint32_t* const ent = ent_[w];
     uint32_t* const sorted = sorted_[w];
@@ -1722,7 +1859,14 @@ __global__ __launch_bounds__(kBlock) void k_slot_gather(
     State dst, Grid G, uint32_t* __restrict__ perm, int want_perm,
     const uint32_t* __restrict__ skey, typename Rec<T>::type* __restrict__ pos,
     typename Vec4<T>::type* __restrict__ vel, uint8_t* __restrict__ type_tape, PairConst<T> C,
-    typename Vec2<T>::type* __restrict__ rp, GatherOp op, uint32_t* __restrict__ counts) {
+    typename Vec2<T>::type* __restrict__ rp, GatherOp op, uint32_t* __restrict__ counts,
+    TileProbe probe) {
+    if constexpr (DIM == 3 && sizeof(T) == 8)
+        if (probe.found && blockIdx.x >= gridDim.x - kProbeBlocks) {
+            tile_probe(probe, G, (int)(blockIdx.x - (gridDim.x - kProbeBlocks)),
+                       [&](uint32_t key) { return start[key + 1] - start[key]; });
+            return;
+        }
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= n) return;
     if (slot_one<DIM, T>((uint32_t)s, tmp, start, skey, perm, want_perm, src, dst, G, pos, vel,
@@ -1738,7 +1882,17 @@ __global__ __launch_bounds__(kBlock) void k_pack(int n, State S, Grid G,
                                                  typename Rec<T>::type* __restrict__ pos,
                                                  typename Vec4<T>::type* __restrict__ vel,
                                                  typename Vec2<T>::type* __restrict__ rp,
-                                                 int with_rp) {
+                                                 int with_rp, TileProbe probe,
+                                                 const uint32_t* __restrict__ cstart,
+                                                 const uint32_t* __restrict__ cend) {
+    if constexpr (DIM == 3 && sizeof(T) == 8)
+        if (probe.found && blockIdx.x >= gridDim.x - kProbeBlocks) {
+            tile_probe(probe, G, (int)(blockIdx.x - (gridDim.x - kProbeBlocks)), [&](uint32_t key) {
+                const uint32_t b = cstart[key], e = cend[key];
+                return e > b ? e - b : 0u;
+            });
+            return;
+        }
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     bool outside = false;

@@ -31,7 +31,11 @@
 //    walk the cells in global memory with the same arithmetic.  A build that
 //    leaves any such target stores its epoch in the workspace's fallback
 //    word; the fallback kernels exit at once when the word holds another
-//    epoch.
+//    epoch.  In FP64, where the staging holds fewer particles, a fluid denser
+//    than the mean of its grid may overflow most tiles: the sort, or the
+//    packing of a sorted state, looks at some of them (tile_probe), and where
+//    they would, the tile passes leave every target to the fallback, whose
+//    density pass writes the global-format lists as it walks.
 #pragma once
 
 #include "sph_kernels.hpp"
@@ -51,46 +55,10 @@ using CfgD = TileCfg<256, 512, 64, 2000>;    // FP64
 template <typename T> struct TileCfgOf;
 template <> struct TileCfgOf<float> { using type = CfgF; };
 template <> struct TileCfgOf<double> { using type = CfgD; };
-constexpr int kTileCellsMax = 1024;              // of every configuration
-constexpr int kTileUnionAxisMax = 12;            // union cells per axis: 12 * 2^27 + 2^29 < 2^31
 template <bool B> struct BoolC { static constexpr bool value = B; };
 constexpr uint32_t kTileOverflow = 0xffffffffu;  // count of a target left to the fallback
 constexpr int kFallbackBlocks = 1024;            // grid of the fallback kernels (grid-stride)
 
-// Tile geometry of one grid (host-computed).
-struct Tiles {
-    int S;                 // stencil reach
-    int tw, th, td;        // tile box, cells
-    int uw, uh, ud;        // union box: tile box + S cells on each side
-    int nt[3];             // tiles per axis
-    int ntiles;
-    int cap;               // staged particles per tile (<= kTileCap)
-    float csf[3];          // cell sizes
-    float inv_csf[3];
-    int cen[3];            // union centre in cells (uw/2, uh/2, ud/2): origin of the float copy
-    float rclip2;          // R^2 (1 + 1e-4): rows farther than this hold no neighbour
-    float clip_pad;        // 1e-4 of a cell: padding of a row's clipped x range
-    float inv_uw, inv_uwh; // 1 / uw, 1 / (uw uh): union cell coordinates (union_coords)
-};
-
-// q = floor(c / d) for 0 <= c < 2^10 and 1 <= d <= 144, inv_d = fl(1 / d):
-// (c + 1/2) / d is at least 1/(2d) >= 1/288 away from an integer, and the
-// FP32 product (c + 1/2) inv_d is within 2^-12 of it, so its truncation is
-// exact (a few VALU instructions instead of an integer division).
-static_assert(kTileCellsMax <= 1024 && kTileUnionAxisMax * kTileUnionAxisMax <= 144,
-              "small_quot's range");
-__device__ __forceinline__ int small_quot(int c, float inv_d) {
-    return (int)(((float)c + 0.5f) * inv_d);
-}
-// Coordinates (ux, uy, uz) of union cell c of a tile.
-__device__ __forceinline__ void union_coords(const Tiles& TL, int c, int uc[3]) {
-    const int z = small_quot(c, TL.inv_uwh);
-    const int r = c - z * (TL.uw * TL.uh);
-    const int y = small_quot(r, TL.inv_uw);
-    uc[0] = r - y * TL.uw;
-    uc[1] = y;
-    uc[2] = z;
-}
 
 // Per-workgroup bookkeeping in LDS.
 template <typename CFG>
@@ -130,26 +98,6 @@ __device__ __forceinline__ uint32_t tile_scan2(uint32_t a, uint32_t b, TileMeta<
     __syncthreads();  // wsum is reused by the next scan
     *total = all;
     return before + incl - v;
-}
-
-// Global cell coordinate of union coordinate u along axis k of a tile whose
-// box starts at cell c0; -1 outside a non-periodic grid.
-__device__ __forceinline__ int tile_axis(const Grid& G, int k, int c0, int u, int S) {
-    int c = c0 - S + u;
-    const int nc = G.nc[k];
-    if (c >= 0 && c < nc) return c;
-    if (!G.periodic[k]) return -1;
-    // c lies within a few grid lengths: wrap by steps, not by a division
-    while (c < 0) c += nc;
-    while (c >= nc) c -= nc;
-    return c;
-}
-
-// Tile origin (first cell) of tile t.
-__device__ __forceinline__ void tile_origin(const Tiles& TL, int t, int c0[3]) {
-    c0[0] = (t % TL.nt[0]) * TL.tw;
-    c0[1] = ((t / TL.nt[0]) % TL.nt[1]) * TL.th;
-    c0[2] = (t / (TL.nt[0] * TL.nt[1])) * TL.td;
 }
 
 // Whether the tile's box holds no particle: the keys of its cells lie
@@ -757,7 +705,8 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
     const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, uint32_t cap, uint4* __restrict__ list,
     uint32_t* __restrict__ ncnt, int count_pairs, unsigned long long* __restrict__ pairs,
-    uint32_t epoch, uint32_t* __restrict__ fallback) {
+    uint32_t epoch, uint32_t* __restrict__ fallback, const uint32_t* __restrict__ found,
+    uint32_t part) {
     using R = typename Rec<T>::type;
     using CFG = typename TileCfgOf<T>::type;
     constexpr int NT = CFG::kThreads;
@@ -777,6 +726,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
     // the cell-range loads go out before the empty-box probe, so that the
     // two round trips overlap
     const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
+    if (sizeof(T) == 8 && found && tiles_off(found, part)) return;
     if (tile_empty(G, TL, c0, cstart, cend)) {
         if (count_pairs) tile_count<NT>(0u, pairs, blk);
         return;
@@ -1353,7 +1303,8 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
     const uint4* __restrict__ list, const uint32_t* __restrict__ ncnt,
     double* __restrict__ rho_out, double* __restrict__ p_out, double4* __restrict__ vel,
-    double2* __restrict__ rp, int with_eos) {
+    double2* __restrict__ rp, int with_eos, const uint32_t* __restrict__ found,
+    uint32_t part) {
     __shared__ TileMeta<CfgD> M;
     __shared__ PosD P;
     __shared__ uint8_t W[CfgD::kCap];
@@ -1362,6 +1313,7 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
     int c0[3];
     tile_origin(TL, blk, c0);
     const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
+    if (tiles_off(found, part)) return;
     if (tile_empty(G, TL, c0, cstart, cend)) return;
     const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
     if (total > (uint32_t)cap_union) return;  // every target is the fallback's
@@ -1418,7 +1370,8 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
     const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
     const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
     CellList cl, uint32_t* __restrict__ flags,
-    double* __restrict__ diag_part, int stride) {
+    double* __restrict__ diag_part, int stride, const uint32_t* __restrict__ found,
+    uint32_t part) {
     __shared__ TileMeta<CfgD> MM[2];
     __shared__ uint16_t cellofs[2][CfgD::kCap];
     __shared__ PosD P;
@@ -1457,6 +1410,12 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
     // prologue (t = t0 - NP): tile t0 set up; the loop's first round stages it
     tile_origin(TL, t0, cs);
     tile_setup(G, TL, cs, cstart, cend, n, MM[0], tid);
+    if (tiles_off(found, part)) {  // the fallback's, all of them
+        if (diag_part)
+            for (int k = (int)threadIdx.x; t0 + (k >> 2) * NP < t1; k += kMom64Threads)
+                diag_part[(int64_t)(k & 3) * stride + t0 + (k >> 2) * NP] = 0.0;
+        return;
+    }
     tile_cellof<CfgD, kMom64Threads>(TL, MM[0], cellofs[0]);
     // set-up of the tile after the next one into the meta that tile t leaves,
     // by all waves (the loaders hold its cell ranges); publishes the staging
@@ -1570,17 +1529,43 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
 
 // Fallback density: the targets the tile build left (count above cap, or
 // kTileOverflow), by the cell walk in global memory (density_one); only the
-// kTileOverflow ones are counted (the build counted the others).
+// kTileOverflow ones are counted (the build counted the others).  With the
+// tiles off (FP64, tiles_off), every target, whose global-format list (list_cap entries
+// at most) and count are written on the way.
 template <int S, int KERNEL, typename T>
 __global__ __launch_bounds__(kBlock) void k_tile_fallback_density(
     int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
     const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
-    const uint32_t* __restrict__ cend, const uint32_t* __restrict__ ncnt, uint32_t cap,
+    const uint32_t* __restrict__ cend, uint32_t* __restrict__ ncnt, uint32_t cap,
+    uint32_t* __restrict__ list, uint32_t list_cap,
     T* __restrict__ rho_out, T* __restrict__ p_out, typename Vec4<T>::type* __restrict__ vel,
     typename Vec2<T>::type* __restrict__ rp, int with_eos, int count_pairs, unsigned long long* __restrict__ pairs,
-    uint32_t epoch, const uint32_t* __restrict__ fallback) {
-    if (*fallback != epoch) return;
+    uint32_t epoch, const uint32_t* __restrict__ fallback, const uint32_t* __restrict__ found,
+    uint32_t part) {
+    const bool all = sizeof(T) == 8 && tiles_off(found, part);
+    if (!all && *fallback != epoch) return;
     uint32_t counted = 0;
+    if (all) {
+        for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+            const typename Rec<T>::type ri = pos[i];
+            uint32_t* __restrict__ col = list + list_column((uint32_t)i, list_cap);
+            uint32_t cnt = 0;
+            double acc = 0.0;
+            walk_pairs<3, S, T>(G, C, skey[i], ri, pos, skey, cstart, cend, (uint32_t)n, NoPayload(),
+                                [&](uint32_t j, const typename Rec<T>::type& rj, int,
+                                    const Geom<T>& g, uint32_t code) {
+                                    if (cnt < list_cap)
+                                        col[cnt * kListTile] = (j << NbrCode<3, S, T>::kBits) | code;
+                                    density_add<KERNEL, T>(acc, g, (double)rec_mass(rj), C);
+                                    ++cnt;
+                                });
+            finish_density<3, T>(i, acc, C, rho_out, 0, p_out, vel, rp, with_eos);
+            counted += cnt;
+            ncnt[i] = cnt;
+        }
+        if (count_pairs) block_count(counted, pairs, blockIdx.x);
+        return;
+    }
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         const uint32_t c = ncnt[i];
         if (c <= cap) continue;
@@ -1593,23 +1578,30 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_density(
     if (count_pairs) block_count(counted, pairs, blockIdx.x);
 }
 
-// Fallback momentum, as k_tile_fallback_density; diagnostics partials of its
-// blocks at diag_part[q * stride + b] (zeros when there is nothing to do).
+// Fallback momentum, as k_tile_fallback_density (list: the lists that it wrote
+// if the tiles are off, null: no density pass went before); diagnostics partials
+// of its blocks at diag_part[q * stride + b] (zeros when there is nothing to
+// do).
 template <int S, int KERNEL, typename T>
-__global__ __launch_bounds__(kBlock) void k_tile_fallback_momentum(
+__global__ __launch_bounds__(kBlock, sizeof(T) == 8 && S == 1 ? 3 : 1) void k_tile_fallback_momentum(
     int n, Grid G, PairConst<T> C, const uint32_t* __restrict__ skey,
     const typename Rec<T>::type* __restrict__ pos, const typename Vec4<T>::type* __restrict__ vel,
     const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type, const uint32_t* __restrict__ cstart,
-    const uint32_t* __restrict__ cend, const uint32_t* __restrict__ ncnt, uint32_t cap, State St,
+    const uint32_t* __restrict__ cend, const uint32_t* __restrict__ ncnt, uint32_t cap,
+    const uint32_t* __restrict__ list, uint32_t list_cap, State St,
     int kick, int drift, double hdt, double dt, CellList cl, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
-    int stride, uint32_t epoch, const uint32_t* __restrict__ fallback) {
+    int stride, uint32_t epoch, const uint32_t* __restrict__ fallback,
+    const uint32_t* __restrict__ found,
+    uint32_t part) {
     double dsum[4] = {0.0, 0.0, 0.0, 0.0};
-    if (*fallback == epoch) {
+    const bool all = sizeof(T) == 8 && tiles_off(found, part);
+    if (all || *fallback == epoch) {
+        if (!all) list = nullptr;
         for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-            if (ncnt[i] <= cap) continue;
+            if (!all && ncnt[i] <= cap) continue;
             double dv[4] = {0.0, 0.0, 0.0, 0.0};
             momentum_one<3, S, KERNEL, T>(i, G, C, skey, pos, vel, rp, type, cstart, cend, n,
-                                          nullptr, ncnt, cap, St, kick, drift, hdt, dt, cl, flags, diag_part != nullptr, dv);
+                                          list, ncnt, list_cap, St, kick, drift, hdt, dt, cl, flags, diag_part != nullptr, dv);
             for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
         }
     }
