@@ -1317,15 +1317,24 @@ __device__ __forceinline__ void tile_probe(const TileProbe& P, const Grid& G, in
     uint32_t total = 0, targets = 0;
     int c0[3];
     tile_origin(TL, (int)t, c0);
-#pragma unroll 4
-    for (int c = lane; c < TL.uw * TL.uh * TL.ud; c += 64) {
+    const int ncu = TL.uw * TL.uh * TL.ud;  // at most 512 (FP64)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {  // all counts in flight
+        const int c = q * 64 + lane;
         int uc[3], g[3];
         union_coords(TL, c, uc);
-        bool in = true, box = true;
+        bool in = c < ncu, box = true;
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
-            g[k] = tile_axis(G, k, c0[k], uc[k], TL.S);
-            in = in && g[k] >= 0;
+            // tile_axis without branches (a box overhangs the grid, 2 S + 1
+            // cells at least where it is periodic, by 3 + S cells at most)
             const int d = uc[k] - TL.S, tw = k == 0 ? TL.tw : (k == 1 ? TL.th : TL.td);
+            const int nc = G.nc[k], p = c0[k] + d;
+            int v = p + (p < 0 ? nc : 0);
+            v -= v >= nc ? nc : 0;
+            v -= v >= nc ? nc : 0;
+            in = in && (G.periodic[k] || v == p);
+            g[k] = v;
             box = box && d >= 0 && d < tw && c0[k] + d < G.nc[k];
         }
         const uint32_t m = in ? count(cell_key(g, G)) : 0u;
