@@ -341,10 +341,11 @@ inline bool enough_targets(const sph::Tiles& T, int64_t n, double mean) {
     if (cells != 8 && (n > 300000 || n <= 70000)) need *= 0.72;
     return cells * mean >= need;
 }
-// Neighbours (self included) of a particle at occ particles per cell, 3D.
+// Neighbours (self included) of a particle at occ particles per cell.
 inline double expected_neighbours(const sph_params* p, const sph::Grid& G, double occ) {
     const double R = support_radius(p);
-    return occ * 4.18879 * R * R * R / (G.cs[0] * G.cs[1] * G.cs[2]);
+    return p->dim == 3 ? occ * 4.18879 * R * R * R / (G.cs[0] * G.cs[1] * G.cs[2])
+                       : occ * 3.14159 * R * R / (G.cs[0] * G.cs[1]);
 }
 
 // Tiles of the 3D summation passes (ntiles = 0: not used).  Mixed precision:
@@ -362,7 +363,10 @@ inline double expected_neighbours(const sph_params* p, const sph::Grid& G, doubl
 // hold enough targets (enough_targets) and the lists have room
 // for the neighbours expected (otherwise the build is for nothing: 64^3,
 // h = 1.8 dx, whole cells 3.54 and 2.93 ms).
-inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells) {
+// few: boxes with few targets too (sph_neighbors, whose other passes are walks:
+// 64^3, h = 1.2 dx, half-size cells 0.26 ms by tiles, 0.32 by global lists).
+inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n, int64_t ncells,
+                             bool few = false) {
     sph::Tiles T;
     std::memset(&T, 0, sizeof T);
     if (p->dim != 3 || p->scheme != SPH_SCHEME_SUMMATION || p->pair_tiles < 0 ||
@@ -375,7 +379,7 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
     T.S = G.S;
     if (f64) {
         if (!box64(box_occ(p, G, occ), &T)) return T;
-        if (p->pair_tiles == 0 && (!enough_targets(T, n, occ) ||
+        if (p->pair_tiles == 0 && ((!few && !enough_targets(T, n, occ)) ||
                                    expected_neighbours(p, G, occ) > (double)list_cap(p, n)))
             return T;
     } else if (T.S == 2) {
@@ -1188,8 +1192,17 @@ struct Engine {
                   int64_t* offsets, int32_t* nbr, int64_t* total) {
         const sph::State user = user_state(pa, prm);
         SPH_TRY(pack(user, false, nullptr, nullptr));
-        // counts from the lists (filled from them below), or without lists
-        // from a walk of the cells
+        // Counts from the lists (filled from them below), or without lists
+        // from a walk of the cells: where the lists' capacity would not do for
+        // most (64^3, h = 1.8 dx: 1.48 ms with lists, 1.22 without), and in 2D
+        // where a cell holds too few targets for the list build's wave (400^2,
+        // h = 1.0 dx, 4 a cell: 0.119 ms, 0.106 without).
+        const double mean = (double)n / (double)ncells;
+        const double nb = expected_neighbours(prm, G, mean);
+        const bool lists = L.cap && nb + std::sqrt(nb) <= (double)L.cap &&
+                           !(DIM == 2 && mean >= 1.0 && mean < 5.0);
+        if constexpr (kTileable)
+            L.tiles = lists ? make_tiles(prm, G, n, ncells, true) : sph::Tiles{};
         if (tiled()) {
             SPH_TRY(tile_lists(user, cs, ce, false, false, false, false));
             if constexpr (kTileable) {
@@ -1200,7 +1213,7 @@ struct Engine {
                 });
                 SPH_TRY(launch_check("k_tile_fallback_count"));
             }
-        } else if (L.cap) {
+        } else if (lists) {
             SPH_TRY(nlist(cs, ce, false));
         } else {
             with_reach([&](auto R) {
@@ -1235,7 +1248,7 @@ struct Engine {
         }
         with_reach([&](auto R) {
             constexpr int S = decltype(R)::value;
-            if (L.cap)
+            if (lists)
                 launch(K_NBR_FILL, sph::k_nbr_expand<DIM, S, T>, blocks_for(n), st, n, G, C, skey(),
                        pos(), cs, ce, (const uint32_t*)list(), lcnt(), L.cap,
                        (const int64_t*)offsets, nbr);
