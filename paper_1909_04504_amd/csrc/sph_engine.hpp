@@ -317,6 +317,10 @@ inline bool box64(double occ, sph::Tiles* T) {
     }
     return false;
 }
+// Cells of the grid (Z-order keys have more).
+inline int64_t real_cells(const sph::Grid& G) {
+    return (int64_t)G.nc[0] * G.nc[1] * G.nc[2];
+}
 inline double box_occ(const sph_params* p, const sph::Grid& G, double mean) {
     if (p->periodic[0] && p->periodic[1] && p->periodic[2]) return mean;
     double lattice = 1.0;
@@ -378,9 +382,10 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
     const double occ = (double)n / (double)ncells;
     T.S = G.S;
     if (f64) {
-        if (!box64(box_occ(p, G, occ), &T)) return T;
-        if (p->pair_tiles == 0 && ((!few && !enough_targets(T, n, occ)) ||
-                                   expected_neighbours(p, G, occ) > (double)list_cap(p, n)))
+        const double mean = (double)n / (double)real_cells(G);
+        if (!box64(box_occ(p, G, mean), &T)) return T;
+        if (p->pair_tiles == 0 && ((!few && !enough_targets(T, n, mean)) ||
+                                   expected_neighbours(p, G, mean) > (double)list_cap(p, n)))
             return T;
     } else if (T.S == 2) {
         T.tw = 6; T.th = 6; T.td = 4;
@@ -399,8 +404,8 @@ inline sph::Tiles make_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
 // particles share a cell and its candidates, so that the walk's loads are
 // broadcasts: 100^3 cube FP64 1.44 ms walked, 1.62 to 3.05 tiled; half-size
 // cells 1.19 walked, 1.10 tiled, and 48^3, where the walk has too few waves,
-// 0.182 and 0.070).  Sparse grids walk (most boxes hold few particles), and
-// those whose boxes hold few targets (enough_targets).
+// 0.182 and 0.070).  Sparse grids walk (most boxes hold few particles); on
+// others the device chooses (Engine::list_need).
 // pair_tiles < 0 asks for no tiles.
 inline sph::Tiles make_list_tiles(const sph_params* p, const sph::Grid& G, int64_t n,
                                   int64_t ncells) {
@@ -409,9 +414,8 @@ inline sph::Tiles make_list_tiles(const sph_params* p, const sph::Grid& G, int64
     if (p->dim != 3 || G.S != 2 || p->pair_tiles < 0 || list_cap(p, n) == 0) return T;
     if (p->pair_tiles == 0 && n < ncells) return T;
     T.S = G.S;
-    const double mean = (double)n / (double)ncells;
+    const double mean = (double)n / (double)real_cells(G);
     if (!box64(box_occ(p, G, mean), &T)) return T;
-    if (p->pair_tiles == 0 && !enough_targets(T, n, mean)) return T;
     T.cap = p->pair_tiles > 0 ? std::min(p->pair_tiles, sph::CfgD::kCap) : sph::CfgD::kCap;
     tile_geometry(p, G, &T, sph::CfgD::kCells, sph::CfgD::kTCells);
     return T;
@@ -591,8 +595,8 @@ inline Layout make_layout(const sph_params* p, const sph::Grid& G, int64_t n, in
     // (and the tile passes' fallback epoch at offset 4)
     L.flags = take(16 + 8 * std::max<size_t>(std::max(nlist_shape(n, ncells).blocks, blocks_for(n)),
                                              std::max<size_t>(ntiles, kTileNlistBlocks)));
-    L.found = take(ntiles && p->precision == SPH_FP64 ? 8 * sph::kProbeBlocks : 0);
     L.ltiles = make_list_tiles(p, G, n, ncells);
+    L.found = take((ntiles && p->precision == SPH_FP64) || L.ltiles.ntiles ? 12 * sph::kProbeBlocks : 0);
     L.sort = sort_shape(p, G, n, ncells, plain);
     const size_t cells = (size_t)ncells + sph::kSortCtl;
     L.counts = take(4 * cells);
@@ -965,8 +969,12 @@ struct Engine {
     // of interactions to the counters).  Every pair pass reads the lists
     // built last, so each change of records is followed by this launch.
     int nlist(const uint32_t* cs, const uint32_t* ce, bool count_pairs) {
+        sph::TileTest test{nullptr, 0u, 0u};
         if constexpr (DIM == 3) {
-            if (L.ltiles.ntiles > 0) return tile_nlist(cs, ce, count_pairs);
+            if (L.ltiles.ntiles > 0) {  // one of the two launches leaves at once
+                test = {found(), off_part(), list_need()};
+                SPH_TRY(tile_nlist(cs, ce, count_pairs, test));
+            }
         }
         with_reach([&](auto R) {
             // cell-cooperative build in 2D with cells of 2h (about 7 targets
@@ -986,19 +994,18 @@ struct Engine {
             } else {
                 launch(K_NLIST, sph::k_nlist_walk<DIM, decltype(R)::value, T>, blocks_for(n), st,
                        n, G, C, skey(), pos(), cs, ce, L.cap, list(), lcnt(), count_pairs ? 1 : 0,
-                       pairs());
+                       pairs(), test);
             }
         });
         return launch_check("k_nlist");
     }
-    int tile_nlist(const uint32_t* cs, const uint32_t* ce, bool count_pairs) {
-        const sph::Tiles& TL = L.ltiles;
+    int tile_nlist(const uint32_t* cs, const uint32_t* ce, bool count_pairs,
+                   const sph::TileTest& test) {
+        const sph::Tiles& TL = L.ltiles;  // half-size cells
         const unsigned wgs = std::min<unsigned>((unsigned)TL.ntiles, kTileNlistBlocks);
-        with_reach([&](auto R) {
-            launch_b(K_NLIST, sph::k_tile_nlist<decltype(R)::value, T>, wgs, sph::CfgD::kThreads, st,
-                     n, G, C, TL, skey(), pos(), cs, ce, L.cap, list(), lcnt(),
-                     count_pairs ? 1 : 0, pairs());
-        });
+        if constexpr (DIM == 3)
+            launch_b(K_NLIST, sph::k_tile_nlist<2, T>, wgs, sph::CfgD::kThreads, st, n, G, C, TL,
+                     skey(), pos(), cs, ce, L.cap, list(), lcnt(), count_pairs ? 1 : 0, pairs(), test);
         return launch_check("k_tile_nlist");
     }
     const uint32_t* list_or_null() const { return L.cap ? list() : nullptr; }
@@ -1010,13 +1017,29 @@ struct Engine {
     bool tiled() const { return kTileable && L.tiles.ntiles > 0; }
     uint32_t tcap() const { return L.cap & ~7u; }
     uint32_t* fbword() const { return (uint32_t*)(ws + L.flags + 4); }
-    // FP64: what tile_probe found, and the part of the targets that turns the
-    // tile passes off (see tiles_off)
+    // what tile_probe found: for the FP64 tile passes, or (the same boxes) the
+    // list tiles where lists are built
     uint32_t* found() const { return (uint32_t*)(ws + L.found); }
-    sph::TileProbe probe() const { return {L.tiles, tiled() && kF64 ? found() : nullptr}; }
+    sph::TileProbe probe() const {
+        if (tiled() && kF64) return {L.tiles, found()};
+        if (L.ltiles.ntiles > 0 && (!tiled() || L.adj_k > 0)) return {L.ltiles, found()};
+        return {L.tiles, nullptr};
+    }
     uint32_t off_part() const {
-        const double occ = (double)n / (double)ncells;
+        const double occ = (double)n / (double)real_cells(G);
         return (double)n * expected_neighbours(prm, G, occ) > 4e7 ? 4u : 4096u;
+    }
+    // k_tile_nlist: targets a tile needs for its work, targets times neighbours
+    // or cells times occupancy squared times the support in cells, to outweigh
+    // its staging and the 2 waves a SIMD: 8,500 (step with list tiles over one
+    // with walks at 113 targets of 58 neighbours 1.16 at 64^3, at 143 of 74 0.96,
+    // 216 of 113 0.6; partly filled the tiles with targets count), 2,000 up to
+    // 70,000 particles, where the walk has few waves (64 of 33 0.84), none up to 35,000.
+    uint32_t list_need() const {
+        const sph::Tiles& TL = L.ltiles;
+        if (n <= 35000 || prm->pair_tiles > 0) return 0;
+        const double work = n <= 70000 ? 2000.0 : 8500.0;
+        return (uint32_t)std::sqrt(work * (TL.tw * TL.th * TL.td) / expected_neighbours(prm, G, 1.0));
     }
     bool tiles_listed = false;  // a density pass followed the tile lists
     uint32_t tile_epoch = 0;
@@ -1034,7 +1057,7 @@ struct Engine {
                 launch_b(K_TILE_BUILD, sph::k_tile_build<decltype(R)::value, T>,
                          (unsigned)TL.ntiles, Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce,
                          tcap(), (uint4*)list(), lcnt(), count_pairs ? 1 : 0, pairs(), tile_epoch,
-                         fbword(), (const uint32_t*)(may_off ? found() : nullptr), off_part());
+                         fbword(), sph::TileTest{may_off ? found() : nullptr, off_part(), 0u});
             });
             SPH_TRY(launch_check("k_tile_build"));
             if (!with_density) return SPH_OK;
@@ -1044,7 +1067,7 @@ struct Engine {
                     launch_b(K_TILE_DENSITY, sph::k_tile_density64<S, KERNEL>, (unsigned)TL.ntiles,
                              Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
                              (const uint4*)list(), lcnt(), (double*)s.rho, (double*)s.p, vel(), rp(),
-                             with_eos ? 1 : 0, found(), off_part());
+                             with_eos ? 1 : 0, sph::TileTest{found(), off_part(), 0u});
                 else
                     launch_b(K_TILE_DENSITY, sph::k_tile_density<S, KERNEL>, (unsigned)TL.ntiles,
                              Cfg::kThreads, st, n, G, C, TL, TL.cap, pos(), cs, ce, tcap(),
@@ -1056,7 +1079,7 @@ struct Engine {
                 launch(K_TILE_FALLBACK, sph::k_tile_fallback_density<decltype(R)::value, KERNEL, T>,
                        fallback_blocks(n), st, n, G, C, skey(), pos(), cs, ce, lcnt(), tcap(),
                        list(), L.cap, (T*)s.rho, (T*)s.p, vel(), rp(), with_eos ? 1 : 0,
-                       count_pairs ? 1 : 0, pairs(), tile_epoch, fbword(), found(), off_part());
+                       count_pairs ? 1 : 0, pairs(), tile_epoch, fbword(), sph::TileTest{found(), off_part(), 0u});
             });
             return launch_check("k_tile_fallback_density");
         }
@@ -1082,7 +1105,7 @@ struct Engine {
                              sph::kMom64Threads, st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type,
                              cs, ce, tcap(), (const uint4*)list(), lcnt(), s, kick ? 1 : 0,
                              drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(), part,
-                             stride, found(), off_part());
+                             stride, sph::TileTest{found(), off_part(), 0u});
                 else
                     launch_b(K_TILE_MOMENTUM, sph::k_tile_momentum<S, KERNEL>, wgs, sph::kMomThreads,
                              st, n, G, C, TL, TL.cap, pos(), vel(), rp(), s.type, cs, ce, tcap(),
@@ -1096,7 +1119,7 @@ struct Engine {
                        skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(),
                        (const uint32_t*)(tiles_listed ? list() : nullptr), L.cap, s, kick ? 1 : 0,
                        drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(),
-                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword(), found(), off_part());
+                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword(), sph::TileTest{found(), off_part(), 0u});
             });
             SPH_TRY(launch_check("k_tile_fallback_momentum"));
             if (diag_out) diag_job = {stride, part, diag_out};
@@ -1142,7 +1165,8 @@ struct Engine {
     int pack(const sph::State& s, bool with_rp, const uint32_t* cs, const uint32_t* ce) {
         sph::TileProbe pb = probe();
         if (!cs) pb.found = nullptr;
-        launch(K_PACK, sph::k_pack<DIM, T>, blocks_for(n) + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st, n, s, G, skey(),
+        launch(K_PACK, sph::k_pack<DIM, T>,
+               blocks_for(n) + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st, n, s, G, skey(),
                pos(), vel(), rp(), with_rp ? 1 : 0, pb, cs, ce);
         return launch_check("k_pack");
     }
@@ -1191,18 +1215,18 @@ struct Engine {
     int neighbors(const sph_particles* pa, const uint32_t* cs, const uint32_t* ce, int64_t capacity,
                   int64_t* offsets, int32_t* nbr, int64_t* total) {
         const sph::State user = user_state(pa, prm);
-        SPH_TRY(pack(user, false, nullptr, nullptr));
         // Counts from the lists (filled from them below), or without lists
         // from a walk of the cells: where the lists' capacity would not do for
         // most (64^3, h = 1.8 dx: 1.48 ms with lists, 1.22 without), and in 2D
         // where a cell holds too few targets for the list build's wave (400^2,
         // h = 1.0 dx, 4 a cell: 0.119 ms, 0.106 without).
-        const double mean = (double)n / (double)ncells;
+        const double mean = (double)n / (double)real_cells(G);
         const double nb = expected_neighbours(prm, G, mean);
         const bool lists = L.cap && nb + std::sqrt(nb) <= (double)L.cap &&
                            !(DIM == 2 && mean >= 1.0 && mean < 5.0);
         if constexpr (kTileable)
             L.tiles = lists ? make_tiles(prm, G, n, ncells, true) : sph::Tiles{};
+        SPH_TRY(pack(user, false, lists && !tiled() ? cs : nullptr, ce));
         if (tiled()) {
             SPH_TRY(tile_lists(user, cs, ce, false, false, false, false));
             if constexpr (kTileable) {

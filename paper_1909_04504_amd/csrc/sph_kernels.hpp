@@ -1295,12 +1295,13 @@ __device__ __forceinline__ void tile_origin(const Tiles& TL, int t, int c0[3]) {
     c0[2] = (t / (TL.nt[0] * TL.nt[1])) * TL.td;
 }
 
-// What a sort, or the packing of a sorted state, finds out for the FP64 tile
-// passes that follow in kProbeBlocks more blocks (found == nullptr: nothing):
-// how many targets would be in tiles that overflow their staging, in a fluid
-// denser than the mean of its grid.  A wave looks at one tile in
-// every ntiles / 32; block b leaves the targets that overflow and all of them
-// in found[2 b] and found[2 b + 1].
+// What a sort, or the packing of a sorted state, finds out in kProbeBlocks
+// more blocks (found == nullptr: nothing) for the FP64 tile passes or the tiled
+// build of global-format lists that follow: how many targets would be in
+// tiles that overflow their staging, in a fluid denser than the mean of its
+// grid, and how many a tile has.  A wave looks at one tile in
+// every ntiles / 32; block b leaves the targets that overflow, all of them and
+// the tiles that have some in found[3 b ..].
 constexpr int kProbeBlocks = 8;
 struct TileProbe {
     Tiles TL;
@@ -1310,7 +1311,7 @@ template <typename Count>
 __device__ __forceinline__ void tile_probe(const TileProbe& P, const Grid& G, int b,
                                            Count&& count) {
     const Tiles& TL = P.TL;
-    __shared__ uint32_t over_[kBlock / 64], all_[kBlock / 64];
+    __shared__ uint32_t got_[3][kBlock / 64];
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
     constexpr int kTiles = kProbeBlocks * kBlock / 64;
     const int64_t t = (int64_t)(b * (kBlock / 64) + w) * TL.ntiles / kTiles;
@@ -1347,30 +1348,37 @@ __device__ __forceinline__ void tile_probe(const TileProbe& P, const Grid& G, in
         targets += (uint32_t)__shfl_xor((int)targets, d, 64);
     }
     if (lane == 0) {
-        over_[w] = total > (uint32_t)TL.cap ? targets : 0u;
-        all_[w] = targets;
+        got_[0][w] = total > (uint32_t)TL.cap ? targets : 0u;
+        got_[1][w] = targets;
+        got_[2][w] = targets ? 1u : 0u;
     }
     __syncthreads();
-    if (threadIdx.x < 2) {
-        const uint32_t* v = threadIdx.x == 0 ? over_ : all_;
+    if (threadIdx.x < 3) {
         uint32_t sum = 0;
-        for (int k = 0; k < kBlock / 64; ++k) sum += v[k];
-        P.found[2 * b + threadIdx.x] = sum;
+        for (int k = 0; k < kBlock / 64; ++k) sum += got_[threadIdx.x][k];
+        P.found[3 * b + threadIdx.x] = sum;
     }
 }
-// Whether the tile passes leave every target to the fallback: more than 1/part
-// of the targets looked at overflow.  The fallback's walks of a few targets take
-// as long as those of many up to some 10^5 (0.33 ms in both passes at
-// h = 1.5 dx), which only the gain of a large problem covers, so the host asks
-// for part = 4 there and for none at all (a large part) elsewhere.
-__device__ __forceinline__ bool tiles_off(const uint32_t* __restrict__ found, uint32_t part) {
-    uint64_t over = 0, all = 0;
+// Whether the tiles are left to the other way (the fallback of the FP64 tile
+// passes, the walk build of lists): more than 1/part of the targets looked at
+// overflow, or the tiles with targets have fewer than `need` on average.  The
+// walks of a few overflowing targets take as long as those of many up to some 10^5
+// (0.33 ms in both FP64 passes at h = 1.5 dx), which only the gain of a large
+// problem covers, so the host asks for part = 4 there and for none at all (a
+// large part) elsewhere.
+struct TileTest {
+    const uint32_t* found;
+    uint32_t part, need;
+};
+__device__ __forceinline__ bool tiles_off(const TileTest& T) {
+    uint64_t over = 0, all = 0, some = 0;
 #pragma unroll
     for (int b = 0; b < kProbeBlocks; ++b) {
-        over += found[2 * b];
-        all += found[2 * b + 1];
+        over += T.found[3 * b];
+        all += T.found[3 * b + 1];
+        some += T.found[3 * b + 2];
     }
-    return over * part > all;
+    return over * T.part > all || all < some * T.need;
 }
 
 // What the sort's gather does with particle i of src, whose slot is d and
@@ -1753,7 +1761,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(GatherArgs<DIM, T> A) {
         diag_sum<DIM>(A.job.nparts, A.job.part, A.job.out);
         return;
     }
-    if constexpr (DIM == 3 && sizeof(T) == 8)
+    if constexpr (DIM == 3)
         if ((int)blockIdx.x >= A.probe_block) {
             const uint32_t* __restrict__ counts = A.cl.counts;
             tile_probe(A.probe, A.G, (int)blockIdx.x - A.probe_block, [&](uint32_t key) { return counts[key]; });
@@ -1870,7 +1878,7 @@ __global__ __launch_bounds__(kBlock) void k_slot_gather(
     typename Vec4<T>::type* __restrict__ vel, uint8_t* __restrict__ type_tape, PairConst<T> C,
     typename Vec2<T>::type* __restrict__ rp, GatherOp op, uint32_t* __restrict__ counts,
     TileProbe probe) {
-    if constexpr (DIM == 3 && sizeof(T) == 8)
+    if constexpr (DIM == 3)
         if (probe.found && blockIdx.x >= gridDim.x - kProbeBlocks) {
             tile_probe(probe, G, (int)(blockIdx.x - (gridDim.x - kProbeBlocks)),
                        [&](uint32_t key) { return start[key + 1] - start[key]; });
@@ -1894,7 +1902,7 @@ __global__ __launch_bounds__(kBlock) void k_pack(int n, State S, Grid G,
                                                  int with_rp, TileProbe probe,
                                                  const uint32_t* __restrict__ cstart,
                                                  const uint32_t* __restrict__ cend) {
-    if constexpr (DIM == 3 && sizeof(T) == 8)
+    if constexpr (DIM == 3)
         if (probe.found && blockIdx.x >= gridDim.x - kProbeBlocks) {
             tile_probe(probe, G, (int)(blockIdx.x - (gridDim.x - kProbeBlocks)), [&](uint32_t key) {
                 const uint32_t b = cstart[key], e = cend[key];
@@ -2282,7 +2290,8 @@ __global__ __launch_bounds__(kBlock) void k_nlist(int n, uint32_t ncells, uint32
 // Neighbour lists of all particles (Sec. 2.2), one particle per lane: the
 // cell walk of walk_pairs, each accepted neighbour (self included) stored as
 // (j << bits) | code while the list has room; ncnt[i] = the full count.
-// Interaction counters as in k_nlist.
+// Interaction counters as in k_nlist.  With test.found, only if k_tile_nlist
+// leaves the lists to it.
 template <int DIM, int SR, typename T>
 __global__ __launch_bounds__(kBlock) void k_nlist_walk(int n, Grid G, PairConst<T> C,
                                                        const uint32_t* __restrict__ skey,
@@ -2291,7 +2300,9 @@ __global__ __launch_bounds__(kBlock) void k_nlist_walk(int n, Grid G, PairConst<
                                                        const uint32_t* __restrict__ cend,
                                                        uint32_t cap, uint32_t* __restrict__ list,
                                                        uint32_t* __restrict__ ncnt, int count_pairs,
-                                                       unsigned long long* __restrict__ pairs) {
+                                                       unsigned long long* __restrict__ pairs,
+                                                       TileTest test) {
+    if (DIM == 3 && test.found && !tiles_off(test)) return;
     using R = typename Rec<T>::type;
     const int blk = xcd_block();
     const int i = blk * kBlock + threadIdx.x;

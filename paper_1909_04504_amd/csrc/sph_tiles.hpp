@@ -705,8 +705,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
     const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
     const uint32_t* __restrict__ cend, uint32_t cap, uint4* __restrict__ list,
     uint32_t* __restrict__ ncnt, int count_pairs, unsigned long long* __restrict__ pairs,
-    uint32_t epoch, uint32_t* __restrict__ fallback, const uint32_t* __restrict__ found,
-    uint32_t part) {
+    uint32_t epoch, uint32_t* __restrict__ fallback, TileTest test) {
     using R = typename Rec<T>::type;
     using CFG = typename TileCfgOf<T>::type;
     constexpr int NT = CFG::kThreads;
@@ -726,7 +725,7 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
     // the cell-range loads go out before the empty-box probe, so that the
     // two round trips overlap
     const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
-    if (sizeof(T) == 8 && found && tiles_off(found, part)) return;
+    if (sizeof(T) == 8 && test.found && tiles_off(test)) return;
     if (tile_empty(G, TL, c0, cstart, cend)) {
         if (count_pairs) tile_count<NT>(0u, pairs, blk);
         return;
@@ -821,7 +820,8 @@ __global__ __launch_bounds__(CfgD::kThreads, 2) void k_tile_nlist(
     int n, Grid G, PairConst<T> C, Tiles TL, const uint32_t* __restrict__ skey, const typename Rec<T>::type* __restrict__ pos,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
     uint32_t* __restrict__ list, uint32_t* __restrict__ ncnt, int count_pairs,
-    unsigned long long* __restrict__ pairs) {
+    unsigned long long* __restrict__ pairs, TileTest test) {
+    if (tiles_off(test)) return;  // k_nlist_walk's
     using R = typename Rec<T>::type;
     using CFG = CfgD;
     using Code = NbrCode<3, S, T>;
@@ -1303,8 +1303,7 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
     const uint4* __restrict__ list, const uint32_t* __restrict__ ncnt,
     double* __restrict__ rho_out, double* __restrict__ p_out, double4* __restrict__ vel,
-    double2* __restrict__ rp, int with_eos, const uint32_t* __restrict__ found,
-    uint32_t part) {
+    double2* __restrict__ rp, int with_eos, TileTest test) {
     __shared__ TileMeta<CfgD> M;
     __shared__ PosD P;
     __shared__ uint8_t W[CfgD::kCap];
@@ -1313,7 +1312,7 @@ __global__ __launch_bounds__(CfgD::kThreads) void k_tile_density64(
     int c0[3];
     tile_origin(TL, blk, c0);
     const SetupLoads sl = tile_setup_loads(G, TL, c0, cstart, cend, (int)threadIdx.x);
-    if (tiles_off(found, part)) return;
+    if (tiles_off(test)) return;
     if (tile_empty(G, TL, c0, cstart, cend)) return;
     const uint32_t total = tile_setup_finish(G, TL, c0, n, sl, M, (int)threadIdx.x);
     if (total > (uint32_t)cap_union) return;  // every target is the fallback's
@@ -1370,8 +1369,7 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
     const uint32_t* __restrict__ cend, uint32_t cap, const uint4* __restrict__ list,
     const uint32_t* __restrict__ ncnt, State St, int kick, int drift, double hdt, double dt,
     CellList cl, uint32_t* __restrict__ flags,
-    double* __restrict__ diag_part, int stride, const uint32_t* __restrict__ found,
-    uint32_t part) {
+    double* __restrict__ diag_part, int stride, TileTest test) {
     __shared__ TileMeta<CfgD> MM[2];
     __shared__ uint16_t cellofs[2][CfgD::kCap];
     __shared__ PosD P;
@@ -1410,7 +1408,7 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
     // prologue (t = t0 - NP): tile t0 set up; the loop's first round stages it
     tile_origin(TL, t0, cs);
     tile_setup(G, TL, cs, cstart, cend, n, MM[0], tid);
-    if (tiles_off(found, part)) {  // the fallback's, all of them
+    if (tiles_off(test)) {  // the fallback's, all of them
         if (diag_part)
             for (int k = (int)threadIdx.x; t0 + (k >> 2) * NP < t1; k += kMom64Threads)
                 diag_part[(int64_t)(k & 3) * stride + t0 + (k >> 2) * NP] = 0.0;
@@ -1540,9 +1538,8 @@ __global__ __launch_bounds__(kBlock) void k_tile_fallback_density(
     uint32_t* __restrict__ list, uint32_t list_cap,
     T* __restrict__ rho_out, T* __restrict__ p_out, typename Vec4<T>::type* __restrict__ vel,
     typename Vec2<T>::type* __restrict__ rp, int with_eos, int count_pairs, unsigned long long* __restrict__ pairs,
-    uint32_t epoch, const uint32_t* __restrict__ fallback, const uint32_t* __restrict__ found,
-    uint32_t part) {
-    const bool all = sizeof(T) == 8 && tiles_off(found, part);
+    uint32_t epoch, const uint32_t* __restrict__ fallback, TileTest test) {
+    const bool all = sizeof(T) == 8 && tiles_off(test);
     if (!all && *fallback != epoch) return;
     uint32_t counted = 0;
     if (all) {
@@ -1591,10 +1588,9 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 && S == 1 ? 3 : 1) void k_ti
     const uint32_t* __restrict__ list, uint32_t list_cap, State St,
     int kick, int drift, double hdt, double dt, CellList cl, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
     int stride, uint32_t epoch, const uint32_t* __restrict__ fallback,
-    const uint32_t* __restrict__ found,
-    uint32_t part) {
+    TileTest test) {
     double dsum[4] = {0.0, 0.0, 0.0, 0.0};
-    const bool all = sizeof(T) == 8 && tiles_off(found, part);
+    const bool all = sizeof(T) == 8 && tiles_off(test);
     if (all || *fallback == epoch) {
         if (!all) list = nullptr;
         for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
