@@ -117,10 +117,12 @@ typedef struct {
                            * at least one particle per cell on average
                            * (default), < 0 = never (lists read from global
                            * memory), k > 0 = used wherever they apply, with at
-                           * most k staged particles per box (3072 at most,
-                           * 2000 in FP64;
-                           * larger boxes take the cell walk).  Results do not
-                           * depend on it. */
+                           * most k staged particles per box (3072 at most, 2000
+                           * in FP64 and where global-format lists are built;
+                           * larger boxes take the cell walk).  In FP64 the
+                           * default also asks for enough particles per box,
+                           * and leaves them where the fluid would overflow
+                           * most.  Results do not depend on it. */
     int32_t cell_order;   /* sort key of the cells (Section 2.2): 0 = row-major,
                            * x fastest (default); 1 = Z-order (Morton, the
                            * bits of the three cell coordinates interleaved,

@@ -38,6 +38,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sph_math.hpp"
+
 namespace sph {
 
 constexpr int kBlock = 256;          // threads per workgroup (4 waves of 64)
@@ -228,39 +230,17 @@ __device__ __forceinline__ double geom_r2d(const Geom<float>& g, const PairConst
 
 // ---------------------------------------------------------------------------
 // Precision-generic helpers.  Mixed precision uses the hardware square root
-// and reciprocal (1 ulp).  FP64 starts from the hardware's approximations
-// (v_rcp_f64, v_rsq_f64: about 26 bits) and takes one correction of third order
-// (with e = 1 - x y the reciprocal is y (1 + e + e^2 + ..), with e = 1 - x y^2
-// the reciprocal square root y (1 + e/2 + 3 e^2/8 + ..)), the square root
-// two steps of Newton's iteration with an exact residual: 4, 6 and 8
-// instructions where the correctly rounded division and square root take
-// about 12 and 18, and at most one unit in the last place from the exact
-// value (over 2^-60 .. 2^20: 0.50, 0.99 and 0.50 units; 1 / sqrt(x) rounded
-// twice 1.49).  The arguments are positive and finite: |r| and |r|^2 of
+// and reciprocal (1 ulp), FP64 the hardware's approximations with one
+// correction (sph_math.hpp).  The arguments are positive and finite: |r| and |r|^2 of
 // accepted pairs (at least the smallest normal number, tiny_normal), sums of
 // densities and |r|^2 + eta h^2 (at least 1e-200 h^2); an infinite density makes
 // its pressure term NaN in either form.
 __device__ __forceinline__ float p_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double p_sqrt(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    const double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    return fma(fma(-g, g, x), h, g);
-}
+__device__ __forceinline__ double p_sqrt(double x) { return sqrt_from(x, __builtin_amdgcn_rsq(x)); }
 __device__ __forceinline__ float p_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double p_rcp(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, y, 1.0);
-    return fma(fma(e, e, e), y, y);
-}
+__device__ __forceinline__ double p_rcp(double x) { return rcp_from(x, __builtin_amdgcn_rcp(x)); }
 __device__ __forceinline__ float p_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double p_rsqrt(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
+__device__ __forceinline__ double p_rsqrt(double x) { return rsqrt_from(x, __builtin_amdgcn_rsq(x)); }
 template <typename T> __device__ __forceinline__ T tiny_normal();
 template <> __device__ __forceinline__ float tiny_normal<float>() { return 1.17549435e-38f; }
 template <> __device__ __forceinline__ double tiny_normal<double>() { return 2.2250738585072014e-308; }
