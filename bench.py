@@ -110,7 +110,8 @@ def source_digest() -> str:
     """Digest of the library's device and launch sources (the traffic of a
     profiled kernel is used only while it matches)."""
     h = hashlib.sha256()
-    for f in ("sph_kernels.hpp", "sph_tiles.hpp", "sph_adjoint.hpp", "sph_engine.hpp", "sph.hip"):
+    for f in ("sph_math.hpp", "sph_kernels.hpp", "sph_tiles.hpp", "sph_adjoint.hpp",
+              "sph_engine.hpp", "sph.hip"):
         with open(os.path.join(ROOT, "paper_1909_04504_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

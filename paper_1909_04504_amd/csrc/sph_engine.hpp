@@ -500,8 +500,8 @@ struct SlotOff {
 };
 
 struct Layout {
-    size_t flags, found, counts, counts2, head, table, start, chunks, sub, next, listed, rank, tmp, perm, skey,
-        lcnt, list;
+    size_t flags, found, counts, counts2, head, table, start, chunks, sub, next, listed, rank;
+    size_t tmp, perm, skey, lcnt, list;
     uint32_t cap;
     SortShape sort;
     sph::Tiles tiles, ltiles;
@@ -926,8 +926,9 @@ struct Engine {
             launch(K_CELL_PLACE, sph::k_cell_place, cb + blocks_for(n), st, n, cb, SG, cells(),
                    start(), skey(), tmp);
             SPH_TRY(launch_check("k_cell_place"));
-            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n) + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st,
-                   n, tmp, start(), src, dst, G, perm(), op.want_perm ? 1 : 0, skey(), pos(), vel(),
+            const unsigned probing = pb.found ? (unsigned)sph::kProbeBlocks : 0u;
+            launch(K_CELL_GATHER, sph::k_slot_gather<DIM, T>, blocks_for(n) + probing, st, n,
+                   tmp, start(), src, dst, G, perm(), op.want_perm ? 1 : 0, skey(), pos(), vel(),
                    typetape, C, rp(), go, counts(cbuf), pb);
             return launch_check("k_slot_gather");
         }
@@ -935,7 +936,8 @@ struct Engine {
         // first launch of the sort)
         const bool dg = diag_job.nparts > 0;
         const unsigned nb = (unsigned)sh.nblocks + (dg ? 1u : 0u);
-        launch(K_CELL_GATHER, sph::k_cell_gather<DIM, T>, nb + (pb.found ? (unsigned)sph::kProbeBlocks : 0u), st,
+        const unsigned probing = pb.found ? (unsigned)sph::kProbeBlocks : 0u;
+        launch(K_CELL_GATHER, sph::k_cell_gather<DIM, T>, nb + probing, st,
                sph::GatherArgs<DIM, T>{n, SG, cells(), src, dst, G, start(), tmp, perm(),
                                        op.want_perm ? 1 : 0, skey(), pos(), vel(), typetape, C, rp(),
                                        go, diag_job, (int)nb, pb});
@@ -1079,7 +1081,8 @@ struct Engine {
                 launch(K_TILE_FALLBACK, sph::k_tile_fallback_density<decltype(R)::value, KERNEL, T>,
                        fallback_blocks(n), st, n, G, C, skey(), pos(), cs, ce, lcnt(), tcap(),
                        list(), L.cap, (T*)s.rho, (T*)s.p, vel(), rp(), with_eos ? 1 : 0,
-                       count_pairs ? 1 : 0, pairs(), tile_epoch, fbword(), sph::TileTest{found(), off_part(), 0u});
+                       count_pairs ? 1 : 0, pairs(), tile_epoch, fbword(),
+                       sph::TileTest{found(), off_part(), 0u});
             });
             return launch_check("k_tile_fallback_density");
         }
@@ -1119,7 +1122,8 @@ struct Engine {
                        skey(), pos(), vel(), rp(), s.type, cs, ce, lcnt(), tcap(),
                        (const uint32_t*)(tiles_listed ? list() : nullptr), L.cap, s, kick ? 1 : 0,
                        drift ? 1 : 0, 0.5 * prm->dt, prm->dt, cells(), flags(),
-                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword(), sph::TileTest{found(), off_part(), 0u});
+                       part ? part + TL.ntiles : nullptr, stride, tile_epoch, fbword(),
+                       sph::TileTest{found(), off_part(), 0u});
             });
             SPH_TRY(launch_check("k_tile_fallback_momentum"));
             if (diag_out) diag_job = {stride, part, diag_out};

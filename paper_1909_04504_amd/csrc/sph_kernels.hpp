@@ -1744,7 +1744,8 @@ __global__ __launch_bounds__(kBlock) void k_cell_gather(GatherArgs<DIM, T> A) {
     if constexpr (DIM == 3)
         if ((int)blockIdx.x >= A.probe_block) {
             const uint32_t* __restrict__ counts = A.cl.counts;
-            tile_probe(A.probe, A.G, (int)blockIdx.x - A.probe_block, [&](uint32_t key) { return counts[key]; });
+            tile_probe(A.probe, A.G, (int)blockIdx.x - A.probe_block,
+                       [&](uint32_t key) { return counts[key]; });
             return;
         }
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
@@ -2474,8 +2475,8 @@ __device__ __forceinline__ void momentum_one(
     const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, int n,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap,
-    const State& S, int kick, int drift, double hdt, double dt, CellList cl, uint32_t* __restrict__ flags, bool diag,
-    double dv[1 + DIM]) {
+    const State& S, int kick, int drift, double hdt, double dt, CellList cl,
+    uint32_t* __restrict__ flags, bool diag, double dv[1 + DIM]) {
     const bool fluid = type[i] == 0;
     T acc[3] = {T(0), T(0), T(0)};
     if (fluid) {
@@ -2551,8 +2552,8 @@ __global__ __launch_bounds__(kBlock) void k_cont_momentum(
     const typename Vec2<T>::type* __restrict__ rp, const uint8_t* __restrict__ type,
     const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ ncnt, uint32_t cap, State S,
-    int euler, int kick, int drift, double dt, CellList cl, uint32_t* __restrict__ flags, double* __restrict__ diag_part,
-    int count_pairs,
+    int euler, int kick, int drift, double dt, CellList cl, uint32_t* __restrict__ flags,
+    double* __restrict__ diag_part, int count_pairs,
     unsigned long long* __restrict__ pairs) {
     const int blk = xcd_block();
     const int i = blk * kBlock + threadIdx.x;

@@ -571,8 +571,8 @@ __device__ __forceinline__ uint4 ring_octet(const uint2* myring, uint32_t k8) {
 // exact(u) is the predicate inside the band.  Entries are appended without
 // branches: every candidate is written at the next free place and the count
 // advances only for accepted ones.
-// Instruction issue and the LDS bound it (97% and 90% of the build's time), so
-// the groups must fill the lanes: with half-size cells the rows of a stencil
+// VALU issue and the LDS bound it (busy 97% and 90% of the 256^3 cube's build),
+// so the groups must fill the lanes: with half-size cells the rows of a stencil
 // plane form a queue in registers, and a lane that ends a row goes on with its
 // next one while others are still in theirs.  A wave of the 256^3 cube then
 // takes 101 groups instead of the 134 of lanes that wait for the longest row
@@ -802,24 +802,25 @@ __global__ __launch_bounds__(TileCfgOf<T>::type::kThreads) void k_tile_build(
 }
 
 // Neighbour lists in the global format (k_nlist_walk's, entry for entry):
-// candidates from the union staged in LDS instead of a walk of each particle's cells through L1
-// and L2.  Each staged particle has its list word for a target in union cell
-// 0, to which a target adds a constant: the mixed-precision code of a stencil
-// offset is linear in the two cells, the FP64 code is the neighbour's image
-// alone.  Completed octets of union indices are turned into words and stored,
-// 256 bytes apart (rows of 64 slots), after a group of candidates that leaves
-// some lane with kFlush of them or more, by the lanes of a wave together: at
-// every completed octet some lane or other would take the whole wave through
-// the stores.  The targets of a tile whose union does
-// not fit (or, in FP64, holds a particle far outside its cell) walk the
-// cells.  Workgroup b takes every gridDim-th tile and adds the interactions it
-// counted to pairs[b].
+// candidates from the union staged in LDS instead of a walk of each
+// particle's cells through L1 and L2.  Each staged particle has its list word
+// for a target in union cell 0, to which a target adds a constant: the
+// mixed-precision code of a stencil offset is linear in the two cells, the
+// FP64 code is the neighbour's image alone.  Completed octets of union indices
+// are turned into words and stored, 256 bytes apart (rows of 64 slots), after
+// a group of candidates that leaves some lane with kFlush of them or more, by
+// the lanes of a wave together: at every completed octet some lane or other
+// would take the whole wave through the stores.  The targets of a tile whose
+// union does not fit (or, in FP64, holds a particle far outside its cell) walk
+// the cells.  Workgroup b takes every gridDim-th tile and adds the
+// interactions it counted to pairs[b].
 // Boxes of 4 x 4 x 4 half-size cells and 256 threads, two workgroups per CU.
 template <int S, typename T>
 __global__ __launch_bounds__(CfgD::kThreads, 2) void k_tile_nlist(
-    int n, Grid G, PairConst<T> C, Tiles TL, const uint32_t* __restrict__ skey, const typename Rec<T>::type* __restrict__ pos,
-    const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ cend, uint32_t cap,
-    uint32_t* __restrict__ list, uint32_t* __restrict__ ncnt, int count_pairs,
+    int n, Grid G, PairConst<T> C, Tiles TL, const uint32_t* __restrict__ skey,
+    const typename Rec<T>::type* __restrict__ pos, const uint32_t* __restrict__ cstart,
+    const uint32_t* __restrict__ cend, uint32_t cap, uint32_t* __restrict__ list,
+    uint32_t* __restrict__ ncnt, int count_pairs,
     unsigned long long* __restrict__ pairs, TileTest test) {
     if (tiles_off(test)) return;  // k_nlist_walk's
     using R = typename Rec<T>::type;
@@ -1105,7 +1106,7 @@ __global__ __launch_bounds__(CfgF::kThreads) void k_tile_density(
 // alternate.  The loads wait in waves of their own since a wave's loads
 // return in order: held by the target waves they stood before the pair loops'
 // first wait, and their 60 registers beside the pair loops'.  The pair loops
-// take half octets at a time and issue instructions 79% of the time.
+// take half octets at a time; the VALU is busy 83% of the time, the LDS 61%.
 // (256^3 cube: 3.83 ms with the loads in the target waves, 3.64 with the loader
 // waves; 75^3 quintic lattice 0.213 and 0.204.  Padded lists without the
 // entry-by-entry tail, as in FP64: 3.55 and 0.209, not taken.)
@@ -1515,7 +1516,8 @@ __global__ __launch_bounds__(kMom64Threads) void k_tile_momentum64(
                     acc[2] = az;
                 }
                 double dv[4] = {0.0, 0.0, 0.0, 0.0};
-                momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, cl, flags, diag_part != nullptr, dv, &ci);
+                momentum_close<3, double>((int)i, acc, fluid, St, G, kick, drift, hdt, dt, cl,
+                                          flags, diag_part != nullptr, dv, &ci);
                 for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
             }
         }
@@ -1597,7 +1599,8 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 && S == 1 ? 3 : 1) void k_ti
             if (!all && ncnt[i] <= cap) continue;
             double dv[4] = {0.0, 0.0, 0.0, 0.0};
             momentum_one<3, S, KERNEL, T>(i, G, C, skey, pos, vel, rp, type, cstart, cend, n,
-                                          list, ncnt, list_cap, St, kick, drift, hdt, dt, cl, flags, diag_part != nullptr, dv);
+                                          list, ncnt, list_cap, St, kick, drift, hdt, dt, cl, flags,
+                                          diag_part != nullptr, dv);
             for (int q = 0; q < 4; ++q) dsum[q] += dv[q];
         }
     }
