@@ -1476,7 +1476,7 @@ __device__ __forceinline__ bool slot_one(uint32_t s, const uint32_t* tmp, const 
 // goes in three parts instead, each spread over several blocks (heaped_sort):
 // the lists' particles go to their cells' slots, then the listed ones, then
 // each slot is ranked and gathered by a thread of its own.
-constexpr int kSortEntries = 768;
+constexpr int kSortEntries = 640;
 constexpr int kSortRounds = 4;  // table entries of a wave's cells: at most 64 kSortRounds
 struct SortGrid {
     int64_t ncells;
@@ -1730,8 +1730,11 @@ __device__ __attribute__((noinline)) void heaped_sort(uint32_t over_, uint64_t a
                              A.vel, A.type_tape, A.C, A.rp, A.op);
 }
 
+// Six waves per SIMD (heaped_sort's registers are held to them, and the LDS of
+// kSortEntries leaves six blocks a CU): 256^3 cube 757 us against 826 with
+// five (768 entries), 160^3 FP64 210 and 222.
 template <int DIM, typename T>
-__global__ __launch_bounds__(kBlock) void k_cell_gather(GatherArgs<DIM, T> A) {
+__global__ __launch_bounds__(kBlock, 6) void k_cell_gather(GatherArgs<DIM, T> A) {
     constexpr int kWaves = kBlock / 64;
     __shared__ uint32_t ent_[kWaves][kSortEntries], sorted_[kWaves][kSortEntries];
     __shared__ uint8_t cellof_[kWaves][kSortEntries];
